@@ -186,7 +186,8 @@ void pivot_fc_plan_destroy(pivot_fc_plan_t* plan);   /* NULL-safe */
 
 /* Scratch a run needs for `batch` rows: arrival counters of split block rows
  * (first; their size does not depend on the batch), their partial sums, and
- * for the matrix-core form that wants it a copy of x in block order.
+ * for the batched matrix-core form a copy of x in the order its fragments are
+ * read in.
  * Reuse rule: clear the buffer once with pivot_workspace_init before its first
  * use with a plan; after that any number of runs of THAT plan may share it, in
  * any order of batch sizes (every run leaves the counters at zero, nothing
@@ -212,7 +213,13 @@ int    pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream);
  *          plan's source-ordered lists) while the staged rows of a work item
  *          fit in 48 KB (beyond batch 16: and the launch rows together
  *          stage at most 5120 columns per work item), else (batch >= 8)
- *          from a copy of x in block order made by one small extra kernel.
+ *          from a copy of x in the order the fragments are read in, made by
+ *          one small extra kernel.  That form takes every tile shape and both
+ *          types, from batch 3 on, wherever the others would stream or gather
+ *          much more than once (F32 and small F16 tiles: 12 MB of weights
+ *          times further groups of four batch rows); chains and the
+ *          recurrent loop, whose kernels produce that order, use it behind
+ *          every boundary from batch 2 on.
  *          Batch 5..16 with at most 4096 input columns, from a quarter of
  *          them staged per work item on: the rows of x are copied into
  *          LDS and the fragments gathered from there (fastest when x is
@@ -236,7 +243,7 @@ int  pivot_fc_kernel_name(const pivot_fc_plan_t* plan, int batch, char* buf, siz
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
  * kernels, same result bits as pivot_fc_run without the workspace: the scratch
  * of the run (arrival counters and partial sums of split block rows, the
- * block-order copy of x of the matrix-core form that wants one) is a fixed
+ * copy of x of the batched matrix-core form, where it fits) is a fixed
  * array in device memory that belongs to the library, PIVOT_STATIC_COUNTER_BYTES
  * + PIVOT_STATIC_DATA_BYTES = 16 MiB on every GPU the library runs on, held
  * until the process ends.  The call allocates and frees nothing and never

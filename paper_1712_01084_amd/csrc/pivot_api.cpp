@@ -188,7 +188,7 @@ void pivot_fc_plan_destroy(pivot_fc_plan_t* plan) {
 
 size_t pivot_fc_workspace_bytes(const pivot_fc_plan_t* plan, int batch) {
     if (!plan || batch < 1) return 0;
-    return fc_workspace_bytes(plan->host, batch) + fc_gather_bytes(plan->host, batch);
+    return fc_ticket_bytes(plan->host) + fc_partial_bytes(plan->host, batch, kXNatural) + fc_gather_bytes(plan->host, batch);
 }
 
 int pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream) {
@@ -202,12 +202,12 @@ namespace {
 
 // Fills the plan-dependent part of a launch.  `tickets`: fc_ticket_bytes(plan) of arrival counters that are zero
 // between runs; `partials`: fc_partial_bytes(plan, batch) of scratch (both may be NULL when the size is 0).
-int prepare(const pivot_fc_plan_t* plan, int batch, void* tickets, void* partials, FcLaunch& L) {
+int prepare(const pivot_fc_plan_t* plan, int batch, void* tickets, void* partials, int x_from, FcLaunch& L) {
     if (!plan) { set_error("plan is NULL"); return PIVOT_E_NULL; }
     if (plan->device < 0) { set_error("host-only plan (device = -1) cannot run"); return PIVOT_E_NO_DEVICE; }
     if (batch < 1 || batch > 64) { set_error("batch %d outside 1..64", batch); return PIVOT_E_SHAPE; }
     const HostPlan& h = plan->host;
-    if ((fc_ticket_bytes(h) > 0 && !tickets) || (fc_partial_bytes(h, batch) > 0 && !partials)) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
+    if ((fc_ticket_bytes(h) > 0 && !tickets) || (fc_partial_bytes(h, batch, x_from) > 0 && !partials)) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
     if (reinterpret_cast<uintptr_t>(tickets) % 16 != 0 || reinterpret_cast<uintptr_t>(partials) % 16 != 0) { set_error("workspace must be 16-byte aligned"); return PIVOT_E_WORKSPACE; }
     const DevPlan& d = plan->dev;
     L.vals = d.vals; L.col_idx = d.col_idx; L.chunks = d.chunks; L.part_base = d.part_base; L.bias_p = d.bias_p;
@@ -215,7 +215,7 @@ int prepare(const pivot_fc_plan_t* plan, int batch, void* tickets, void* partial
     L.M_pad = h.M_pad; L.K_pad = h.K_pad; L.bh = h.d.bh; L.bw = h.d.bw; L.wdtype = h.d.wdtype; L.layout = h.d.layout; L.T = h.T; L.act = h.d.act;
     L.nchunks = h.nchunks; L.nbr = h.nbr; L.chunk_tiles = h.chunk_tiles; L.wg_waves = h.wg_waves;
     L.lds_tiles = h.lds_tiles(); L.xrow_len = h.xrow_len();
-    L.row_slices = h.row_slices;
+    L.row_slices = h.row_slices; L.x_from = x_from;
     L.uniform_ct = h.uniform_ct; L.uniform_parts = h.uniform_parts;
     L.batch = batch;
     L.tickets = reinterpret_cast<uint32_t*>(tickets);
@@ -224,13 +224,13 @@ int prepare(const pivot_fc_plan_t* plan, int batch, void* tickets, void* partial
 }
 
 // Input side of a launch whose x is in natural order: the vector kernel
-// gathers through the composed index array; the matrix-core kernel wants block
+// gathers through the composed index array; the batched matrix-core kernel wants fragment
 // order, so x is copied there first (`xg`: fc_gather_bytes of scratch).
 int natural_input(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, int batch, void* xg, void* stream,
                   FcLaunch& L) {
     const HostPlan& h = plan->host;
-    if (fc_uses_matrix_cores(fc_shape(h), batch)) {
-        int rc = launch_gather_x(x_dev, ldx, plan->dev.pcol_pad, xg, h.K_pad, batch, h.d.wdtype, stream);
+    if (fc_wants_frag(fc_shape(h, L.x_from), batch)) {
+        int rc = launch_gather_frag(x_dev, ldx, plan->dev.pcol_pad, xg, h.d.K, h.K_pad, batch, h.d.wdtype, stream);
         if (rc != PIVOT_OK) return rc;
         L.x = xg; L.ldx = h.K_pad; L.xidx = plan->dev.xidx_blk; L.xsort = plan->host.sorted_ok ? plan->dev.xsort_blk : nullptr; L.x_block_order = 1;
     } else {
@@ -244,13 +244,13 @@ int natural_input(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, i
 namespace pivot {
 
 int run_layer(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, void* y_dev, int64_t ldy, int batch,
-              void* tickets, void* partials, void* xg, void* stream) {
+              void* tickets, void* partials, void* xg, void* stream, int x_from) {
     FcLaunch L{};
-    int rc = prepare(plan, batch, tickets, partials, L);
+    int rc = prepare(plan, batch, tickets, partials, x_from, L);
     if (rc != PIVOT_OK) return rc;
     if (!x_dev || !y_dev) { set_error("x_dev and y_dev are required"); return PIVOT_E_NULL; }
     if (ldx < plan->host.d.K || ldy < plan->host.d.M) { set_error("ldx/ldy smaller than K/M"); return PIVOT_E_SHAPE; }
-    if (fc_gather_bytes(plan->host, batch) > 0 && !xg) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
+    if (x_from == kXNatural && fc_gather_bytes(plan->host, batch) > 0 && !xg) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
     rc = natural_input(plan, x_dev, ldx, batch, xg, stream, L);
     if (rc != PIVOT_OK) return rc;
     L.scatter = plan->dev.prow_pad;
@@ -268,7 +268,7 @@ int pivot_fc_run(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, vo
     if (plan->device < 0) { set_error("host-only plan (device = -1) cannot run"); return PIVOT_E_NO_DEVICE; }
     if (batch < 1 || batch > 64) { set_error("batch %d outside 1..64", batch); return PIVOT_E_SHAPE; }
     const HostPlan& h = plan->host;
-    const size_t nt = fc_ticket_bytes(h), np = fc_partial_bytes(h, batch), ng = fc_gather_bytes(h, batch);
+    const size_t nt = fc_ticket_bytes(h), np = fc_partial_bytes(h, batch, kXNatural), ng = fc_gather_bytes(h, batch);
     if (nt + np + ng > 0 && (!ws_dev || ws_bytes < nt + np + ng)) {
         set_error("workspace too small: need %zu bytes, got %zu", nt + np + ng, ws_dev ? ws_bytes : (size_t)0);
         return PIVOT_E_WORKSPACE;
@@ -391,16 +391,20 @@ namespace {
 // copy of x (matrix path)] [intermediate 0] ...  The counters come first and their sizes do not depend on the
 // batch, so they are only ever touched as counters, whatever batches the workspace is reused with (they rely on
 // being zero between launches; every run leaves them so).  Every layer has its own.
-// Intermediate l holds batch rows of K_pad_{l+1} elements of wdtype in the consumer's block order; its padding
-// columns are never read by the kernels that stage x in LDS (their gather index is -1 there) and are cleared
-// before a kernel that reads the rows directly.
+// Intermediate l holds batch rows of K_pad_{l+1} elements of wdtype in the consumer's block order, or in fragment
+// order if that is what the consumer's kernel reads; its padding columns are never read by the kernels that stage x
+// in LDS (their gather index is -1 there) and are cleared by the producer for the kernel that reads them (against
+// zero weights: they must hold finite values, whatever the workspace held before).
 struct MlpLayout { size_t gather_off, total; std::vector<size_t> inter_off, ticket_off, partial_off; };
 
 MlpLayout mlp_layout(const pivot_mlp_plan_t* mp, int batch) {
     MlpLayout m{0, 0, {}, {}, {}};
     size_t off = 0;
     for (auto* l : mp->layers) { m.ticket_off.push_back(off); off += align_up(fc_ticket_bytes(l->host), 256); }
-    for (auto* l : mp->layers) { m.partial_off.push_back(off); off += align_up(fc_partial_bytes(l->host, batch), 256); }
+    for (size_t l = 0; l < mp->layers.size(); ++l) {
+        m.partial_off.push_back(off);
+        off += align_up(fc_partial_bytes(mp->layers[l]->host, batch, l == 0 ? kXNatural : kXBlock), 256);
+    }
     m.gather_off = off;
     off += fc_gather_bytes(mp->layers[0]->host, batch);
     for (size_t l = 0; l + 1 < mp->layers.size(); ++l) {
@@ -458,7 +462,7 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
     for (int l = 0; l < Lc; ++l) {
         const pivot_fc_plan_t* p = plan->layers[l];
         FcLaunch L{};
-        int rc = prepare(p, batch, ws + m.ticket_off[l], ws + m.partial_off[l], L);
+        int rc = prepare(p, batch, ws + m.ticket_off[l], ws + m.partial_off[l], l == 0 ? kXNatural : kXBlock, L);
         if (rc != PIVOT_OK) return rc;
         L.stream = stream;
         if (l == 0) {
@@ -466,10 +470,6 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
             if (rc != PIVOT_OK) return rc;
         } else {
             L.xidx = p->dev.xidx_blk; L.xsort = p->host.sorted_ok ? p->dev.xsort_blk : nullptr; L.x = ws + m.inter_off[l - 1]; L.ldx = p->host.K_pad; L.x_block_order = 1;
-            // the kernel that reads its B fragments straight from the rows also reads the padding columns
-            // (against zero weights): they must hold finite values, whatever the workspace held before
-            if (p->host.K_pad > p->host.d.K && fc_uses_matrix_cores(fc_shape(p->host), batch) &&
-                (rc = launch_zero_pad_cols(ws + m.inter_off[l - 1], p->host.d.K, p->host.K_pad, batch, elem_size(p->host.d.wdtype), stream)) != PIVOT_OK) return rc;
         }
         if (l + 1 < Lc) {
             // producer-side store through the composed boundary array; identity boundaries store contiguously
@@ -477,6 +477,10 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
             L.y = ws + m.inter_off[l];
             L.ldy = plan->layers[l + 1]->host.K_pad;
             L.out_f16 = (p->host.d.wdtype == PIVOT_F16);
+            const HostPlan& next = plan->layers[l + 1]->host;
+            if (fc_wants_frag(fc_shape(next, kXBlock), batch)) {
+                L.out_frag = 1; L.zero_from = next.d.K; L.zero_to = next.K_pad;
+            }
         } else {
             L.scatter = keep ? p->dev.rowid_pad : p->dev.prow_pad;
             L.y = y_dev; L.ldy = ldy; L.out_f16 = 0;
@@ -522,7 +526,7 @@ struct LstmLayout { size_t tickets, scratch, z_off, ctl_off, part_off, xg_off, x
 LstmLayout lstm_layout(const pivot_fc_plan_t* p, int steps, int batch) {
     LstmLayout m{};
     m.tickets = fc_ticket_bytes(p->host);
-    m.scratch = align_up(fc_workspace_bytes(p->host, batch), 256);
+    m.scratch = align_up(m.tickets + fc_partial_bytes(p->host, batch, kXBlock), 256);
     m.z_off = m.scratch;
     m.ctl_off = m.z_off + align_up((size_t)batch * p->host.d.M * 4, 256);
     m.part_off = m.ctl_off + kLstmCtlBytes;
@@ -573,23 +577,20 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
         P.H = H; P.I = I; P.batch = batch; P.steps = steps; P.device = plan->device; P.stream = stream;
         return launch_lstm_persist(P);
     }
-    // one layer launch and one cell launch per step
-    if ((rc = launch_fill_zero(ws + m.ctl_off, kLstmCtlBytes, stream)) != PIVOT_OK) return rc;
-    // block-order inputs of all steps: padding zero, x_t placed once, h_0 placed into step 0
-    if ((rc = launch_fill_zero(xg, m.xg_step * (size_t)steps, stream)) != PIVOT_OK) return rc;
-    if (m.xg_step != (size_t)batch * h.K_pad * elem_size(h.d.wdtype)) {
-        // steps are padded apart: place step by step
-        for (int t = 0; t < steps; ++t) {
-            const char* xs_t = reinterpret_cast<const char*>(xs_dev) + (size_t)t * batch * I * elem_size(h.d.wdtype);
-            if ((rc = launch_lstm_place_inputs(xs_t, xg + m.xg_step * (size_t)t, plan->dev.invpcol, H, I, h.K_pad, 1, batch, h.d.wdtype, stream)) != PIVOT_OK) return rc;
-        }
-    } else {
-        if ((rc = launch_lstm_place_inputs(xs_dev, xg, plan->dev.invpcol, H, I, h.K_pad, steps, batch, h.d.wdtype, stream)) != PIVOT_OK) return rc;
+    // one layer launch and one cell launch per step, behind one that places the inputs of all steps
+    const int frag = fc_wants_frag(fc_shape(h, kXBlock), batch) ? 1 : 0;
+    for (int t = 0; t < steps; t += 65535) {
+        // (the step is a grid dimension of at most 65535; what a later piece places for its first h is overwritten by the cell)
+        LstmInputsLaunch N{};
+        N.pcol_pad = plan->dev.pcol_pad; N.xs = reinterpret_cast<const char*>(xs_dev) + (size_t)t * batch * I * elem_size(h.d.wdtype);
+        N.h0 = h_dev; N.xg = xg + m.xg_step * (size_t)t; N.ctl = reinterpret_cast<uint32_t*>(ws + m.ctl_off);
+        N.xg_step_bytes = m.xg_step; N.H = H; N.I = I; N.K_pad = h.K_pad; N.steps = std::min(65535, steps - t); N.batch = batch;
+        N.wdtype = h.d.wdtype; N.frag = frag; N.stream = stream;
+        if ((rc = launch_lstm_inputs(N)) != PIVOT_OK) return rc;
     }
-    if ((rc = launch_lstm_place_state(h_dev, xg, plan->dev.invpcol, H, h.K_pad, batch, h.d.wdtype, stream)) != PIVOT_OK) return rc;
     for (int t = 0; t < steps; ++t) {
         FcLaunch L{};
-        rc = prepare(plan, batch, ws, ws + m.tickets, L);
+        rc = prepare(plan, batch, ws, ws + m.tickets, kXBlock, L);
         if (rc != PIVOT_OK) return rc;
         L.xidx = plan->dev.xidx_blk; L.xsort = plan->host.sorted_ok ? plan->dev.xsort_blk : nullptr; L.x_block_order = 1;
         L.x = xg + m.xg_step * (size_t)t; L.ldx = h.K_pad;
@@ -601,7 +602,7 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
         C.h = h_dev; C.c = c_dev;
         C.xg_next = (t + 1 < steps) ? (void*)(xg + m.xg_step * (size_t)(t + 1)) : nullptr;
         C.z_dbg = (t + 1 == steps) ? z_dbg : nullptr;
-        C.H = H; C.M_pad = h.M_pad; C.K_pad = h.K_pad; C.batch = batch; C.wdtype = h.d.wdtype; C.stream = stream;
+        C.H = H; C.K_pad = h.K_pad; C.batch = batch; C.wdtype = h.d.wdtype; C.frag = frag; C.stream = stream;
         if ((rc = launch_lstm_cell(C)) != PIVOT_OK) return rc;
     }
     return PIVOT_OK;
@@ -637,8 +638,9 @@ int pivot_fc_kernel_name(const pivot_fc_plan_t* plan, int batch, char* buf, size
     L.nchunks = h.nchunks; L.nbr = h.nbr; L.chunk_tiles = h.chunk_tiles; L.wg_waves = h.wg_waves;
     L.lds_tiles = h.lds_tiles(); L.xrow_len = h.xrow_len(); L.row_slices = h.row_slices; L.uniform_ct = h.uniform_ct; L.uniform_parts = h.uniform_parts;
     L.batch = batch;
-    // a natural-order x, 16-byte aligned, rows densely packed (what the matrix-core form reads is its own copy)
-    const bool blk = fc_uses_matrix_cores(fc_shape(h), batch);
+    // a natural-order x, 16-byte aligned, rows densely packed (what the batched matrix-core form reads is its own copy)
+    const bool blk = fc_wants_frag(fc_shape(h, kXNatural), batch);
+    L.x_from = kXNatural;
     L.x = reinterpret_cast<const void*>(uintptr_t(256)); L.ldx = blk ? h.K_pad : h.d.K; L.x_block_order = blk ? 1 : 0;
     L.xsort = h.sorted_ok ? reinterpret_cast<const int32_t*>(uintptr_t(256)) : nullptr;
     std::string name;

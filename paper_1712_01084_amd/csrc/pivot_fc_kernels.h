@@ -48,6 +48,9 @@ struct FcArgs {
     uint32_t*      tickets;
     long long ldx, ldy;
     int batch, act, out_f16, nchunks, nbr, xs_stride;
+    int out_shift, out_group;   // column c of batch row b of y lies at b*ldy + (c >> out_shift)*out_group + (c mod
+                                // 1 << out_shift): shift 0 and group 1 for rows, fragment order (frag_index) otherwise
+    int zero_from, zero_to;     // columns of a fragment-order y to clear (the consumer's padding columns)
     int bh_full;                // rows of a whole tile (the kernels' BH is the height of one row slice)
     int tile_elems;             // bh_full * bw
     int uniform_ct;             // > 0: every chunk has exactly this many tiles and chunk i starts at tile i*uniform_ct,
@@ -116,7 +119,12 @@ struct FcArgs {
 // Per-dtype / per-path launchers, each in its own translation unit.
 int launch_gemv_f32(const FcArgs& a, int bhs, int bw, int nb, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
 int launch_gemv_f16(const FcArgs& a, int bhs, int bw, int nb, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
-int launch_mfma_f16(const FcArgs& a, int kind, int bhs, int bw, int nw, dim3 grid, size_t smem, hipStream_t st);
+int launch_frag_f32_8(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
+int launch_frag_f32_16(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
+int launch_frag_f32_32(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
+int launch_frag_f16_8(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
+int launch_frag_f16_16(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
+int launch_frag_f16_32(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
 int launch_mfma_lds_f16(const FcArgs& a, int kind, int bhs, int bw, int nbs, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
 int launch_mfma_xrow_f16(const FcArgs& a, int kind, int bhs, int bw, dim3 grid, size_t smem, hipStream_t st);
 int launch_colmajor(const FcArgs& a, int layout, int wdtype, int bh, int bw, int nw, dim3 grid, size_t smem, hipStream_t st);
@@ -486,6 +494,16 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
                                             int b0, int tid, int* s_flag) {
     constexpr int N = BH * NBT;
     const int gy = blockIdx.y, slice = blockIdx.z, SL = gridDim.z;
+    // a y that is the input of the next layer: its padding columns, which no row lands in (behind everything else:
+    // looked at earlier, these arguments cost every launch 0.1 us)
+    auto clear_padding = [&]() {
+        if (a.zero_from < a.zero_to && blockIdx.x == 0 && slice == 0) {
+            for (int i = tid; i < (a.zero_to - a.zero_from) * NBT; i += NT) {
+                const int b = b0 + i % NBT, c = a.zero_from + i / NBT;
+                if (b < a.batch) store_out(a.y, (long long)frag_index(b, c, a.batch, a.out_shift), 0.f, a.out_f16);
+            }
+        }
+    };
     if (nparts > 1) {
         float* mine = a.partials + (((size_t)gy * a.nchunks + slot) * SL + slice) * N;
         for (int idx = tid; idx < N; idx += NT) {
@@ -510,7 +528,7 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
             *s_flag = last;
         }
         __syncthreads();
-        if (!*s_flag) return;
+        if (!*s_flag) { clear_padding(); return; }
     }
     #pragma unroll
     for (int k = 0; k < RowPre<BH, N, NT>::CNT; ++k) {
@@ -527,8 +545,12 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
         }
         const float v = apply_act(s + rp.bias[k], a.act);
         if ((PIVOT_ABLATE & 8) && !(v == 12345.678f)) continue;      // ablation: computed, never stored
-        if (rp.dst[k] >= 0) store_out(a.y, (long long)(b0 + j) * a.ldy + rp.dst[k], v, a.out_f16);
+        if (rp.dst[k] < 0) continue;
+        const long long at = (long long)(b0 + j) * a.ldy + (long long)(rp.dst[k] >> a.out_shift) * a.out_group
+                             + (rp.dst[k] & ((1 << a.out_shift) - 1));
+        store_out(a.y, at, v, a.out_f16);
     }
+    clear_padding();
 }
 
 // ---------------------------------------------------------------------------
@@ -731,16 +753,12 @@ __global__ void __launch_bounds__(NW * 64) fc_gemv_kernel(PIVOT_GEMV_PARAMS, FcA
 }
 
 // ---------------------------------------------------------------------------
-// batch >= 8, fp16 weights: matrix-core kernels.  The tile is the A operand,
-// the x-segment (k x batch) the B operand, accumulation in fp32.  x must be in
-// block order already ([batch][K_pad], produced by the previous layer's store,
-// by the recurrent cell, or by gather_x_kernel): lane l reads its B fragment,
-// 8 consecutive k of one batch row, with one 16-byte load, no LDS staging.
+// fp16 weights, x in LDS: matrix-core kernels.  The tile is the A operand,
+// the x-segment (k x batch) the B operand, accumulation in fp32.
 // KIND 0: v_mfma_f32_16x16x32_f16, slices with BH % 16 == 0, BW % 32 == 0, 16 batch columns.
 //         lane l supplies A[row l%16][k 8(l/16)..+7] = 16 contiguous bytes of a BRC tile row.
 // KIND 1: v_mfma_f32_32x32x16_f16, slices with BH % 32 == 0, BW % 16 == 0, 32 batch columns.
 //         lane l supplies A[row l%32][k 8(l/32)..+7].
-// Batch columns past `batch` read row batch-1 again; their results are never stored.
 // ---------------------------------------------------------------------------
 template <int KIND> struct Mfma;
 template <> struct Mfma<0> {
@@ -760,137 +778,11 @@ template <> struct Mfma<1> {
     }
     __device__ static __forceinline__ int row_of(int lane, int v) { return 8 * (v / 4) + 4 * (lane / 32) + (v % 4); }
 };
-// KIND 2 (LDS-fed kernel only): v_mfma_f32_16x16x32_f16 over PAIRS of consecutive 16-column tiles of a block
+// KIND 2: v_mfma_f32_16x16x32_f16 over PAIRS of consecutive 16-column tiles of a block
 // row, so that tiles 16 columns wide can still be cut into 16-row slices: lanes with k group 0-1 supply rows of
 // the pair's first tile, groups 2-3 of its second (each tile's slice is 512 contiguous bytes); the staged
 // x-segments of consecutive tiles are adjacent in LDS, so the B fragment is the same single 16-byte read.
 template <> struct Mfma<2> : Mfma<0> {};
-
-template <int KIND, int BH, int BW, int NW>
-__global__ void __launch_bounds__(NW * 64) fc_mfma_kernel(PIVOT_LEAD_PARAMS, FcArgs a) {
-    using MF = Mfma<KIND>;
-    using acc_t = typename MF::acc_t;
-    constexpr int MR = MF::MR, MK = MF::MK, NBT = MF::NBT, CV = MF::CV;
-    constexpr int NT = NW * 64;
-    constexpr int RB = BH / MR;                         // row blocks per tile slice
-    constexpr int KS = BW / MK;                         // k steps per tile
-    constexpr int LT = RB * KS;                         // 16-byte weight loads per lane per tile
-    constexpr int U  = (LT >= 8) ? 1 : 8 / LT;          // tiles in flight per wave
-    constexpr int N  = BH * NBT;
-    constexpr int RW = NW < 4 ? NW : 4;                 // waves that hold the sums at the end
-    static_assert(BH % MR == 0 && BW % MK == 0, "tile shape does not fit this MFMA");
-
-    extern __shared__ __align__(16) char smem[];
-    __shared__ int s_flag;
-    float* red = reinterpret_cast<float*>(smem);        // RW * N floats
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int b0 = blockIdx.y * NBT, slice = blockIdx.z;
-    const Chunk ck = load_chunk(a.uniform_ct, a.uniform_parts, p_chunks, p_part_base);
-    const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles, slot = ck.slot;
-    const int first = ck.first, nparts = ck.nparts;
-    const int row0 = br * a.bh_full + slice * BH;
-
-    RowPre<BH, N, NT> rp;
-    rp.load(p_bias, p_scatter, row0, tid);
-
-    const int li = lane % MR;                           // A row / B column of this lane
-    const int lg = lane / MR;                           // k group of 8
-    const _Float16* vbase = reinterpret_cast<const _Float16*>(p_vals) + (size_t)tile_begin * a.tile_elems
-                            + (size_t)slice * BH * BW + li * BW + lg * 8;
-    const int brow = (b0 + li < a.batch) ? b0 + li : a.batch - 1;
-    const _Float16* xb = reinterpret_cast<const _Float16*>(p_x) + (long long)brow * a.ldx + lg * 8;
-    const int32_t* ci_base = p_idx + tile_begin;    // wave-uniform: scalar loads, their own counter
-
-    const int tmax = ntiles > 0 ? ntiles - 1 : 0;       // clamped, unconditional loads (see fc_gemv_kernel)
-    f16x8 w[U][LT];
-    f16x8 xv[U][KS];
-    auto issue = [&](int t0) {
-        int ci[U];
-        #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = t0 + u * NW;
-            ci[u] = ci_base[t < tmax ? t : tmax];
-        }
-        #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int t = t0 + u * NW;
-            const int tc = t < tmax ? t : tmax;
-            #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-                #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    w[u][rb * KS + ks] = load16<f16x8>(vbase + (size_t)tc * a.tile_elems + rb * MR * BW + ks * MK);
-        }
-        #pragma unroll
-        for (int u = 0; u < U; ++u)
-            #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) xv[u][ks] = load16<f16x8>(xb + (size_t)ci[u] * BW + ks * MK);
-    };
-
-    acc_t acc[RB];
-    #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) acc[rb] = acc_t(0);
-
-    // One tile's loads: block column (scalar), A fragments, B fragments.
-    auto fill = [&](int u, int t) {
-        const int tc = t < tmax ? t : tmax;
-        const int ci = ci_base[tc];
-        #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-            #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                w[u][rb * KS + ks] = load16<f16x8>(vbase + (size_t)tc * a.tile_elems + rb * MR * BW + ks * MK);
-        #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) xv[u][ks] = load16<f16x8>(xb + (size_t)ci * BW + ks * MK);
-    };
-    auto consume = [&](int u) {
-        #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[rb] = MF::run(w[u][rb * KS + ks], xv[u][ks], acc[rb]);
-    };
-
-    issue(wave);
-    // all rounds but the last: consume a slot and refill it at once (loads stay in flight)
-    int t0 = wave;
-    for (; t0 + NW * U < ntiles; t0 += NW * U) {
-        #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            consume(u);
-            fill(u, t0 + u * NW + NW * U);
-        }
-    }
-    #pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (t0 + u * NW < ntiles) consume(u);
-
-    // waves -> one sum: rounds of (up to) 4 writers into a 4-slot LDS buffer
-    auto put = [&](int w_slot) {
-        #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-            #pragma unroll
-            for (int v = 0; v < CV; ++v)
-                red[w_slot * N + li * BH + rb * MR + MF::row_of(lane, v)] = acc[rb][v];
-    };
-    #pragma unroll
-    for (int base = RW; base < NW; base += RW) {
-        if (wave >= base && wave < base + RW) put(wave - base);
-        __syncthreads();
-        if (wave < RW) {
-            #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-                #pragma unroll
-                for (int v = 0; v < CV; ++v)
-                    acc[rb][v] += red[wave * N + li * BH + rb * MR + MF::row_of(lane, v)];
-        }
-        __syncthreads();
-    }
-    if (wave < RW) put(wave);
-    __syncthreads();
-    finish_rows<BH, NBT, NT>(a, red, RW, br, slot, first, nparts, rp, b0, tid, &s_flag);
-}
 
 // ---------------------------------------------------------------------------
 // batch 3..16, fp16 weights: matrix cores fed from LDS.  With several batch

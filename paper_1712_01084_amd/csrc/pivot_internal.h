@@ -21,6 +21,13 @@ constexpr size_t kValsPadBytes = 16 * 1024;
 constexpr int kSortSrcBits = 19;               // packed gather entry: source index below, staged position above
 constexpr int kSortSrcNone = (1 << kSortSrcBits) - 1;
 
+// Where element (b, c) of a batch of inputs in block order lies in fragment order (pivot_frag.h): groups of
+// 1 << shift columns (16 bytes), the batch rows of a group side by side.
+constexpr size_t frag_index(int b, int c, int batch, int shift) {
+    return (((size_t)(c >> shift) * batch + b) << shift) + (c & ((1 << shift) - 1));
+}
+constexpr int frag_shift(int wdtype) { return wdtype == PIVOT_F32 ? 2 : 3; }
+
 // Which MFMA shape a row-major fp16 tile feeds: 0 = 16x16x32, 1 = 32x32x16, -1 = none.
 inline int mfma_kind(int wdtype, int bh, int bw) {
     if (wdtype != PIVOT_F16) return -1;
@@ -108,13 +115,17 @@ struct FcLaunch {
     int lds_tiles;              // chunk_tiles if the plan carries the packed gather lists, else 0
     int xrow_len;               // HostPlan::xrow_len()
     int uniform_ct, uniform_parts;  // > 0: regular schedule, the kernels compute the chunk descriptor
-    int x_block_order;          // 1: x is [batch][K_pad] in block order (what the matrix-core kernel needs)
+    int x_block_order;          // 1: x is [batch][K_pad] in block order, rows of K_pad elements, or in fragment
+                                // order (pivot_frag.h) if that is the kernel the launch takes
+    int x_from;                 // FcShape::x_from
     int K;                      // row length of a natural-order x
     int x_resident;             // 0: never copy the whole of x into LDS; 1: the launcher decides; 2: whenever possible
     // data
     const void* x; int64_t ldx;
     void*       y; int64_t ldy;
     int out_f16;                // 1: y is fp16 (chain intermediates of F16 plans), 0: fp32
+    int out_frag;               // 1: y is written in fragment order with ldy columns (chain intermediates whose consumer reads that)
+    int zero_from, zero_to;     // columns of such a y that no row lands in (the consumer's padding) and that are to be cleared
     int batch;
     float*    partials;
     uint32_t* tickets;
@@ -122,29 +133,30 @@ struct FcLaunch {
 };
 
 // Batch rows one launch of the layer kernel covers (grid.y repeats it).
-enum { kPathVector = 0, kPathMfmaLds = 1, kPathMfmaGather = 2, kPathMfmaXrow = 3 };
+enum { kPathVector = 0, kPathMfmaLds = 1, kPathFrag = 2, kPathMfmaXrow = 3 };
 // What decides the path besides the batch.  `lds_tiles`: HostPlan::lds_tiles() (0 rules the LDS-fed matrix-core
 // kernel out); `chunk_tiles`, `xrow_len`: the plan's chunk size and HostPlan::xrow_len() (0 rules out the
-// matrix-core kernel that gathers its fragments from a copy of x in LDS).
-struct FcShape { int layout, wdtype, bh, bw, lds_tiles, chunk_tiles, xrow_len, mean_tiles; };   // mean_tiles: kept tiles per work item, rounded up
+// matrix-core kernel that gathers its fragments from a copy of x in LDS); `x_from`: where x comes from (kXNatural:
+// the caller, in natural order; kXNoCopy: the same, with no scratch for a fragment-order copy, which rules out the
+// kernel that reads one; kXBlock: the layer or cell before, which writes the order the kernel wants).
+enum { kXNoCopy = 0, kXNatural = 1, kXBlock = 2 };
+struct FcShape { int layout, wdtype, bh, bw, lds_tiles, chunk_tiles, xrow_len, mean_tiles, nchunks, x_from; };   // mean_tiles: kept tiles per work item, rounded up
 inline int mean_tiles_of(int T, int nchunks) { return nchunks > 0 ? (T + nchunks - 1) / nchunks : 0; }
-inline FcShape fc_shape(const HostPlan& h) { return FcShape{h.d.layout, h.d.wdtype, h.d.bh, h.d.bw, h.lds_tiles(), h.chunk_tiles, h.xrow_len(), mean_tiles_of(h.T, h.nchunks)}; }
+inline FcShape fc_shape(const HostPlan& h, int x_from) { return FcShape{h.d.layout, h.d.wdtype, h.d.bh, h.d.bw, h.lds_tiles(), h.chunk_tiles, h.xrow_len(), mean_tiles_of(h.T, h.nchunks), h.nchunks, x_from}; }
 int    fc_path(const FcShape& s, int batch);
 int    fc_batch_tile(const FcShape& s, int batch);
-bool   fc_uses_matrix_cores(const FcShape& s, int batch);   // the form that needs x in block order
+bool   fc_wants_frag(const FcShape& s, int batch);          // the form that reads x in fragment order
 int    fc_row_slices(const FcShape& s, int batch, int want);
-// Workspace of one layer application: [arrival counters][partials of split rows][x in block order (matrix path)]
+// Workspace of one layer application: [arrival counters][partials of split rows][x in fragment order (batched matrix path)]
 size_t fc_ticket_bytes(const HostPlan& hp);                   // the same for every batch (0 without split block rows)
-size_t fc_partial_bytes(const HostPlan& hp, int batch);
-size_t fc_workspace_bytes(const HostPlan& hp, int batch);     // counters + partials
-size_t fc_gather_bytes(const HostPlan& hp, int batch);        // block-order copy of a natural-order x
+size_t fc_partial_bytes(const HostPlan& hp, int batch, int x_from);
+size_t fc_gather_bytes(const HostPlan& hp, int batch);        // fragment-order copy of a natural-order x
 // describe != NULL: nothing is launched, *describe receives the name of the kernel instantiation the call would run
 int    launch_fc(const FcLaunch& L, std::string* describe = nullptr);
-int    launch_gather_x(const void* x, int64_t ldx, const int32_t* pcol_pad, void* xg, int K_pad, int batch,
-                       int wdtype, void* stream);
+// x in natural order -> fragment order (pivot_frag.h), zero in the padding columns
+int    launch_gather_frag(const void* x, int64_t ldx, const int32_t* pcol_pad, void* xg, int K, int K_pad, int batch,
+                          int wdtype, void* stream);
 int    launch_fill_zero(void* dev, size_t bytes, void* stream);
-// Zeroes columns [K, K_pad) of every row of a [batch][K_pad] buffer of `es`-byte elements.
-int    launch_zero_pad_cols(void* buf, int K, int K_pad, int batch, int es, void* stream);
 int    launch_null(void* stream);
 int    launch_stream_read(const void* buf, size_t bytes, float* out, void* stream);
 int    launch_exchange_probe(void* scratch, int rounds, void* stream);
@@ -160,16 +172,19 @@ struct LstmCellLaunch {
     float* h; float* c;         // [batch][H]
     void* xg_next;              // [batch][K_pad] of wdtype: next step's block-order input, or NULL
     float* z_dbg;               // optional [batch][4H] natural order
-    int H, M_pad, K_pad, batch, wdtype;
+    int H, K_pad, batch, wdtype;
+    int frag;                   // 1: xg_next is in fragment order
     void* stream;
 };
 int launch_lstm_cell(const LstmCellLaunch& L);
-// Places x_t (natural columns H..H+I-1) of every step into its block-order input buffer.
-int launch_lstm_place_inputs(const void* xs, void* xg_all, const int32_t* invpcol, int H, int I,
-                             int K_pad, int steps, int batch, int wdtype, void* stream);
-// Places h (fp32, natural) into one block-order input buffer.
-int launch_lstm_place_state(const float* h, void* xg, const int32_t* invpcol, int H, int K_pad,
-                            int batch, int wdtype, void* stream);
+// Block-order inputs of every step (launch-per-step form): x_t, and h_0 in step 0; clears the control words.
+struct LstmInputsLaunch {
+    const int32_t* pcol_pad; const void* xs; const float* h0; void* xg; uint32_t* ctl;
+    size_t xg_step_bytes; int H, I, K_pad, steps, batch, wdtype;
+    int frag;                   // 1: in fragment order
+    void* stream;
+};
+int launch_lstm_inputs(const LstmInputsLaunch& L);
 
 // The whole recurrent loop in one launch (weights resident in registers, grid barriers between the phases).
 struct LstmPersistLaunch {
@@ -213,10 +228,11 @@ int    launch_chain_persist(const ChainPersistLaunch& C);
 
 namespace pivot {
 // One layer application on a natural-order x, its scratch given as three separate regions: arrival counters
-// (fc_ticket_bytes, zero between runs), partial sums (fc_partial_bytes) and the block-order copy of x
-// (fc_gather_bytes); a region of size 0 may be NULL.  Checks its arguments like pivot_fc_run.
+// (fc_ticket_bytes, zero between runs), partial sums (fc_partial_bytes) and the fragment-order copy of x
+// (fc_gather_bytes); a region of size 0 may be NULL.  x_from: kXNatural, or kXNoCopy to run without
+// a fragment-order copy of x, whatever the batch (xg is not used).  Checks its arguments like pivot_fc_run.
 int run_layer(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, void* y_dev, int64_t ldy, int batch,
-              void* tickets, void* partials, void* xg, void* stream);
+              void* tickets, void* partials, void* xg, void* stream, int x_from = 1 /* kXNatural */);
 }
 
 struct pivot_fc_plan {

@@ -4,7 +4,7 @@
 #include <cstdio>
 #include <cstdlib>
 
-#include "pivot_fc_kernels.h"
+#include "pivot_frag.h"
 
 namespace pivot {
 
@@ -28,35 +28,52 @@ static int device_cus() {
 // were slower again from 10 % kept on: the weights are then streamed four times).
 static int mfma_lds_rows(int batch) { return batch <= 4 ? 4 : 8; }
 
+// Tiles per wavefront whose block columns fit the batched matrix-core kernel's registers (64 each, frag_cols), less
+// one group of tiles for the rounding of the split over wavefronts.
+static int frag_wave_tiles(const FcShape& s) { return frag_cols(s.bw, 16 / elem_size(s.wdtype)) * 64 - 8; }
+
 // Which kernel applies the layer:
-//   kPathVector      batch 1-2 (and whatever the matrix cores cannot take): FMA / dot2 against x staged in LDS
-//   kPathMfmaLds     fp16, batch >= 3: MFMA with the B fragments read from x staged in LDS (4 or 8 batch rows per launch row)
-//   kPathMfmaGather  fp16, batch >= 8 otherwise: MFMA with B fragments read from an x in block order
-// Every work item of the LDS-fed form gathers its own x-segments for all batch rows (rows * tiles * bw
-// elements), the block-order form gathers x once in a launch of its own.  Measured (4096x4096, 64x16 tiles):
-// at batch 3-4 the LDS-fed form beats the vector kernel at every density (LDS reads per weight load 4 -> 1).
-// From batch 8 on the gather decides: read in the order of the tile list every element costs a cache line per
-// batch row, and the form lost beyond a few thousand staged elements (dense, batch 8: 14.2 -> 18.6 us); read
-// through the plan's source-ordered lists (neighbouring lanes, neighbouring addresses) it wins wherever the
-// staged rows fit in 48 KB of LDS (batch 8: 7.6 -> 5.4 us at 10 % kept, 9.8 -> 7.4 at 25 %, 12.3 -> 10.1 at
-// 50 %, 14.2 -> 12.4 dense; batch 16: 7.3 -> 6.1 at 5 %, 11.0 -> 9.5 at 25 %).  Letting it take up to 136 KB of
-// LDS (one workgroup per compute unit) for 16 staged rows at 50 % and dense was measured too: 13.5 -> 13.2 us and
-// 14.5 -> 15.4 us, so longer rows stay with the block-order form.
-//   kPathMfmaXrow    fp16, batch 5-16: MFMA with the B fragments gathered from a copy of the rows of x in LDS
-// At batch 9-16 the staging itself bounds the LDS-fed form (16 rows x staged columns two-byte gathers per work
-// item, repeated by every row slice, and the weights streamed once per launch row of 8); gathering where the
-// fragment is formed needs one copy of x per work item instead, whatever the number of staged columns.  The copy
-// costs a work item 1.5-2.3 us (4096 columns: 128 KB through one compute unit's memory pipeline before its first
-// MFMA), the gathers 0.2-0.9 us, so the form is taken from a quarter of the columns staged per work item on
-// (4096x4096, 64x16 tiles, batch 16, cold: 8.3 -> 7.1 us at 25 % kept, 12.5 -> 9.1 at 50 %, 14.9 -> 12.7 dense;
-// at 10 % it would lose, 6.0 -> 6.3, at 5 % 4.8 -> 6.3).  Batch 5-8 takes it under the same rule (only the rows
-// that exist are copied; same matrix, batch 8: 6.5 -> 6.1 us at 25 %, 9.65 -> 8.1 at 50 %, 12.45 -> 11.7 dense,
-// batch 5 the same within 0.1 us; warm 0.2 us slower at 25 %, 0.3-0.45 faster above); at batch 4 it loses
-// (5.6 -> 6.0, 7.7 -> 7.9, 9.8 -> 11.1).
+//   kPathVector    batch 1-2 (and whatever the others do not take): FMA / dot2 against x staged in LDS, launch rows of
+//                  at most 4 batch rows
+//   kPathFrag      both types, every tile shape: MFMA with the B fragments read from an x in fragment order, the
+//                  weights streamed once for up to 64 batch rows; a natural-order x is copied by a launch of its own
+//   kPathMfmaLds   fp16, batch >= 3: MFMA with the B fragments read from x staged in LDS (4 or 8 batch rows per launch row)
+//   kPathMfmaXrow  fp16, batch 5-16: MFMA with the B fragments gathered from a copy of the rows of x in LDS
+// An x that the layer or cell before produced (kXBlock) arrives in the order the kernel wants, so from batch 2 on the
+// fragment form has nothing to pay for and streams the weights once: always (three fp16 layers of 25088-4096-4096-1000
+// at 10 % kept, batch 32: 23.1 us with the LDS-fed form behind the boundaries, 17.9 with this one).  For an x from the
+// caller the copy costs about 2.2 us and a second launch, and the other forms repeat work per launch row instead:
+// - fp32, and fp16 tiles no other matrix-core form takes: the vector kernel streams the weights, LDS-bound at 2-5.5
+//   TB/s, once per 4 batch rows.  4096x9216 fp32, 10 % kept (15 MB), vector / fragment form, batch 2: 6.6 / 9.3 us, 4:
+//   8.9 / 7.9, 8: 13.5 / 9.3, 16: 20.5 / 8.8, 64: 64.6 / 17.2; 2048x2048, 25 % (4 MB), batch 8: 4.8 / 6.1, 16: 7.5 /
+//   6.4; 1000x4000, 10 % (1.6 MB), batch 16: 6.0 / 5.7, 64: 15.9 / 7.4; 1000x1000, 25 % (1 MB), batch 64: 5.9 / 6.1.
+//   So from 12 MB of repeated weights on (14 MB of weights where one launch row covers batch 3-4).
+// - fp16 tiles that fit an MFMA shape: the LDS-fed form gathers the x-segments of its work items anew in every launch
+//   row of 8.  LDS-fed / fragment form, batch 16: 8192x8192, 25 % (524 K columns staged per launch row) 15.7 / 12.2 us,
+//   10 % (210 K) 10.6 / 9.5, 4096x9216, 10 % (118 K) 8.4 / 7.6, 4096x4096, 10 % (52 K) 5.5 / 5.6 and at batch 32 8.4 /
+//   6.8, 64x16 tiles (26 K) at batch 32 6.05 / 6.9 and at batch 64 9.5 / 9.1.  So from 100 K restaged columns on.
+// The LDS-fed form gathers through the plan's source-ordered lists and is taken while its staged rows fit in 48 KB.
+// At batch 9-16 its staging (16 rows x staged columns two-byte gathers per work item, repeated by every row slice)
+// bounds it; gathering where the fragment is formed needs one copy of x per work item instead, whatever the number of
+// staged columns.  The copy costs a work item 1.5-2.3 us (4096 columns: 128 KB through one compute unit's memory
+// pipeline before its first MFMA), the gathers 0.2-0.9 us, so the x-row form is taken from a quarter of the columns
+// staged per work item on (4096x4096, 64x16 tiles, batch 16, cold: 8.3 -> 7.1 us at 25 % kept, 12.5 -> 9.1 at 50 %, 14.9
+// -> 12.7 dense; at 10 % it would lose, 6.0 -> 6.3, at 5 % 4.8 -> 6.3).  Batch 5-8 takes it under the same rule (only
+// the rows that exist are copied; same matrix, batch 8: 6.5 -> 6.1 us at 25 %, 9.65 -> 8.1 at 50 %, 12.45 -> 11.7 dense,
+// batch 5 the same within 0.1 us); at batch 4 it loses (5.6 -> 6.0, 7.7 -> 7.9, 9.8 -> 11.1).  The fragment form is
+// 0.5-1 us behind it (batch 16: 6.2 / 7.0 at 25 %, 8.4 / 8.8 at 50 %, 11.7 / 12.6 dense).
 int fc_path(const FcShape& s, int batch) {
     const int layout = s.layout, wdtype = s.wdtype, bh = s.bh, bw = s.bw, lds_tiles = s.lds_tiles;
     // the matrix-core kernels read A fragments from row-major (BRC) tiles only
-    if (layout != PIVOT_BRC || mfma_kind(wdtype, bh, bw) < 0 || batch < 3) return kPathVector;
+    if (layout != PIVOT_BRC || batch < 2) return kPathVector;
+    const bool frag = s.x_from != kXNoCopy && (long long)s.xrow_len * batch * elem_size(wdtype) < (1ll << 31) && s.chunk_tiles <= 4 * frag_wave_tiles(s);
+    if (frag && s.x_from == kXBlock) return kPathFrag;
+    const double weight_mb = (double)s.nchunks * s.mean_tiles * bh * bw * elem_size(wdtype) * 1e-6;
+    if (mfma_kind(wdtype, bh, bw) < 0) {
+        const int launch_rows = (batch + 3) / 4;
+        return frag && batch >= 3 && (launch_rows > 1 ? (launch_rows - 1) * weight_mb >= 12.0 : weight_mb >= 14.0) ? kPathFrag : kPathVector;
+    }
+    if (batch < 3) return kPathVector;
     if (batch >= 5 && batch <= 16 && s.xrow_len > 0 && s.chunk_tiles > 0) {
         // 16 rows of x (each with 16 zeroed bytes behind it) and the work item's gather indices in LDS; a lane
         // copies at most 8 vectors of a row, a thread at most 4 int4 of indices
@@ -65,11 +82,8 @@ int fc_path(const FcShape& s, int batch) {
         const size_t lds = 16 * (vecs * 16 + 16) + cols * 4;
         // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few
         // long block rows among many short ones most work items copy all of x for a handful of tiles, which the
-        // 8-row LDS-fed form does not: 8192x3072, 16x32 tiles, per-row counts from 96 down to 2, batch 8, x
-        // already in block order (a step of the recurrent layer): 11.0 -> 12.0 us.  (With x in natural order the
-        // copy wins on that matrix too, 12.0 -> 10.4 us, and on 4096x4096 with the same profile it loses at batch
-        // 16 and wins at batch 5-8; the path does not depend on where x comes from, and batch 9-16 keeps the rule
-        // it was measured with.)
+        // 8-row LDS-fed form does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and
+        // wins at batch 5-8; batch 9-16 keeps the rule it was measured with).
         const size_t rule_cols = batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols;
         if (vecs <= 512 && cols <= 8192 && lds <= 156 * 1024 && rule_cols * 4 >= (size_t)s.xrow_len) return kPathMfmaXrow;
     }
@@ -78,24 +92,48 @@ int fc_path(const FcShape& s, int batch) {
         const size_t xs_bytes = (size_t)rows * ((size_t)lds_tiles * bw + 8 + 16) * 2;   // + the paired form's zeroed columns
         // every launch row of 8 batch rows streams the weights again and gathers its own rows: beyond two launch
         // rows the form is kept while the launch rows together stage at most 5120 columns per work item
-        // (4096x4096, 64x16 tiles: batch 24 at 5 / 25 % kept 7.9 -> 5.6 us, 12.1 -> 10.7; batch 64 at 5 %
-        // 9.8 -> 8.5; but batch 24 dense 16.1 -> 19.1 and batch 64 at 25 % 14.4 -> 21.0, which stay with the
-        // block-order form)
+        // (4096x4096, 64x16 tiles, against the fragment form: batch 24 at 5 % kept 6.2 -> 5.1 us, batch 64 8.7 -> 7.8)
         const size_t launch_rows = (size_t)(batch + rows - 1) / rows;
-        if (xs_bytes <= 48 * 1024 && (launch_rows <= 2 || launch_rows * lds_tiles * bw <= 5120)) return kPathMfmaLds;
+        const bool restage = frag && (double)(launch_rows - 1) * s.nchunks * s.mean_tiles * bw >= 100e3;
+        if (!restage && xs_bytes <= 48 * 1024 && (launch_rows <= 2 || launch_rows * lds_tiles * bw <= 5120)) return kPathMfmaLds;
     }
-    return batch >= 8 ? kPathMfmaGather : kPathVector;
+    return frag && batch >= 8 ? kPathFrag : kPathVector;
 }
 
-bool fc_uses_matrix_cores(const FcShape& s, int batch) {
-    return fc_path(s, batch) == kPathMfmaGather;
+bool fc_wants_frag(const FcShape& s, int batch) { return fc_path(s, batch) == kPathFrag; }
+
+// Row slices and blocks of 16 batch rows per launch row of the batched matrix-core kernel: slices of at most 32
+// rows and the whole batch in one launch row (the weights stream once) where that gives a work item to every
+// compute unit, else slices down to 16 rows (each reads the x of the whole block row), then shorter launch rows (each
+// streams the weights).  Us per call with 32- / 16-row slices: 8192x8192 fp32 25 % kept, batch 64 (256 block rows)
+// 33.0 / 37.4, 4096x25088 fp16 10 %, batch 4 (128 block rows) 9.15 / 8.8; with 1 / 2 / 4 blocks per launch row:
+// 8192x8192 fp16, batch 64 26.9 / 20.0 / 17.5, 1000x4096 fp16 16x32 tiles (63 block rows), batch 64 7.55 / 7.56 / 8.8.
+static void frag_split(const FcShape& s, int batch, int* slices, int* blocks) {
+    int sl = s.bh > 32 ? s.bh / 32 : 1;
+    const int need = (batch + 15) / 16;
+    int nbt = need > 2 ? 4 : need;
+    auto items = [&]() { return (long long)s.nchunks * sl * ((need + nbt - 1) / nbt); };
+    while (items() < 256 && s.bh / sl > 16) sl *= 2;
+    while (items() < 256 && nbt > 1) nbt /= 2;
+    *slices = sl;
+    *blocks = nbt;
 }
 
+// Wavefronts per work item of the batched matrix-core kernel.  Each keeps 8 KB of weights and the x that goes with
+// them in flight, so four fill a compute unit's queue, and several small workgroups per compute unit overlap one's
+// epilogue with another's loads (us per layer call, 8 / 4 / 2 wavefronts: 4096x1024 fp16 8x8 tiles, batch 32
+// 11.4 / 8.0 / 6.9; 4096x9216 fp32 10 % kept, batch 32 13.6 / 12.4 / 14.7; 8192x8192 fp16 25 % kept, batch 64
+// 19.1 / 17.6 / 18.9; 16384x16384 fp16 64x64 tiles 10 % kept, batch 8 22.1 / 19.4 / 17.6): two with fp16 weights
+// from two work items per compute unit on.
+static int frag_waves(const FcShape& s, int slices) {
+    int nw = s.wdtype == PIVOT_F16 && (long long)s.nchunks * slices >= 512 ? 2 : 4;
+    return nw == 2 && s.chunk_tiles > 2 * frag_wave_tiles(s) ? 4 : nw;
+}
 // Batch rows one launch row covers in the kernel's epilogue and in the workspace (grid.y repeats it).
 int fc_batch_tile(const FcShape& s, int batch) {
     if (s.layout != PIVOT_BRC) return 1;     // the column-major kernels take one batch row per launch row
     const int path = fc_path(s, batch);
-    if (path == kPathMfmaGather) return mfma_kind(s.wdtype, s.bh, s.bw) == 0 ? 16 : 32;
+    if (path == kPathFrag) { int sl, nbt; frag_split(s, batch, &sl, &nbt); return 16 * nbt; }
     if (path == kPathMfmaLds) return mfma_lds_rows(batch);
     if (path == kPathMfmaXrow) return 16;
     return batch >= 3 ? 4 : batch;
@@ -108,6 +146,7 @@ int fc_batch_tile(const FcShape& s, int batch) {
 int fc_row_slices(const FcShape& s, int batch, int want) {
     const int layout = s.layout, wdtype = s.wdtype, bh = s.bh, bw = s.bw;
     if (layout != PIVOT_BRC) return 1;       // a row slice is contiguous only in row-major tiles
+    if (fc_path(s, batch) == kPathFrag) { int fs, nbt; frag_split(s, batch, &fs, &nbt); return fs; }
     int sl = want < 1 ? 1 : want;
     // The LDS-fed matrix-core kernel beyond 8 batch rows (several launch rows of 8): every row slice of a block
     // row stages the same x-segments again, so at most two slices (4096x4096, 64x16 tiles, cold, four slices ->
@@ -121,9 +160,8 @@ int fc_row_slices(const FcShape& s, int batch, int want) {
         if (ok) {
             const int path = fc_path(s, batch);
             if (path != kPathVector) {
-                // whole MFMA row blocks: 16 rows (32 for tiles 16 columns wide, except in the kernels fed from
-                // LDS, which pair such tiles)
-                const int mr = (mfma_kind(wdtype, bh, bw) == 0 || (path != kPathMfmaGather && bw == 16)) ? 16 : 32;
+                // whole MFMA row blocks: 16 rows (tiles 16 columns wide are then taken in pairs)
+                const int mr = (mfma_kind(wdtype, bh, bw) == 0 || bw == 16) ? 16 : 32;
                 ok = (bhs % mr == 0);
             } else {
                 const int vec = 16 / elem_size(wdtype);
@@ -144,29 +182,26 @@ int fc_row_slices(const FcShape& s, int batch, int want) {
 // Plans without split block rows use no counters.
 size_t fc_ticket_bytes(const HostPlan& hp) {
     if (hp.max_parts <= 1) return 0;
-    int ngy_max = 1;
-    for (int batch = 1; batch <= 64; ++batch) {
-        const int nbt = fc_batch_tile(fc_shape(hp), batch);
-        ngy_max = std::max(ngy_max, (batch + nbt - 1) / nbt);
+    int most = 1;                            // launch rows x row slices of any batch, wherever x comes from
+    for (int x_from : {kXNoCopy, kXNatural, kXBlock}) {
+        const FcShape s = fc_shape(hp, x_from);
+        for (int batch = 1; batch <= 64; ++batch) {
+            const int nbt = fc_batch_tile(s, batch);
+            most = std::max(most, (batch + nbt - 1) / nbt * fc_row_slices(s, batch, hp.row_slices));
+        }
     }
-    // counters are sized for the plan's slice count (a launch may use fewer)
-    return (size_t)4 * kTicketStride * hp.nbr * ngy_max * hp.row_slices;
+    return (size_t)4 * kTicketStride * hp.nbr * most;
 }
 
-size_t fc_partial_bytes(const HostPlan& hp, int batch) {
+size_t fc_partial_bytes(const HostPlan& hp, int batch, int x_from) {
     if (hp.max_parts <= 1) return 0;
-    const int nbt = fc_batch_tile(fc_shape(hp), batch);
+    const int nbt = fc_batch_tile(fc_shape(hp, x_from), batch);
     const int ngy = (batch + nbt - 1) / nbt;
     return align_up((size_t)4 * hp.nchunks * hp.d.bh * nbt * ngy, 256);
 }
 
-size_t fc_workspace_bytes(const HostPlan& hp, int batch) {
-    if (batch < 1) return 0;
-    return fc_ticket_bytes(hp) + fc_partial_bytes(hp, batch);
-}
-
 size_t fc_gather_bytes(const HostPlan& hp, int batch) {
-    if (!fc_uses_matrix_cores(fc_shape(hp), batch)) return 0;
+    if (!fc_wants_frag(fc_shape(hp, kXNatural), batch)) return 0;
     return align_up((size_t)batch * hp.K_pad * elem_size(hp.d.wdtype), 256);
 }
 
@@ -179,9 +214,9 @@ static std::string kernel_name(const char* fmt, A... args) {
 }
 
 int launch_fc(const FcLaunch& L, std::string* describe) {
-    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks)};
+    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from};
     const int path = fc_path(shape, L.batch);
-    const bool mc = path == kPathMfmaGather, ml = path == kPathMfmaLds, mx = path == kPathMfmaXrow;
+    const bool ml = path == kPathMfmaLds, mx = path == kPathMfmaXrow;
     const int nbt = fc_batch_tile(shape, L.batch);
     const int ngy = (L.batch + nbt - 1) / nbt;
     const int sl = fc_row_slices(shape, L.batch, L.row_slices);
@@ -199,6 +234,8 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     a.x = L.x; a.y = L.y; a.partials = L.partials; a.tickets = L.tickets;
     a.ldx = L.ldx; a.ldy = L.ldy; a.batch = L.batch; a.act = L.act; a.out_f16 = L.out_f16;
     a.nchunks = L.nchunks; a.nbr = L.nbr;
+    a.out_shift = 0; a.out_group = 1; a.zero_from = L.zero_from; a.zero_to = L.zero_to;
+    if (L.out_frag) { a.out_shift = frag_shift(L.wdtype); a.out_group = L.batch << a.out_shift; a.ldy = 1 << a.out_shift; }
     a.bh_full = L.bh; a.tile_elems = L.bh * L.bw;
     a.uniform_ct = L.uniform_ct; a.uniform_parts = L.uniform_parts;
     a.T = L.T; a.chunk_tiles = L.chunk_tiles;
@@ -210,15 +247,18 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     dim3 grid(L.nchunks, ngy, sl);
     hipStream_t st = reinterpret_cast<hipStream_t>(L.stream);
 
-    if (mc) {
-        if (!L.x_block_order) { set_error("internal: the matrix-core kernel needs x in block order"); return PIVOT_E_UNSUPPORTED; }
-        a.xs_stride = 0;
-        const int rw = nw < 4 ? nw : 4;
-        size_t smem = (size_t)rw * bhs * nbt * 4;
-        if (describe) { *describe = kernel_name("fc_mfma_kernel<%d, %d, %d, %d>", mfma_kind(L.wdtype, L.bh, L.bw), bhs, L.bw, nw); return PIVOT_OK; }
-        return launch_mfma_f16(a, mfma_kind(L.wdtype, L.bh, L.bw), bhs, L.bw, nw, grid, smem, st);
-    }
     if (L.uniform_ct > 0xFFFF || L.uniform_parts > 0x7FFF) a.uniform_ct = a.uniform_parts = 0;   // packed into 16 bits each: fall back to loaded descriptors
+    if (path == kPathFrag) {
+        if (!L.x_block_order) { set_error("internal: the batched matrix-core kernel needs x in fragment order"); return PIVOT_E_UNSUPPORTED; }
+        if (L.bh > 64 || L.batch > 64) { set_error("shape outside the kernel's packed arguments"); return PIVOT_E_UNSUPPORTED; }
+        a.xidx = L.col_idx; a.xs_stride = 0; a.xn_vecs = 0;
+        const int fnw = frag_waves(shape, sl);
+        if (describe) { *describe = kernel_name("fc_frag_kernel<%s, %d, %d, %d, %d>", L.wdtype == PIVOT_F32 ? "float" : "_Float16", bhs, L.bw, nbt / 16, fnw); return PIVOT_OK; }
+        using Launch = int (*)(const FcArgs&, int, int, int, dim3, hipStream_t);
+        static const Launch by_height[2][3] = {{launch_frag_f32_8, launch_frag_f32_16, launch_frag_f32_32},
+                                               {launch_frag_f16_8, launch_frag_f16_16, launch_frag_f16_32}};
+        return by_height[L.wdtype == PIVOT_F32 ? 0 : 1][bhs == 8 ? 0 : (bhs == 16 ? 1 : 2)](a, L.bw, nbt / 16, fnw, grid, st);
+    }
     if (mx) {
         if (L.chunk_tiles > 0xFFFF || L.bh > 64) { set_error("shape outside the kernel's packed arguments"); return PIVOT_E_UNSUPPORTED; }
         const int xlen = L.x_block_order ? L.K_pad : L.K;

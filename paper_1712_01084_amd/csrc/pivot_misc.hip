@@ -6,29 +6,127 @@
 namespace pivot {
 
 // ---------------------------------------------------------------------------
-// x in natural order -> block order: xg[b][c] = x[b][pcol_pad[c]] (0 in padding
-// columns).  The matrix-core kernel reads its B fragments from xg; gathering
-// once per launch costs K*batch loads instead of (kept tiles)*bw*batch.
+// x in natural order -> fragment order (pivot_frag.h): the group fetch through
+// P_col, once per launch instead of once per kept tile.
+// gather_frag_kernel: a workgroup copies ONE row of x into LDS, whole, with
+// coalesced loads, and makes one segment of its groups from there; gathered
+// straight from memory every element moves a line of its own.  The segment is
+// the fastest grid dimension and a multiple of 8 of them are launched, so the
+// workgroups that write the batch rows of one group, 16 bytes of a line each,
+// share an XCD (round-robin over workgroups) and its L2 makes whole lines of
+// them.
+// gather_frag_far_kernel: rows too long for LDS.  A workgroup makes 32 groups
+// for eight batch rows; half a wavefront takes one batch row, and the groups
+// change places through LDS so that they are stored as whole 128-byte lines.
 // ---------------------------------------------------------------------------
 template <typename WT>
-__global__ void gather_x_kernel(const WT* x, long long ldx, const int32_t* pcol_pad, WT* xg, int K_pad, int batch) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    const int b = blockIdx.y;
-    if (c >= K_pad) return;
-    const int src = pcol_pad[c];
-    xg[(size_t)b * K_pad + c] = (src >= 0) ? x[(size_t)b * ldx + src] : WT(0);
+struct GroupIdx {
+    int4 s4[Elem<WT>::VEC / 4];
+    __device__ __forceinline__ void load(const int32_t* pcol_pad, int g) {
+        #pragma unroll
+        for (int q = 0; q < Elem<WT>::VEC / 4; ++q) s4[q] = reinterpret_cast<const int4*>(pcol_pad + (size_t)g * Elem<WT>::VEC)[q];
+    }
+    __device__ __forceinline__ typename Elem<WT>::vec gather(const WT* row) const {
+        constexpr int VEC = Elem<WT>::VEC;
+        int src[VEC];
+        #pragma unroll
+        for (int q = 0; q < VEC / 4; ++q) { src[4 * q] = s4[q].x; src[4 * q + 1] = s4[q].y; src[4 * q + 2] = s4[q].z; src[4 * q + 3] = s4[q].w; }
+        typename Elem<WT>::vec v;
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = row[src[e] > 0 ? src[e] : 0];
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) v[e] = src[e] >= 0 ? v[e] : WT(0);
+        return v;
+    }
+};
+
+template <typename WT>
+__global__ void __launch_bounds__(512) gather_frag_kernel(const int32_t* __restrict__ pcol_pad, const WT* __restrict__ x,
+                                                          WT* __restrict__ xg, long long ldx, int K, int ngroups, int batch, int seg_groups) {
+    using V = typename Elem<WT>::vec;
+    constexpr int VEC = Elem<WT>::VEC, NT = 512;
+    extern __shared__ __align__(16) char smem[];
+    WT* row = reinterpret_cast<WT*>(smem);
+    const int tid = threadIdx.x, b = blockIdx.y;
+    const WT* xr = x + (long long)b * ldx;
+    // whole vectors from the first 16-byte boundary of the row on, single elements in front and behind
+    const int head0 = (int)((16 - (reinterpret_cast<uintptr_t>(xr) & 15)) & 15) / (int)sizeof(WT);
+    const int head = head0 < K ? head0 : K;
+    const int nvec = (K - head) / VEC;
+    const V* xv = reinterpret_cast<const V*>(xr + head);
+    const int g0 = blockIdx.x * seg_groups, g1 = g0 + seg_groups < ngroups ? g0 + seg_groups : ngroups;
+    V v[8];                                             // 64 KB by 512 threads: the whole row at once
+    #pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int i = u * NT + tid;
+        if (i < nvec) v[u] = xv[i];
+    }
+    const int tail = head + nvec * VEC + tid;
+    const WT first = xr[tid < head ? tid : 0], last = xr[tail < K ? tail : 0];
+    GroupIdx<WT> gi;
+    gi.load(pcol_pad, g0 + tid < g1 ? g0 + tid : 0);
+    #pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int i = u * NT + tid;
+        if (i < nvec) {
+            if (head == 0) *reinterpret_cast<V*>(row + i * VEC) = v[u];
+            else {
+                #pragma unroll
+                for (int e = 0; e < VEC; ++e) row[head + i * VEC + e] = v[u][e];
+            }
+        }
+    }
+    if (tid < head) row[tid] = first;
+    if (tail < K) row[tail] = last;
+    __syncthreads();
+    for (int g = g0 + tid; g < g1; g += NT) {
+        if (g != g0 + tid) gi.load(pcol_pad, g);
+        reinterpret_cast<V*>(xg)[(size_t)g * batch + b] = gi.gather(row);
+    }
 }
 
-int launch_gather_x(const void* x, int64_t ldx, const int32_t* pcol_pad, void* xg, int K_pad, int batch,
-                    int wdtype, void* stream) {
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    dim3 grid((K_pad + 255) / 256, batch);
-    if (wdtype == PIVOT_F16)
-        hipLaunchKernelGGL(gather_x_kernel<_Float16>, grid, dim3(256), 0, st, (const _Float16*)x, (long long)ldx, pcol_pad, (_Float16*)xg, K_pad, batch);
-    else
-        hipLaunchKernelGGL(gather_x_kernel<float>, grid, dim3(256), 0, st, (const float*)x, (long long)ldx, pcol_pad, (float*)xg, K_pad, batch);
+template <typename WT>
+__global__ void __launch_bounds__(256) gather_frag_far_kernel(const int32_t* __restrict__ pcol_pad, const WT* __restrict__ x,
+                                                              WT* __restrict__ xg, long long ldx, int ngroups, int batch) {
+    using V = typename Elem<WT>::vec;
+    __shared__ V s_v[32][9];
+    const int tid = threadIdx.x;
+    const int g0 = blockIdx.x * 32, b0 = blockIdx.y * 8;
+    {
+        const int gl = tid & 31, bl = tid >> 5;
+        const int g = g0 + gl < ngroups ? g0 + gl : ngroups - 1, b = b0 + bl < batch ? b0 + bl : batch - 1;
+        GroupIdx<WT> gi;
+        gi.load(pcol_pad, g);
+        s_v[gl][bl] = gi.gather(x + (long long)b * ldx);
+    }
+    __syncthreads();
+    const int gl = tid >> 3, bl = tid & 7;
+    if (g0 + gl < ngroups && b0 + bl < batch) reinterpret_cast<V*>(xg)[(size_t)(g0 + gl) * batch + b0 + bl] = s_v[gl][bl];
+}
+
+template <typename WT>
+static int launch_gather_frag_t(const WT* x, int64_t ldx, const int32_t* pcol_pad, WT* xg, int K, int K_pad, int batch, hipStream_t st) {
+    const int ngroups = K_pad / Elem<WT>::VEC;
+    const size_t smem = align_up((size_t)K * sizeof(WT), 16);
+    // The copy pays for long fp16 inputs (us per call of a layer, copied / direct: 9216 columns, batch 32 6.2 / 6.4
+    // and 64 6.9 / 9.0; 25088 columns, batch 16 6.6 / 6.9, 32 8.25 / 10.1, 64 10.1 / 13.4; 4096 columns, batch 64
+    // 6.2 / 5.9).  Of fp32 rows a line holds half as many elements and the copy is twice as long: 9216 columns,
+    // batch 16 8.4 / 6.9 and 64 12.7 / 10.6, always slower.
+    if (sizeof(WT) == 2 && smem <= 64 * 1024 && (size_t)batch * K >= 256 * 1024) {
+        const int segs = 8;
+        hipLaunchKernelGGL(gather_frag_kernel<WT>, dim3(segs, batch), dim3(512), smem, st, pcol_pad, x, xg, (long long)ldx, K, ngroups, batch, (ngroups + segs - 1) / segs);
+    } else {
+        hipLaunchKernelGGL(gather_frag_far_kernel<WT>, dim3((ngroups + 31) / 32, (batch + 7) / 8), dim3(256), 0, st, pcol_pad, x, xg, (long long)ldx, ngroups, batch);
+    }
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
+}
+
+int launch_gather_frag(const void* x, int64_t ldx, const int32_t* pcol_pad, void* xg, int K, int K_pad, int batch,
+                       int wdtype, void* stream) {
+    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    if (wdtype == PIVOT_F16) return launch_gather_frag_t<_Float16>((const _Float16*)x, ldx, pcol_pad, (_Float16*)xg, K, K_pad, batch, st);
+    return launch_gather_frag_t<float>((const float*)x, ldx, pcol_pad, (float*)xg, K, K_pad, batch, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -38,23 +136,6 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t nwords) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < nwords; i += stride) p[i] = 0u;
-}
-
-// columns [K, K_pad) of every row of a [batch][K_pad] buffer, in 2-byte units (es = 2 or 4 bytes per element)
-__global__ void zero_pad_cols_kernel(unsigned short* buf, int first, int row_len, int batch) {
-    const int n = row_len - first;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n * batch; i += gridDim.x * blockDim.x)
-        buf[(size_t)(i / n) * row_len + first + i % n] = 0;
-}
-
-int launch_zero_pad_cols(void* buf, int K, int K_pad, int batch, int es, void* stream) {
-    if (K_pad <= K || batch < 1) return PIVOT_OK;
-    const int u = es / 2;                                  // 2-byte units per element
-    const int n = (K_pad - K) * u * batch;
-    hipLaunchKernelGGL(zero_pad_cols_kernel, dim3((n + 255) / 256), dim3(256), 0, reinterpret_cast<hipStream_t>(stream),
-                       reinterpret_cast<unsigned short*>(buf), K * u, K_pad * u, batch);
-    HIP_TRY(hipGetLastError());
-    return PIVOT_OK;
 }
 
 __global__ void null_kernel() {}
@@ -351,85 +432,91 @@ int launch_csr(const int32_t* row_ptr, const int32_t* col, const void* val, int 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float sigmoidf_(float v) { return 1.0f / (1.0f + __expf(-v)); }
 
-__global__ void lstm_cell_kernel(LstmCellLaunch L) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= L.batch * L.H) return;
-    const int b = idx / L.H, j = idx - b * L.H;
+// Arguments stay within 64 bytes: a launch whose arguments need more costs the host 0.8 us more.
+// flags: batch | fp16 << 8 | fragment order << 9.
+constexpr int lstm_flags(int batch, int wdtype, int frag) { return batch | (wdtype == PIVOT_F16 ? 256 : 0) | (frag ? 512 : 0); }
+
+__global__ void __launch_bounds__(256) lstm_cell_kernel(const float* __restrict__ z_all, const int32_t* __restrict__ invpcol,
+                                                        float* __restrict__ h_all, float* __restrict__ c_all, void* __restrict__ xg_next,
+                                                        float* __restrict__ z_dbg, int H, int K_pad, int flags) {
+    const int batch = flags & 0xFF;
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= batch * H) return;
+    const int b = idx / H, j = idx - b * H;
     // the layer kernel scattered the gate pre-activations into natural order: coalesced reads here
-    const float* z = L.z + (size_t)b * 4 * L.H;
+    const float* z = z_all + (size_t)b * 4 * H;
     const float zi = z[j];
-    const float zf = z[L.H + j];
-    const float zg = z[2 * L.H + j];
-    const float zo = z[3 * L.H + j];
-    const int dstc = L.xg_next ? L.invpcol[j] : 0;
-    const float c = sigmoidf_(zf) * L.c[idx] + sigmoidf_(zi) * tanhf(zg);
+    const float zf = z[H + j];
+    const float zg = z[2 * H + j];
+    const float zo = z[3 * H + j];
+    const int dstc = xg_next ? invpcol[j] : 0;
+    const float c = sigmoidf_(zf) * c_all[idx] + sigmoidf_(zi) * tanhf(zg);
     const float h = sigmoidf_(zo) * tanhf(c);
-    L.c[idx] = c;
-    L.h[idx] = h;
-    if (L.xg_next) {
+    c_all[idx] = c;
+    h_all[idx] = h;
+    if (xg_next) {
         // boundary fusion (Section 4.2.1 applied to the recurrence): h_t goes straight to its
         // block-order position in the next step's input
-        const size_t o = (size_t)b * L.K_pad + dstc;
-        if (L.wdtype == PIVOT_F16) reinterpret_cast<_Float16*>(L.xg_next)[o] = (_Float16)h;
-        else                       reinterpret_cast<float*>(L.xg_next)[o] = h;
+        const int shift = (flags & 256) ? 3 : 2;
+        const size_t o = (flags & 512) ? frag_index(b, dstc, batch, shift) : (size_t)b * K_pad + dstc;
+        if (flags & 256) reinterpret_cast<_Float16*>(xg_next)[o] = (_Float16)h;
+        else             reinterpret_cast<float*>(xg_next)[o] = h;
     }
-    if (L.z_dbg) {
-        float* zd = L.z_dbg + (size_t)b * 4 * L.H;
-        zd[j] = zi; zd[L.H + j] = zf; zd[2 * L.H + j] = zg; zd[3 * L.H + j] = zo;
+    if (z_dbg) {
+        float* zd = z_dbg + (size_t)b * 4 * H;
+        zd[j] = zi; zd[H + j] = zf; zd[2 * H + j] = zg; zd[3 * H + j] = zo;
     }
 }
 
 int launch_lstm_cell(const LstmCellLaunch& L) {
     int n = L.batch * L.H;
-    hipLaunchKernelGGL(lstm_cell_kernel, dim3((n + 255) / 256), dim3(256), 0, reinterpret_cast<hipStream_t>(L.stream), L);
+    hipLaunchKernelGGL(lstm_cell_kernel, dim3((n + 255) / 256), dim3(256), 0, reinterpret_cast<hipStream_t>(L.stream),
+                       L.z, L.invpcol, L.h, L.c, L.xg_next, L.z_dbg, L.H, L.K_pad, lstm_flags(L.batch, L.wdtype, L.frag));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }
 
+// Block-order inputs of all steps for the launch-per-step form, in one launch: x_t and h_0 in place, zero in the
+// padding columns and wherever a later h_t will land; clears the control words too.  A thread makes one 16-byte
+// group of one batch row; blockIdx.y is the step.
 template <typename WT>
-__global__ void lstm_place_inputs_kernel(const WT* xs, WT* xg_all, const int32_t* invpcol, int H, int I,
-                                         int K_pad, size_t total) {
-    size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; idx < total; idx += stride) {
-        const size_t tb = idx / I;               // step*batch + b
-        const int i = (int)(idx - tb * I);
-        xg_all[tb * K_pad + invpcol[H + i]] = xs[idx];
+__global__ void __launch_bounds__(256) lstm_inputs_kernel(const int32_t* __restrict__ pcol_pad, const WT* __restrict__ xs,
+                                                          const float* __restrict__ h0, WT* __restrict__ xg, uint32_t* __restrict__ ctl,
+                                                          unsigned step_vecs, int H, int I, int K_pad, int flags) {
+    using V = typename Elem<WT>::vec;
+    constexpr int VEC = Elem<WT>::VEC;
+    const int batch = flags & 0xFF, ngroups = K_pad / VEC;
+    const int i = blockIdx.x * 256 + threadIdx.x, t = blockIdx.y;
+    if (t == 0 && blockIdx.x == 0)
+        for (int k = threadIdx.x; k < (int)kLstmCtlBytes / 4; k += 256) ctl[k] = 0u;
+    if (i >= ngroups * batch) return;
+    const bool frag = (flags & 512) != 0;
+    const int g = frag ? i / batch : i % ngroups, b = frag ? i % batch : i / ngroups;
+    GroupIdx<WT> gi;
+    gi.load(pcol_pad, g);
+    const int* src = reinterpret_cast<const int*>(gi.s4);
+    const WT* x = xs + ((size_t)t * batch + b) * I;
+    V v;
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        const int s = src[e];
+        v[e] = WT(0);
+        if (s >= H) v[e] = x[s - H];
+        else if (s >= 0 && t == 0) v[e] = (WT)h0[(size_t)b * H + s];
     }
+    reinterpret_cast<V*>(xg)[(size_t)t * step_vecs + i] = v;
 }
 
-int launch_lstm_place_inputs(const void* xs, void* xg_all, const int32_t* invpcol, int H, int I, int K_pad,
-                             int steps, int batch, int wdtype, void* stream) {
-    size_t total = (size_t)steps * batch * I;
-    if (total == 0) return PIVOT_OK;
-    int blocks = (int)((total + 255) / 256 > 4096 ? 4096 : (total + 255) / 256);
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (wdtype == PIVOT_F16)
-        hipLaunchKernelGGL(lstm_place_inputs_kernel<_Float16>, dim3(blocks), dim3(256), 0, st,
-                           (const _Float16*)xs, (_Float16*)xg_all, invpcol, H, I, K_pad, total);
+int launch_lstm_inputs(const LstmInputsLaunch& L) {
+    hipStream_t st = reinterpret_cast<hipStream_t>(L.stream);
+    const int es = elem_size(L.wdtype), ngroups = L.K_pad * es / 16;
+    const dim3 grid((unsigned)(((size_t)ngroups * L.batch + 255) / 256), L.steps);
+    const unsigned step_vecs = (unsigned)(L.xg_step_bytes / 16);
+    const int flags = lstm_flags(L.batch, L.wdtype, L.frag);
+    if (L.wdtype == PIVOT_F16)
+        hipLaunchKernelGGL(lstm_inputs_kernel<_Float16>, grid, dim3(256), 0, st, L.pcol_pad, (const _Float16*)L.xs, L.h0, (_Float16*)L.xg, L.ctl, step_vecs, L.H, L.I, L.K_pad, flags);
     else
-        hipLaunchKernelGGL(lstm_place_inputs_kernel<float>, dim3(blocks), dim3(256), 0, st,
-                           (const float*)xs, (float*)xg_all, invpcol, H, I, K_pad, total);
-    HIP_TRY(hipGetLastError());
-    return PIVOT_OK;
-}
-
-template <typename WT>
-__global__ void lstm_place_state_kernel(const float* h, WT* xg, const int32_t* invpcol, int H, int K_pad, int n) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n) return;
-    const int b = idx / H, j = idx - b * H;
-    xg[(size_t)b * K_pad + invpcol[j]] = (WT)h[idx];
-}
-
-int launch_lstm_place_state(const float* h, void* xg, const int32_t* invpcol, int H, int K_pad, int batch,
-                            int wdtype, void* stream) {
-    int n = batch * H;
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (wdtype == PIVOT_F16)
-        hipLaunchKernelGGL(lstm_place_state_kernel<_Float16>, dim3((n + 255) / 256), dim3(256), 0, st, h, (_Float16*)xg, invpcol, H, K_pad, n);
-    else
-        hipLaunchKernelGGL(lstm_place_state_kernel<float>, dim3((n + 255) / 256), dim3(256), 0, st, h, (float*)xg, invpcol, H, K_pad, n);
+        hipLaunchKernelGGL(lstm_inputs_kernel<float>, grid, dim3(256), 0, st, L.pcol_pad, (const float*)L.xs, L.h0, (float*)L.xg, L.ctl, step_vecs, L.H, L.I, L.K_pad, flags);
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

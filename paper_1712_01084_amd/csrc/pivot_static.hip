@@ -2,7 +2,7 @@
 // allocate device memory nor hand over a workspace (code under HIP graph
 // capture, tight serving loops, harnesses that forbid hipMalloc).  The scratch
 // of a run (arrival counters and partial sums of split block rows, and the
-// block-order copy of x that one matrix-core form reads) lives in a file-scope
+// fragment-order copy of x that one matrix-core form reads) lives in a file-scope
 // device array of fixed size instead of a caller's buffer; the kernels are the
 // ones pivot_fc_run launches and take the array's address as an argument just
 // as they take the workspace there.
@@ -17,7 +17,7 @@ namespace pivot {
 
 namespace {
 
-// [arrival counters][partial sums, then the block-order copy of x].  The counter region is only ever used for
+// [arrival counters][partial sums, then the fragment-order copy of x].  The counter region is only ever used for
 // counters, whatever plan runs: every run leaves its counters at zero (the last workgroup to arrive resets
 // them), so no call has to clear anything for the next one, and nothing a run keeps in the second region is
 // read before the same run has written it.
@@ -72,7 +72,11 @@ int pivot_fc_run_static(const pivot_fc_plan_t* plan, const void* x_dev, int64_t 
     if (plan->device < 0) { set_error("host-only plan (device = -1) cannot run"); return PIVOT_E_NO_DEVICE; }
     if (batch < 1 || batch > 64) { set_error("batch %d outside 1..64", batch); return PIVOT_E_SHAPE; }
     const HostPlan& h = plan->host;
-    const size_t nt = fc_ticket_bytes(h), np = fc_partial_bytes(h, batch), ng = fc_gather_bytes(h, batch);
+    const size_t nt = fc_ticket_bytes(h);
+    size_t np = fc_partial_bytes(h, batch, kXNatural), ng = fc_gather_bytes(h, batch);
+    // a fragment-order copy of x that does not fit beside the rest: the kernels that need none
+    const bool frag_ok = np + ng <= kDataBytes;
+    if (!frag_ok) { np = fc_partial_bytes(h, batch, kXNoCopy); ng = 0; }
     if (nt > kCounterBytes || np + ng > kDataBytes) {
         set_error("this plan at batch %d needs %zu bytes of arrival counters and %zu bytes of partial sums and staged "
                   "input; the built-in scratch holds %zu and %zu: use pivot_fc_run with a workspace",
@@ -82,7 +86,7 @@ int pivot_fc_run_static(const pivot_fc_plan_t* plan, const void* x_dev, int64_t 
     unsigned char* base = nullptr;
     const int rc = scratch_of(plan->device, stream, &base);
     if (rc != PIVOT_OK) return rc;
-    return run_layer(plan, x_dev, ldx, y_dev, ldy, batch, base, base + kCounterBytes, base + kCounterBytes + np, stream);
+    return run_layer(plan, x_dev, ldx, y_dev, ldy, batch, base, base + kCounterBytes, base + kCounterBytes + np, stream, frag_ok ? kXNatural : kXNoCopy);
 }
 
 }  // extern "C"

@@ -1,0 +1,83 @@
+"""Parity of the batched matrix-core kernel (x in fragment order) and of the
+two ways its input is made, at the sizes where they can go wrong: every tile
+shape, odd tile counts, ragged sides, each side of a block of 16 batch rows,
+split and empty block rows, rows of x too long or not aligned for the copy.
+Needs a GPU.  Bounds: those of gpu_util (fp32 sums of n <= 16384 products,
+worst case n * 2^-24 = 1e-3 of |W||x| and typically sqrt(n) * 2^-24 = 8e-6, here
+measured below 1e-7; fp16 products are exact in fp32, so the same holds)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1712_01084_amd import binding as B
+from paper_1712_01084_amd import workloads as WL
+
+import gpu_util as G
+from test_gpu_chain import _check_chain
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(bh, bw) for bh in (8, 16, 32, 64) for bw in (8, 16, 32, 64)]
+
+
+@pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
+@pytest.mark.parametrize("bh,bw", SHAPES)
+def test_every_tile_shape_behind_a_boundary(bh, bw, wdtype):
+    # a layer fed by another one takes this kernel from batch 2 on, whatever its size
+    for i, (batch, chunk) in enumerate([(2, 0), (15, 3), (16, 0), (17, 1), (33, 2), (64, 0)]):
+        probs = WL.config4(seed=70 + i, batch=batch, dims=(100, 5 * bw + 3, 3 * bh - 1), bh=bh, bw=bw, frac=0.7, wdtype=wdtype,
+                           eliminated=bool(i % 2))
+        if i >= 4:
+            probs[1].tile_mask[0, :] = 0            # an empty block row
+        err, _ = _check_chain(probs, chunk_tiles=chunk)
+        print("%s %dx%d batch %d: %.3g" % (wdtype, bh, bw, batch, err), flush=True)
+        assert err <= 1e-5 or wdtype == WL.F16
+
+
+@pytest.mark.parametrize("wdtype,M,K,bh,bw,batch,frac", [
+    (WL.F32, 2048, 2048, 32, 32, 3, 1.0),        # the smallest batch; every wavefront runs several rounds
+    (WL.F32, 1000, 1501, 8, 8, 64, 0.8),         # stacked tiles, a ragged last column, all four batch blocks
+    (WL.F32, 600, 2300, 64, 64, 37, 0.9),
+    (WL.F32, 500, 30000, 16, 16, 17, 0.12),
+    (WL.F16, 64, 16390, 8, 8, 64, 1.0),          # items of 768 tiles; rows of x copied into LDS
+    (WL.F16, 200, 33000, 64, 32, 20, 0.5),       # rows of x too long for the copy
+    (WL.F16, 4096, 4100, 32, 32, 40, 0.2),
+])
+def test_natural_input(wdtype, M, K, bh, bw, batch, frac):
+    p = WL.gen_fc(M, K, bh, bw, frac, seed=81, wdtype=wdtype, batch=batch, act=WL.ACT_RELU)
+    plan = G.dev_plan(p)
+    try:
+        assert "fc_frag_kernel" in B.pivot_fc_kernel_name(plan, batch)
+        st = torch.cuda.current_stream().cuda_stream
+        y_ref, D = G.oracle_of(p)
+        ws = G.workspace(B.pivot_fc_workspace_bytes(plan, batch))
+        for off, ldx in ((0, K), (1, K + 3)):       # aligned, densely packed rows; and rows that are neither
+            ws[B.pivot_fc_workspace_bytes(plan, batch) // 2:].fill_(0xFF)      # scratch of x and partial sums: NaN patterns
+            G.B.pivot_workspace_init(ws.data_ptr(), ws.numel() // 2 // 4 * 4, st)
+            buf = torch.full((batch * ldx + 8,), float("nan"), dtype=G.tdtype(p), device="cuda")
+            rows = buf[off:off + batch * ldx].view(batch, ldx)
+            rows[:, :K] = torch.from_numpy(p.x).cuda()
+            y = torch.full((batch, M), float("nan"), device="cuda")
+            B.pivot_fc_run(plan, rows.data_ptr(), ldx, y.data_ptr(), M, batch, ws.data_ptr(), ws.numel(), st)
+            torch.cuda.synchronize()
+            err = G.O.max_scaled_error(y.cpu().numpy().astype(np.float64), y_ref, D)
+            print("%s %dx%d batch %d offset %d: %.3g" % (wdtype, M, K, batch, off, err), flush=True)
+            assert err <= 1e-5
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
+def test_static_scratch_without_room_for_the_copy():
+    # 64 rows of 50000 fp32 columns are 12.8 MB, more than the built-in scratch holds: the kernels that need no copy run
+    p = WL.gen_fc(96, 50000, 32, 32, 0.9, seed=82, batch=64)
+    plan = G.dev_plan(p)
+    try:
+        assert "fc_frag_kernel" in B.pivot_fc_kernel_name(plan, 64)
+        st = torch.cuda.current_stream().cuda_stream
+        xd, y = torch.from_numpy(p.x).cuda(), torch.full((64, p.M), float("nan"), device="cuda")
+        B.pivot_fc_run_static(plan, xd.data_ptr(), p.K, y.data_ptr(), p.M, 64, st)
+        torch.cuda.synchronize()
+        y_ref, D = G.oracle_of(p)
+        assert G.O.max_scaled_error(y.cpu().numpy().astype(np.float64), y_ref, D) <= 1e-5
+    finally:
+        B.pivot_fc_plan_destroy(plan)
