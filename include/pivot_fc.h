@@ -343,22 +343,24 @@ int    pivot_mlp_status_word(const pivot_mlp_plan_t* plan, const uint32_t** word
  *   z_dbg    device, optional [batch][4H] fp32: gate pre-activations of the
  *            last step in natural order (NULL to skip)
  *
- * Two forms.  Plans with fp16 16x32 BRC tiles, batch <= 8, at most 15 kept
- * tiles per wavefront of a full-device grid (one workgroup per compute unit,
- * all co-resident) and K_pad/32 <= that grid run the whole sequence in ONE
- * launch: the kept tiles stay in registers for all steps and per step only h,
- * x_t and the gate sums move.  There are no grid barriers: the exchanged data
- * carries the step it belongs to and a consumer re-reads until it sees its
- * step.  Its workgroups wait for each other, so nothing else should occupy
- * the device while it runs; a wait that does not end within 2^18 polls gives
- * up, every workgroup leaves, h/c are left unwritten and the status word
- * reads 1.  Every other plan (or
- * PIVOT_PLAN_LSTM_LAUNCH_PER_STEP), and every sequence of fewer than 4 steps,
- * runs one layer launch and one cell launch per step (the one-launch form
- * loads every kept tile into registers first: a first step from weights that
- * are not in cache costs it 23 us on the 8192x3072 workload against 18 us with
- * launches per step, every further step 6.8 against 9.1 us: it is ahead from
- * the fourth step on).  pivot_lstm_status synchronises the stream and returns the status
+ * Three forms.  Two run the whole sequence in ONE launch, the weights in
+ * registers and LDS for all steps.  In the first a workgroup owns whole units
+ * and per step only h moves: BRC plans of both types, H up to 512 (F32) or 1024
+ * (F16; 1024 or 2048 with the conditions of the second form), I up to 512 or
+ * 1024, where the batch leaves at least 4 launches' workgroups room on the
+ * device (half as many workgroups as compute units, half a compute unit each).
+ * In the second h and the gate sums move: fp16 16x32 BRC tiles, batch <= 8, at
+ * most 15 kept tiles per wavefront of a full-device grid (one workgroup per
+ * compute unit, all co-resident) and K_pad/32 <= that grid.  There are no grid
+ * barriers: the exchanged data carries the step it belongs to and a consumer
+ * re-reads until it sees its step.  The workgroups wait for each other, so
+ * nothing else should occupy the device while they run; a wait that does not
+ * end within 2^18 polls gives up, every workgroup leaves, h/c are left
+ * unwritten and the status word reads 1.  Every other plan (or
+ * PIVOT_PLAN_LSTM_LAUNCH_PER_STEP), and every sequence of fewer than 4 steps
+ * (8 steps for the first form where a block row keeps more than 128 pieces of 16
+ * bytes per row), runs one layer launch and one cell launch per step: the
+ * one-launch forms place every kept tile first.  pivot_lstm_status synchronises the stream and returns the status
  * word of the last pivot_lstm_run on this workspace (0 = completed).
  */
 size_t pivot_lstm_workspace_bytes(const pivot_fc_plan_t* plan, int H, int I, int steps, int batch);

@@ -523,7 +523,7 @@ namespace {
 // one-launch form][inputs of all steps]
 struct LstmLayout { size_t tickets, scratch, z_off, ctl_off, part_off, xg_off, xg_step, total; };
 
-LstmLayout lstm_layout(const pivot_fc_plan_t* p, int steps, int batch) {
+LstmLayout lstm_layout(const pivot_fc_plan_t* p, int H, int I, int steps, int batch) {
     LstmLayout m{};
     m.tickets = fc_ticket_bytes(p->host);
     m.scratch = align_up(m.tickets + fc_partial_bytes(p->host, batch, kXBlock), 256);
@@ -531,7 +531,7 @@ LstmLayout lstm_layout(const pivot_fc_plan_t* p, int steps, int batch) {
     m.ctl_off = m.z_off + align_up((size_t)batch * p->host.d.M * 4, 256);
     m.part_off = m.ctl_off + kLstmCtlBytes;
     m.xg_off = m.part_off + lstm_persist_partial_bytes(p->host, batch);
-    m.xg_step = align_up((size_t)batch * p->host.K_pad * elem_size(p->host.d.wdtype), 256);
+    m.xg_step = align_up(std::max((size_t)batch * p->host.K_pad * elem_size(p->host.d.wdtype), lstm_units_step_bytes(p->host, H, I, batch)), 256);
     m.total = m.xg_off + m.xg_step * (size_t)(steps > 0 ? steps : 1);
     return m;
 }
@@ -542,8 +542,7 @@ extern "C" {
 
 size_t pivot_lstm_workspace_bytes(const pivot_fc_plan_t* plan, int H, int I, int steps, int batch) {
     if (!plan || batch < 1 || steps < 0) return 0;
-    (void)H; (void)I;
-    return lstm_layout(plan, steps, batch).total;
+    return lstm_layout(plan, H, I, steps, batch).total;
 }
 
 int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev, float* h_dev, float* c_dev,
@@ -555,26 +554,30 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
     if (H < 1 || I < 0 || h.d.M != 4 * H || h.d.K != H + I) { set_error("plan is %dx%d, expected 4H x (H+I) with H=%d I=%d", h.d.M, h.d.K, H, I); return PIVOT_E_SHAPE; }
     if (steps < 0 || batch < 1 || batch > 64) { set_error("bad steps/batch"); return PIVOT_E_SHAPE; }
     if (steps == 0) return PIVOT_OK;
-    LstmLayout m = lstm_layout(plan, steps, batch);
+    LstmLayout m = lstm_layout(plan, H, I, steps, batch);
     if (!ws_dev || ws_bytes < m.total) { set_error("workspace too small: need %zu bytes", m.total); return PIVOT_E_WORKSPACE; }
     char* ws = reinterpret_cast<char*>(ws_dev);
     float* z = reinterpret_cast<float*>(ws + m.z_off);
     char* xg = ws + m.xg_off;
     int rc;
     // (fewer than 4 steps: loading every tile into registers first does not pay yet)
-    if (!(h.d.flags & PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) && (steps >= 4 || (h.d.flags & PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS)) && lstm_persist_supported(h, H, batch, plan->device, nullptr, nullptr)) {
+    const bool always = (h.d.flags & PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS) != 0;
+    const bool one_launch = !(h.d.flags & PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) && (steps >= 4 || always);
+    const bool units = one_launch && (always || steps >= lstm_units_min_steps(h)) && lstm_units_supported(h, H, I, batch, plan->device);
+    if (units || (one_launch && lstm_persist_supported(h, H, batch, plan->device, nullptr, nullptr))) {
         // one launch for the whole sequence
-        // control words + the partial buffers this sequence will use
-        if ((rc = launch_fill_zero(ws + m.ctl_off, (m.part_off - m.ctl_off) + lstm_persist_used_partial_bytes(h, batch, steps), stream)) != PIVOT_OK) return rc;
         LstmPersistLaunch P{};
         P.hp = &h;
         P.vals = plan->dev.vals; P.col_idx = plan->dev.col_idx; P.row_ptr = plan->dev.row_ptr;
-        P.invprow = plan->dev.invprow; P.invpcol = plan->dev.invpcol; P.pcol_pad = plan->dev.pcol_pad; P.bias_p = plan->dev.bias_p;
+        P.invprow = plan->dev.invprow; P.invpcol = plan->dev.invpcol; P.pcol_pad = plan->dev.pcol_pad; P.xidx = plan->dev.xidx; P.bias_p = plan->dev.bias_p;
         P.xs = xs_dev; P.xg = xg; P.xg_step_elems = m.xg_step / elem_size(h.d.wdtype);
         P.partials = ws + m.part_off;
         P.ctl = reinterpret_cast<uint32_t*>(ws + m.ctl_off);
         P.h = h_dev; P.c = c_dev; P.z_dbg = z_dbg;
         P.H = H; P.I = I; P.batch = batch; P.steps = steps; P.device = plan->device; P.stream = stream;
+        if (units) return launch_lstm_units(P);
+        // control words + the partial buffers this sequence will use
+        if ((rc = launch_fill_zero(ws + m.ctl_off, (m.part_off - m.ctl_off) + lstm_persist_used_partial_bytes(h, batch, steps), stream)) != PIVOT_OK) return rc;
         return launch_lstm_persist(P);
     }
     // one layer launch and one cell launch per step, behind one that places the inputs of all steps
@@ -611,7 +614,7 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
 int pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, void* stream, int* status) {
     if (!plan || !ws_dev || !status) { set_error("plan, ws_dev and status are required"); return PIVOT_E_NULL; }
     if (plan->device < 0) { set_error("host-only plan"); return PIVOT_E_NO_DEVICE; }
-    LstmLayout m = lstm_layout(plan, steps, batch);
+    LstmLayout m = lstm_layout(plan, 0, 0, steps, batch);   // (the control words lie in front of what depends on H and I)
     uint32_t word = 0;
     DeviceGuard g(plan->device);
     API_HIP(hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream)), (void)0);
@@ -622,7 +625,7 @@ int pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, const v
 
 int pivot_lstm_status_word(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, const uint32_t** word_dev) {
     if (!plan || !ws_dev || !word_dev) { set_error("plan, ws_dev and word_dev are required"); return PIVOT_E_NULL; }
-    LstmLayout m = lstm_layout(plan, steps, batch);
+    LstmLayout m = lstm_layout(plan, 0, 0, steps, batch);   // (the control words lie in front of what depends on H and I)
     *word_dev = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(ws_dev) + m.ctl_off + 1024);
     return PIVOT_OK;
 }

@@ -40,6 +40,7 @@ inline int mfma_kind(int wdtype, int bh, int bw) {
 struct HostPlan {
     pivot_fc_desc d{};
     int nbr = 0, nbc = 0, M_pad = 0, K_pad = 0, T = 0, chunk_tiles = 0, nchunks = 0, wg_waves = 4, row_slices = 1;
+    int max_row_tiles = 0;             // kept tiles of the longest block row
     int max_parts = 1;                 // largest number of pieces of one block row
     int uniform_ct = 0, uniform_parts = 0;  // set when every block row keeps the same number of tiles and every
                                        // chunk is full: chunk i = tiles [i*ct, (i+1)*ct) of block row i / parts
@@ -190,9 +191,9 @@ int launch_lstm_inputs(const LstmInputsLaunch& L);
 struct LstmPersistLaunch {
     const HostPlan* hp;
     const void* vals; const int32_t* col_idx; const int32_t* row_ptr; const int32_t* invprow; const int32_t* invpcol;
-    const int32_t* pcol_pad; const float* bias_p;
+    const int32_t* pcol_pad; const int32_t* xidx; const float* bias_p;
     const void* xs;                    // [steps][batch][I]
-    void* xg; size_t xg_step_elems;    // block-order inputs of all steps (written here)
+    void* xg; size_t xg_step_elems;    // block-order inputs of all steps (written here); one exchange: its buffers
     void* partials;                    // lstm_persist_partial_bytes, zeroed
     uint32_t* ctl;                     // kLstmCtlBytes, zeroed: progress word per workgroup, status word at [256]
     float* h; float* c; float* z_dbg;
@@ -204,6 +205,11 @@ size_t lstm_persist_partial_bytes(const HostPlan& hp, int batch);
 size_t lstm_persist_used_partial_bytes(const HostPlan& hp, int batch, int steps);
 constexpr size_t kLstmCtlBytes = 2048;
 int    launch_lstm_persist(const LstmPersistLaunch& P);
+// The same with one exchange per step (workgroups own whole units): both weight types, every BRC tile shape, batches to 64.
+bool   lstm_units_supported(const HostPlan& hp, int H, int I, int batch, int device);
+int    lstm_units_min_steps(const HostPlan& hp);                   // shortest sequence it pays for
+size_t lstm_units_step_bytes(const HostPlan& hp, int H, int I, int batch);   // of P.xg, per step
+int    launch_lstm_units(const LstmPersistLaunch& P);              // clears ctl itself; uses neither partials nor xg_step_elems
 
 // A chain of layers in one launch (BRC plans of one weight type with whole block rows per work item, batch 1).
 struct ChainPersistLayer {

@@ -259,6 +259,7 @@ int build_host_plan(const pivot_fc_desc& d, const void* W, int w_space, const ui
             hp.row_ptr[i + 1] = (int32_t)hp.col_idx.size();
         }
         hp.T = (int)hp.col_idx.size();
+        for (int i = 0; i < hp.nbr; ++i) hp.max_row_tiles = std::max(hp.max_row_tiles, hp.row_ptr[i + 1] - hp.row_ptr[i]);
         size_t nvals = (size_t)hp.T * d.bh * d.bw;
         if (nvals * elem_size(d.wdtype) > ((size_t)1 << 36)) { set_error("kept tiles exceed 64 GiB"); return PIVOT_E_SHAPE; }
         hp.vals.assign(nvals * elem_size(d.wdtype), 0);

@@ -1,0 +1,81 @@
+"""The one-launch recurrent form whose workgroups own whole units: every
+instantiation, ragged sizes, both weight types and several tile shapes against
+the CPU oracle, and infinities and NaNs against the launch-per-step form.
+Needs a GPU."""
+import numpy as np
+import pytest
+
+from oracle import pivot_oracle as O
+from paper_1712_01084_amd import binding as B
+from paper_1712_01084_amd import workloads as WL
+
+import gpu_util as G
+from test_gpu_chain import FREE_RUN_GATE, _lstm_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(H, I, steps, batch, bh, bw, wdtype, frac, seed=11):
+    rng = np.random.default_rng(seed)
+    fc = WL.gen_fc(4 * H, H + I, bh, bw, frac, seed, mask="uniform", wdtype=wdtype, batch=batch, act=WL.ACT_NONE, rng=rng, draw_x=False)
+    td = np.float16 if wdtype == WL.F16 else np.float32
+    xs = rng.standard_normal((steps, batch, I)).astype(td)
+    h0 = (0.5 * rng.standard_normal((batch, H))).astype(np.float32)
+    c0 = rng.standard_normal((batch, H)).astype(np.float32)
+    return WL.LSTMProblem(fc, H, I, xs, h0, c0)
+
+
+# (H, I, batch, bh, bw, dtype): pairs of k-steps (up to 8 rows, short and long K), single teams, several teams, two
+# batch blocks per team; H, I no multiples of anything (the copy of x), H and I at the edges of a k-step
+CASES = [(64, 32, 1, 16, 32, "f16"), (65, 33, 8, 8, 8, "f16"), (31, 1, 3, 16, 16, "f16"), (512, 256, 8, 64, 64, "f16"),
+         (1100, 40, 2, 16, 32, "f16"), (2048, 8, 7, 16, 32, "f16"), (513, 33, 12, 32, 16, "f16"), (400, 24, 40, 16, 64, "f16"),
+         (1000, 500, 32, 16, 32, "f16"), (200, 96, 64, 16, 32, "f16"),
+         (70, 13, 5, 8, 16, "f32"), (256, 128, 8, 16, 32, "f32"), (700, 4, 3, 32, 8, "f32"), (400, 24, 12, 16, 32, "f32"),
+         (250, 60, 20, 64, 64, "f32"), (300, 300, 48, 8, 8, "f32")]
+
+
+@pytest.mark.parametrize("H,I,batch,bh,bw,dtype", CASES)
+def test_sequence_against_the_oracle(H, I, batch, bh, bw, dtype):
+    # fp32 sums of fp16 or fp32 products in another order, sigmoids of fp32: the free-run gate of the other forms
+    wdtype = WL.F16 if dtype == "f16" else WL.F32
+    lp = _problem(H, I, 5, batch, bh, bw, wdtype, 0.3)
+    p = lp.fc
+    Wd = O.dense_masked_natural(p.Wp, p.tile_mask, p.prow, p.pcol, p.bh, p.bw)
+    h_ref, c_ref, _ = O.oracle_lstm(Wd, p.bias, lp.xs, lp.h0, lp.c0, H, state_dtype=np.float16 if dtype == "f16" else np.float32)
+    plan = G.dev_plan(p, flags=B.PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS)
+    try:
+        for n in (5, 5):
+            h, c, z = _lstm_gpu(lp, plan, lp.xs[:n], lp.h0, lp.c0)
+            assert np.abs(h - h_ref).max() < FREE_RUN_GATE and np.abs(c - c_ref).max() < FREE_RUN_GATE
+            assert np.isfinite(z).all()
+        h2, c2, z2 = _lstm_gpu(lp, plan, lp.xs, lp.h0, lp.c0)
+        assert np.array_equal(h, h2) and np.array_equal(c, c2) and np.array_equal(z, z2)
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("what", ["inf x", "nan x", "inf h", "nan h"])
+def test_infinities_and_nans_reach_the_rows_of_kept_tiles_only(dtype, what):
+    # columns outside the kept tiles are zeros in this form's dense rows; a product with an infinity must not count
+    wdtype = WL.F16 if dtype == "f16" else WL.F32
+    lp = _problem(96, 40, 4, 3, 16, 32, wdtype, 0.25, seed=4)
+    bad = np.inf if what.startswith("inf") else np.nan
+    if what.endswith("x"):
+        lp.xs[1, 2, 7], lp.xs[2, 0, 39] = bad, -bad
+    else:
+        lp.h0[1, 5] = bad
+    res = []
+    for flags in (B.PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS, B.PIVOT_PLAN_LSTM_LAUNCH_PER_STEP):
+        plan = G.dev_plan(lp.fc, flags=flags)
+        try:
+            # the step that meets the value, and a few behind it
+            res.append([_lstm_gpu(lp, plan, lp.xs[:n], lp.h0, lp.c0) for n in (1, 2, 4)])
+        finally:
+            B.pivot_fc_plan_destroy(plan)
+    for one, per in zip(*res):
+        for a, b in zip(one, per):
+            assert np.array_equal(np.isnan(a), np.isnan(b))
+            fin = np.isfinite(b)
+            assert np.array_equal(a[~fin & ~np.isnan(b)], b[~fin & ~np.isnan(b)])
+            assert np.abs(a[fin] - b[fin]).max() < 20 * FREE_RUN_GATE if fin.any() else True
