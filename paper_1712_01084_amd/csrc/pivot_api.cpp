@@ -132,6 +132,7 @@ int pivot_fc_plan(const pivot_fc_desc* desc, const void* W, int w_space, const u
     if (!p) { set_error("out of host memory"); return PIVOT_E_ALLOC; }
     int rc = build_host_plan(*desc, W, w_space, tile_mask, prow, pcol, bias, p->host);
     if (rc != PIVOT_OK) { delete p; return rc; }
+    p->host.ticket_bytes = count_ticket_bytes(p->host);
     p->device = desc->device;
     if (p->device >= 0) {
         rc = upload(p);

@@ -41,6 +41,7 @@ struct HostPlan {
     pivot_fc_desc d{};
     int nbr = 0, nbc = 0, M_pad = 0, K_pad = 0, T = 0, chunk_tiles = 0, nchunks = 0, wg_waves = 4, row_slices = 1;
     int max_row_tiles = 0;             // kept tiles of the longest block row
+    size_t ticket_bytes = 0;           // count_ticket_bytes, once the schedule stands
     int max_parts = 1;                 // largest number of pieces of one block row
     int uniform_ct = 0, uniform_parts = 0;  // set when every block row keeps the same number of tiles and every
                                        // chunk is full: chunk i = tiles [i*ct, (i+1)*ct) of block row i / parts
@@ -149,7 +150,10 @@ int    fc_batch_tile(const FcShape& s, int batch);
 bool   fc_wants_frag(const FcShape& s, int batch);          // the form that reads x in fragment order
 int    fc_row_slices(const FcShape& s, int batch, int want);
 // Workspace of one layer application: [arrival counters][partials of split rows][x in fragment order (batched matrix path)]
-size_t fc_ticket_bytes(const HostPlan& hp);                   // the same for every batch (0 without split block rows)
+// Arrival counters: the same for every batch (0 without split block rows).  Counted once per plan: the count goes over
+// all batches and sources of x, 4 us of host time that every run of a plan with split block rows paid twice.
+size_t count_ticket_bytes(const HostPlan& hp);
+inline size_t fc_ticket_bytes(const HostPlan& hp) { return hp.ticket_bytes; }
 size_t fc_partial_bytes(const HostPlan& hp, int batch, int x_from);
 size_t fc_gather_bytes(const HostPlan& hp, int batch);        // fragment-order copy of a natural-order x
 // describe != NULL: nothing is launched, *describe receives the name of the kernel instantiation the call would run

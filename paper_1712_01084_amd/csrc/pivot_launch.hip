@@ -180,7 +180,7 @@ int fc_row_slices(const FcShape& s, int batch, int want) {
 // place of everything that follows it in a workspace, does not depend on the batch of a run: counters are only
 // ever touched as counters (every run leaves them at zero), never overlaid by another batch's partial sums.
 // Plans without split block rows use no counters.
-size_t fc_ticket_bytes(const HostPlan& hp) {
+size_t count_ticket_bytes(const HostPlan& hp) {
     if (hp.max_parts <= 1) return 0;
     int most = 1;                            // launch rows x row slices of any batch, wherever x comes from
     for (int x_from : {kXNoCopy, kXNatural, kXBlock}) {
