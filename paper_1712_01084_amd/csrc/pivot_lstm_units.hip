@@ -90,9 +90,9 @@ __device__ __forceinline__ bool unit_keep_waiting(uint32_t* ctl, uint32_t& spins
     return true;
 }
 
-// What crosses workgroups is finite, -0xFF..F ("not there yet": no value has these bits) or, of NaN and of an
-// infinite h_0 alone, something else; every NaN is handed over as the bits below the mark.  So one unsigned maximum
-// over the words read tells both: all ones, or an exponent of all ones behind a sign bit.
+// What crosses workgroups is a finite value, the mark (all bits set: not there yet), a NaN, which is always handed
+// over as the bits just below the mark, or an infinite h_0.  So one unsigned maximum over the words read tells the
+// mark (all ones) and NaNs (an exponent of all ones behind a sign bit); only in step 0 infinities are looked for.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 template <typename WT> struct Pattern;
 template <> struct Pattern<_Float16> {
@@ -194,7 +194,8 @@ __global__ void __launch_bounds__(kUT, 2) lstm_units_kernel(UnitArgs a) {
     // Scatters the columns that `place` accepts of the wavefront's four rows of a 16-row block.  The rows' tiles make
     // one list, of which a lane takes VEC consecutive columns of a tile at a time and four such pieces together, so
     // that a pass over typical rows costs one trip to memory and a long row shares its trips (2048 units, 1024 inputs,
-    // row lengths by a Zipf law, before the first step: a row at a time 90 us, four rows side by side 33, one list 20).
+    // rows by a Zipf law: 32 steps at batch 1 184.6 us with a row at a time, 155.4 with four rows side by side; 4 steps
+    // at batch 8 63.8 us with four rows side by side, 55.2 with one list).
     const int vpt = a.bw / VEC;                         // vectors per tile row
     auto scatter_rows = [&](int block, auto&& place) {
         int t0[4], rr[4], end[4];
