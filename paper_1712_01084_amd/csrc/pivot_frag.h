@@ -165,12 +165,20 @@ __global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcA
         for (int rs = 0; rs < RS; ++rs)
             #pragma unroll
             for (int nb = 0; nb < NBT; ++nb) acc[rb][rs][nb] = f32x4(0);
-    auto consume = [&](int u, int s) {
-        if constexpr (TPG > 1) {                        // tiles a last, incomplete group does not have
-            const bool have = (wave + (s / KS) * NW) * TPG + ta < ntiles;
+    // Tiles that the last, incomplete group does not have: neither the weights nor the x loaded in their place may
+    // count (zero weights alone are not enough: 0 times an infinity is a NaN).
+    auto clear_missing = [&](int u, int s) {
+        if constexpr (TPG > 1) {
+            const int t0 = (wave + (s / KS) * NW) * TPG;
             #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) w[u][rb] = have ? w[u][rb] : V(0);
+            for (int rb = 0; rb < RB; ++rb) w[u][rb] = t0 + ta < ntiles ? w[u][rb] : V(0);
+            #pragma unroll
+            for (int rs = 0; rs < RS; ++rs)
+                #pragma unroll
+                for (int nb = 0; nb < NBT; ++nb) xv[u][rs][nb] = t0 + rs * TPS + ts < ntiles ? xv[u][rs][nb] : V(0);
         }
+    };
+    auto consume = [&](int u) {
         #pragma unroll
         for (int e = 0; e < MF::NE; ++e)
             #pragma unroll
@@ -185,15 +193,30 @@ __global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcA
     for (; s0 + U < nsteps; s0 += U) {
         #pragma unroll
         for (int u = 0; u < U; ++u) {
-            consume(u, s0 + u);
+            consume(u);                                 // (never a group the wavefront ends with)
             fill_w(u, s0 + u + U);
             fill_x(u, s0 + u + U);
             __builtin_amdgcn_sched_barrier(0);          // a slot is refilled as soon as it is consumed
         }
     }
-    #pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (s0 + u < nsteps) consume(u, s0 + u);
+    // The masks only in the wavefront that has the incomplete group (in all of them: up to 1 us a call), chosen per
+    // step for stacked tiles and once for the others (the other way round 0.2-0.4 us slower).
+    const bool incomplete = TPG > 1 && (wave + imax * NW) * TPG + TPG > ntiles;
+    if (RS == 2 || !incomplete) {
+        #pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u < nsteps) {
+                if (RS == 2 && (wave + ((s0 + u) / KS) * NW) * TPG + TPG > ntiles) clear_missing(u, s0 + u);
+                consume(u);
+            }
+    } else {
+        #pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u < nsteps) {
+                clear_missing(u, s0 + u);
+                consume(u);
+            }
+    }
 
     // Every wavefront's sums go to LDS, the epilogue adds them.  Accumulator element v of lane l is
     // C[row 4(l/16)+v][batch column l%16]; of stacked tiles rows 8-15 of the second set (lanes 32-63) belong to

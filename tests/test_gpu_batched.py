@@ -13,7 +13,8 @@ from paper_1712_01084_amd import binding as B
 from paper_1712_01084_amd import workloads as WL
 
 import gpu_util as G
-from test_gpu_chain import _check_chain
+from oracle import pivot_oracle as O
+from test_gpu_chain import _check_chain, _run_chain
 
 pytestmark = pytest.mark.gpu
 
@@ -65,6 +66,40 @@ def test_natural_input(wdtype, M, K, bh, bw, batch, frac):
             assert err <= 1e-5
     finally:
         B.pivot_fc_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
+@pytest.mark.parametrize("bh,bw", SHAPES)
+def test_infinities_reach_the_rows_of_their_tiles_and_stay_infinite(bh, bw, wdtype):
+    # Tiles are taken in groups (up to 8 of them), whose last is filled up with copies of the item's last tile: an
+    # infinity in that tile's x must not meet the copies' zero weights.  The first layer's bias puts the infinity
+    # into one column of the second one's input, each time in another block row's last tile, behind which every
+    # number of tiles from 1 to 11 occurs; with ReLU a NaN would be stored as 0.
+    for i, (batch, act) in enumerate([(2, WL.ACT_RELU), (17, WL.ACT_NONE), (40, WL.ACT_RELU)]):
+        probs = WL.config4(seed=90 + i, batch=batch, dims=(60, 11 * bw - 3, 11 * bh - 1), bh=bh, bw=bw, frac=0.7, wdtype=wdtype)
+        p = probs[1]
+        p.act = act
+        p.tile_mask[:] = 0
+        for br in range(11):
+            p.tile_mask[br, np.random.default_rng(br).permutation(11)[:br + 1]] = 1
+        br = (3, 4, 8)[i]
+        c = int(np.flatnonzero(p.tile_mask[br])[-1]) * bw + 2
+        j = int(p.pcol[c])
+        probs[0].bias[j] = np.inf
+        y = _run_chain(probs)
+        h, _ = G.oracle_of(probs[0])
+        h = h.astype(np.float16 if wdtype == WL.F16 else np.float32).astype(np.float64)
+        assert np.isinf(h[:, j]).all() and np.isfinite(np.delete(h, j, axis=1)).all()
+        kept = O.unpivot_weights(np.ascontiguousarray(O.expand_tile_mask(p.tile_mask, bh, bw, p.M, p.K)[:p.M, :p.K]), p.prow, p.pcol) != 0
+        W = O.unpivot_weights(p.Wp, p.prow, p.pcol).astype(np.float64)
+        W[~kept] = 0.0
+        rows = kept[:, j]
+        ref, D = O.fc_dense(W, np.where(np.isinf(h), 0.0, h), p.bias, act), O.error_scale(W, np.where(np.isinf(h), 0.0, h), p.bias)
+        assert rows.any() and not rows.all() and (W[rows, j] != 0).all()
+        want = np.where(W[rows, j] > 0, np.inf, 0.0 if act == WL.ACT_RELU else -np.inf)
+        print("%s %dx%d batch %d: %d rows" % (wdtype, bh, bw, batch, rows.sum()), flush=True)
+        assert np.array_equal(y[:, rows], np.broadcast_to(want, (batch, rows.sum())))
+        assert O.max_scaled_error(y[:, ~rows], ref[:, ~rows], D[:, ~rows]) <= G.TOL[wdtype]
 
 
 def test_static_scratch_without_room_for_the_copy():
