@@ -251,7 +251,7 @@ int run_layer(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, void*
     if (rc != PIVOT_OK) return rc;
     if (!x_dev || !y_dev) { set_error("x_dev and y_dev are required"); return PIVOT_E_NULL; }
     if (ldx < plan->host.d.K || ldy < plan->host.d.M) { set_error("ldx/ldy smaller than K/M"); return PIVOT_E_SHAPE; }
-    if (x_from == kXNatural && fc_gather_bytes(plan->host, batch) > 0 && !xg) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
+    if (x_from != kXNoCopy && fc_gather_bytes(plan->host, batch) > 0 && !xg) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
     rc = natural_input(plan, x_dev, ldx, batch, xg, stream, L);
     if (rc != PIVOT_OK) return rc;
     L.scatter = plan->dev.prow_pad;

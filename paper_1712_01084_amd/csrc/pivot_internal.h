@@ -140,8 +140,9 @@ enum { kPathVector = 0, kPathMfmaLds = 1, kPathFrag = 2, kPathMfmaXrow = 3 };
 // kernel out); `chunk_tiles`, `xrow_len`: the plan's chunk size and HostPlan::xrow_len() (0 rules out the
 // matrix-core kernel that gathers its fragments from a copy of x in LDS); `x_from`: where x comes from (kXNatural:
 // the caller, in natural order; kXNoCopy: the same, with no scratch for a fragment-order copy, which rules out the
-// kernel that reads one; kXBlock: the layer or cell before, which writes the order the kernel wants).
-enum { kXNoCopy = 0, kXNatural = 1, kXBlock = 2 };
+// kernel that reads one; kXNaturalRows16: as kXNatural, that kernel in launch rows of 16 batch rows, whose partial sums
+// take less scratch where the last launch row is short; kXBlock: the layer or cell before, which writes the order the kernel wants).
+enum { kXNoCopy = 0, kXNatural = 1, kXBlock = 2, kXNaturalRows16 = 3 };
 struct FcShape { int layout, wdtype, bh, bw, lds_tiles, chunk_tiles, xrow_len, mean_tiles, nchunks, x_from; };   // mean_tiles: kept tiles per work item, rounded up
 inline int mean_tiles_of(int T, int nchunks) { return nchunks > 0 ? (T + nchunks - 1) / nchunks : 0; }
 inline FcShape fc_shape(const HostPlan& h, int x_from) { return FcShape{h.d.layout, h.d.wdtype, h.d.bh, h.d.bw, h.lds_tiles(), h.chunk_tiles, h.xrow_len(), mean_tiles_of(h.T, h.nchunks), h.nchunks, x_from}; }
@@ -154,6 +155,7 @@ int    fc_row_slices(const FcShape& s, int batch, int want);
 // all batches and sources of x, 4 us of host time that every run of a plan with split block rows paid twice.
 size_t count_ticket_bytes(const HostPlan& hp);
 inline size_t fc_ticket_bytes(const HostPlan& hp) { return hp.ticket_bytes; }
+size_t run_ticket_bytes(const HostPlan& hp, int batch, int x_from);   // of one run
 size_t fc_partial_bytes(const HostPlan& hp, int batch, int x_from);
 size_t fc_gather_bytes(const HostPlan& hp, int batch);        // fragment-order copy of a natural-order x
 // describe != NULL: nothing is launched, *describe receives the name of the kernel instantiation the call would run
@@ -239,7 +241,7 @@ int    launch_chain_persist(const ChainPersistLaunch& C);
 namespace pivot {
 // One layer application on a natural-order x, its scratch given as three separate regions: arrival counters
 // (fc_ticket_bytes, zero between runs), partial sums (fc_partial_bytes) and the fragment-order copy of x
-// (fc_gather_bytes); a region of size 0 may be NULL.  x_from: kXNatural, or kXNoCopy to run without
+// (fc_gather_bytes); a region of size 0 may be NULL.  x_from: kXNatural, kXNaturalRows16, or kXNoCopy to run without
 // a fragment-order copy of x, whatever the batch (xg is not used).  Checks its arguments like pivot_fc_run.
 int run_layer(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, void* y_dev, int64_t ldy, int batch,
               void* tickets, void* partials, void* xg, void* stream, int x_from = 1 /* kXNatural */);

@@ -111,7 +111,7 @@ bool fc_wants_frag(const FcShape& s, int batch) { return fc_path(s, batch) == kP
 static void frag_split(const FcShape& s, int batch, int* slices, int* blocks) {
     int sl = s.bh > 32 ? s.bh / 32 : 1;
     const int need = (batch + 15) / 16;
-    int nbt = need > 2 ? 4 : need;
+    int nbt = s.x_from == kXNaturalRows16 ? 1 : (need > 2 ? 4 : need);
     auto items = [&]() { return (long long)s.nchunks * sl * ((need + nbt - 1) / nbt); };
     while (items() < 256 && s.bh / sl > 16) sl *= 2;
     while (items() < 256 && nbt > 1) nbt /= 2;
@@ -175,22 +175,28 @@ int fc_row_slices(const FcShape& s, int batch, int want) {
     return sl;
 }
 
-// Arrival counters of split block rows: one 256-byte line per (launch row, block row, row slice).  The region is
-// sized for the largest number of launch rows any batch up to 64 can have, so that its size, and with it the
-// place of everything that follows it in a workspace, does not depend on the batch of a run: counters are only
-// ever touched as counters (every run leaves them at zero), never overlaid by another batch's partial sums.
-// Plans without split block rows use no counters.
-size_t count_ticket_bytes(const HostPlan& hp) {
+// Arrival counters of split block rows: one 256-byte line per (launch row, block row, row slice).  Plans without split
+// block rows use none.
+size_t run_ticket_bytes(const HostPlan& hp, int batch, int x_from) {
     if (hp.max_parts <= 1) return 0;
-    int most = 1;                            // launch rows x row slices of any batch, wherever x comes from
+    const FcShape s = fc_shape(hp, x_from);
+    const int nbt = fc_batch_tile(s, batch), launch_rows = (batch + nbt - 1) / nbt;
+    return (size_t)4 * kTicketStride * hp.nbr * launch_rows * fc_row_slices(s, batch, hp.row_slices);
+}
+
+// The counter region of a workspace is sized for the largest number of launch rows any batch up to 64 can have, so
+// that its size, and with it the place of everything that follows it, does not depend on the batch of a run: counters
+// are only ever touched as counters (every run leaves them at zero), never overlaid by another batch's partial sums.
+// kXNoCopy, which only runs with the built-in scratch take, counts where the vector kernel is all there is beside the
+// form with the copy; fp16 tiles of an MFMA shape have forms of 8 and 16 rows, and the vector kernel, with up to 16
+// launch rows, only stands in for them where the copy does not fit (counted there, by run_ticket_bytes).
+size_t count_ticket_bytes(const HostPlan& hp) {
+    size_t most = 0;
     for (int x_from : {kXNoCopy, kXNatural, kXBlock}) {
-        const FcShape s = fc_shape(hp, x_from);
-        for (int batch = 1; batch <= 64; ++batch) {
-            const int nbt = fc_batch_tile(s, batch);
-            most = std::max(most, (batch + nbt - 1) / nbt * fc_row_slices(s, batch, hp.row_slices));
-        }
+        if (x_from == kXNoCopy && mfma_kind(hp.d.wdtype, hp.d.bh, hp.d.bw) >= 0) continue;
+        for (int batch = 1; batch <= 64; ++batch) most = std::max(most, run_ticket_bytes(hp, batch, x_from));
     }
-    return (size_t)4 * kTicketStride * hp.nbr * most;
+    return most;
 }
 
 size_t fc_partial_bytes(const HostPlan& hp, int batch, int x_from) {

@@ -8,6 +8,7 @@
 // as they take the workspace there.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -72,11 +73,17 @@ int pivot_fc_run_static(const pivot_fc_plan_t* plan, const void* x_dev, int64_t 
     if (plan->device < 0) { set_error("host-only plan (device = -1) cannot run"); return PIVOT_E_NO_DEVICE; }
     if (batch < 1 || batch > 64) { set_error("batch %d outside 1..64", batch); return PIVOT_E_SHAPE; }
     const HostPlan& h = plan->host;
-    const size_t nt = fc_ticket_bytes(h);
-    size_t np = fc_partial_bytes(h, batch, kXNatural), ng = fc_gather_bytes(h, batch);
-    // a fragment-order copy of x that does not fit beside the rest: the kernels that need none
-    const bool frag_ok = np + ng <= kDataBytes;
-    if (!frag_ok) { np = fc_partial_bytes(h, batch, kXNoCopy); ng = 0; }
+    // the form pivot_fc_run takes; where its scratch does not fit, shorter launch rows, then the kernels that need no
+    // fragment-order copy of x
+    size_t nt = 0, np = 0, ng = 0;
+    int x_from = kXNoCopy;
+    for (int form : {kXNatural, kXNaturalRows16, kXNoCopy}) {
+        x_from = form;
+        nt = std::max(fc_ticket_bytes(h), run_ticket_bytes(h, batch, form));
+        np = fc_partial_bytes(h, batch, form);
+        ng = form == kXNoCopy ? 0 : fc_gather_bytes(h, batch);
+        if (nt <= kCounterBytes && np + ng <= kDataBytes) break;
+    }
     if (nt > kCounterBytes || np + ng > kDataBytes) {
         set_error("this plan at batch %d needs %zu bytes of arrival counters and %zu bytes of partial sums and staged "
                   "input; the built-in scratch holds %zu and %zu: use pivot_fc_run with a workspace",
@@ -86,7 +93,7 @@ int pivot_fc_run_static(const pivot_fc_plan_t* plan, const void* x_dev, int64_t 
     unsigned char* base = nullptr;
     const int rc = scratch_of(plan->device, stream, &base);
     if (rc != PIVOT_OK) return rc;
-    return run_layer(plan, x_dev, ldx, y_dev, ldy, batch, base, base + kCounterBytes, base + kCounterBytes + np, stream, frag_ok ? kXNatural : kXNoCopy);
+    return run_layer(plan, x_dev, ldx, y_dev, ldy, batch, base, base + kCounterBytes, base + kCounterBytes + np, stream, x_from);
 }
 
 }  // extern "C"

@@ -102,6 +102,43 @@ def test_infinities_reach_the_rows_of_their_tiles_and_stay_infinite(bh, bw, wdty
         assert O.max_scaled_error(y[:, ~rows], ref[:, ~rows], D[:, ~rows]) <= G.TOL[wdtype]
 
 
+def test_static_scratch_takes_plans_whose_runs_need_few_counters():
+    # 1040 split block rows: 16 launch rows of 4 batch rows would need more counters than the built-in scratch holds,
+    # but no run of this plan takes that form while the copy of x fits
+    p = WL.gen_fc(16640, 1088, 16, 32, 1.0, seed=83, wdtype=WL.F16, batch=40)
+    plan = G.dev_plan(p, chunk_tiles=32)
+    try:
+        st = torch.cuda.current_stream().cuda_stream
+        y_ref, D = G.oracle_of(p)
+        for batch in (1, 40):
+            xd, y = torch.from_numpy(p.x[:batch]).cuda(), torch.full((batch, p.M), float("nan"), device="cuda")
+            B.pivot_fc_run_static(plan, xd.data_ptr(), p.K, y.data_ptr(), p.M, batch, st)
+            torch.cuda.synchronize()
+            assert G.O.max_scaled_error(y.cpu().numpy().astype(np.float64), y_ref[:batch], D[:batch]) <= 1e-5
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
+def test_static_scratch_takes_shorter_launch_rows_where_long_ones_do_not_fit():
+    # 3658 pieces of 16 rows: partial sums of one launch row of 64 batch rows are 15 MB, of three of 16 rows 11.2 MB, and
+    # the nine launch rows of the kernel without a copy of x need too many counters.  Whole numbers: every order of
+    # summation gives the same bits
+    M, K, batch = 29264, 2112, 33
+    rng = np.random.default_rng(84)
+    W = np.ascontiguousarray(np.tile(rng.integers(-2, 3, (77, K)).astype(np.float16), (M // 77 + 1, 1))[:M])
+    x = torch.from_numpy(rng.integers(-2, 3, (batch, K)).astype(np.float16)).cuda()
+    ident = lambda n: np.arange(n, dtype=np.int32)
+    plan = B.pivot_fc_plan(M, K, 16, 32, B.PIVOT_F16, W, B.PIVOT_W_PIVOTED, np.ones((M // 16, K // 32), np.uint8), ident(M), ident(K),
+                           None, chunk_tiles=33, device=0)
+    try:
+        y = torch.full((batch, M), float("nan"), device="cuda")
+        B.pivot_fc_run_static(plan, x.data_ptr(), K, y.data_ptr(), M, batch, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(y, x.float() @ torch.from_numpy(W).cuda().float().t())
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
 def test_static_scratch_without_room_for_the_copy():
     # 64 rows of 50000 fp32 columns are 12.8 MB, more than the built-in scratch holds: the kernels that need no copy run
     p = WL.gen_fc(96, 50000, 32, 32, 0.9, seed=82, batch=64)

@@ -217,6 +217,24 @@ def test_error_paths_return_codes():
     B.pivot_fc_plan_destroy(None)                             # NULL-safe
 
 
+def test_workspace_holds_what_runs_take():
+    # counters: one 256-byte line per block row and launch row, of which no batch of an fp16 plan with split rows
+    # needs more than one per 8 batch rows; partial sums of whole launch rows of at most 64; the copy of x
+    M, K, bh, bw = 20000, 3072, 16, 32
+    nbr, nbc = M // bh, K // bw
+    tm = WL.mask_zipf(np.random.default_rng(1), nbr, nbc, 0.125)
+    plan = B.pivot_fc_plan(M, K, bh, bw, B.PIVOT_F16, np.zeros((M, K), np.float16), B.PIVOT_W_PIVOTED, tm, np.arange(M, dtype=np.int32),
+                           np.arange(K, dtype=np.int32), None, chunk_tiles=1, device=-1)
+    try:
+        n = len(B.pivot_fc_plan_host_view(plan)["chunks"])
+        up = lambda v: -(-v // 256) * 256
+        for batch in (1, 2, 8, 33, 64):
+            size = B.pivot_fc_workspace_bytes(plan, batch)
+            assert size <= 256 * nbr * 8 + up(4 * n * bh * (batch if batch <= 2 else 64 * -(-batch // 64) if batch > 32 else 16 * -(-batch // 16))) + up(2 * K * batch), batch
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
 def test_host_only_plan_cannot_run_and_workspace_sizes():
     p = WL.gen_fc(32, 32, 8, 8, 0.5, seed=5)
     plan = _host_plan(p, chunk_tiles=1)
