@@ -480,7 +480,7 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
             L.out_f16 = (p->host.d.wdtype == PIVOT_F16);
             const HostPlan& next = plan->layers[l + 1]->host;
             if (fc_wants_frag(fc_shape(next, kXBlock), batch)) {
-                L.out_frag = 1; L.zero_from = next.d.K; L.zero_to = next.K_pad;
+                L.out_frag = 1; L.out_pad = next.K_pad - next.d.K;
             }
         } else {
             L.scatter = keep ? p->dev.rowid_pad : p->dev.prow_pad;

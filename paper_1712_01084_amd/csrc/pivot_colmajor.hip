@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_LEAD_PARAMS,
         for (int v = 0; v < VEC; ++v) red[wave * N + rq * VEC + v] = acc[v];
     }
     __syncthreads();
-    finish_rows<BH, 1, NT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
+    finish_rows<BH, 1, NT, kEither>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
 }
 
 template <typename WT, int LAYOUT, int BH, int BW>

@@ -47,10 +47,7 @@ struct FcArgs {
     float*         partials;
     uint32_t*      tickets;
     long long ldx, ldy;
-    int batch, act, out_f16, nchunks, nbr, xs_stride;
-    int out_shift, out_group;   // column c of batch row b of y lies at b*ldy + (c >> out_shift)*out_group + (c mod
-                                // 1 << out_shift): shift 0 and group 1 for rows, fragment order (frag_index) otherwise
-    int zero_from, zero_to;     // columns of a fragment-order y to clear (the consumer's padding columns)
+    int batch, act, out_form, nchunks, nbr, xs_stride;   // out_form: kOutF16 | kOutFrag | padding columns << kOutPadShift
     int bh_full;                // rows of a whole tile (the kernels' BH is the height of one row slice)
     int tile_elems;             // bh_full * bw
     int uniform_ct;             // > 0: every chunk has exactly this many tiles and chunk i starts at tile i*uniform_ct,
@@ -116,9 +113,13 @@ struct FcArgs {
     ((a).uniform_ct > 0 ? ((a).uniform_ct | ((a).uniform_parts << 16)) : (a).chunk_tiles), \
     ((a).bh_full | ((a).batch << 7) | (int)((unsigned)(a).xn_vecs << 14))
 
-// Per-dtype / per-path launchers, each in its own translation unit.
+#define PIVOT_GEMV_PASS p_chunks, p_idx, p_vals, p_x, p_bias, p_scatter, q_ct_parts, q_misc
+
+// Per-dtype / per-path launchers, each in its own translation unit (..._chain: y in fragment order).
 int launch_gemv_f32(const FcArgs& a, int bhs, int bw, int nb, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
 int launch_gemv_f16(const FcArgs& a, int bhs, int bw, int nb, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
+int launch_gemv_f32_chain(const FcArgs& a, int bhs, int bw, int nb, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
+int launch_gemv_f16_chain(const FcArgs& a, int bhs, int bw, int nb, int nw, int xres, dim3 grid, size_t smem, hipStream_t st);
 int launch_frag_f32_8(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
 int launch_frag_f32_16(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
 int launch_frag_f32_32(const FcArgs& a, int bw, int nbt, int nw, dim3 grid, hipStream_t st);
@@ -155,8 +156,11 @@ __device__ __forceinline__ float dot_vec(const f16x8& w, const f16x8& x, float a
     return acc;
 }
 
-__device__ __forceinline__ void store_out(void* y, long long idx, float v, int out_f16) {
-    if (out_f16) reinterpret_cast<_Float16*>(y)[idx] = (_Float16)v;
+constexpr int kOutF16 = 1;     // y is fp16, else fp32
+constexpr int kOutFrag = 2;    // y is in fragment order (frag_index) with ldy columns, else rows of ldy elements
+constexpr int kOutPadShift = 2;   // above: how many of the last columns of a y in fragment order no row lands in
+__device__ __forceinline__ void store_out(void* y, long long idx, float v, int out_form) {
+    if (out_form & kOutF16) reinterpret_cast<_Float16*>(y)[idx] = (_Float16)v;
     else         reinterpret_cast<float*>(y)[idx] = v;
 }
 
@@ -484,26 +488,34 @@ __device__ __forceinline__ Chunk load_chunk(int uniform_ct, int uniform_parts, c
     return c;
 }
 
+// A y in fragment order is the input of the next layer: its padding columns, which no row lands in.  (They are told
+// by what the epilogue has loaded anyway; two more arguments were fetched in the middle of the staging.)
+template <int NBT, int NT>
+__device__ __forceinline__ void clear_padding(const FcArgs& a, int b0, int tid) {
+    if (blockIdx.x != 0 || blockIdx.z != 0) return;
+    const int npad = a.out_form >> kOutPadShift, first = (int)a.ldy - npad;
+    for (int i = tid; i < npad * NBT; i += NT) {
+        const int b = b0 + i % NBT, c = first + i / NBT;
+        if (b < a.batch) store_out(a.y, (long long)frag_index(b, c, a.batch, 2 + (a.out_form & kOutF16)), 0.f, a.out_form);
+    }
+}
+
 // Everything after the per-wave sums are in LDS `red[w*N + idx]`, idx = j*BH + r
 // (j = batch column of this launch tile, r = row inside the row slice):
 // hand-over between the chunks of a split block row (Section 4.1.5: tiles that
 // share rows need one more reduction), bias, activation, store through P_row.
-template <int BH, int NBT, int NT>
+// OUT: how y is written.  The vector kernel and those that hold x in LDS have a kernel of their own for fragment order
+// (fc_..._chain_kernel): chosen output by output, or once in the epilogue, the form that is not taken cost every
+// launch 0.03-0.2 us (us, both forms in one kernel / one: 1000x1000 fp32 16x32 tiles, batch 2 3.61 / 3.50; 256x256 fp16
+// 16x16, batch 16 3.72 / 3.65).  The batched kernel, which follows itself in a chain, keeps both in one: with two kernels
+// a chain fetches the code of both (4096-4096-1000 fp32 32x64, batch 3 11.8 / 12.3).
+enum { kRows = 0, kFragOrder = 1, kEither = 2 };
+template <int BH, int NBT, int NT, int OUT>
 __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, int nred, int br, int slot,
                                             int first, int nparts, const RowPre<BH, BH * NBT, NT>& rp,
                                             int b0, int tid, int* s_flag) {
     constexpr int N = BH * NBT;
     const int gy = blockIdx.y, slice = blockIdx.z, SL = gridDim.z;
-    // a y that is the input of the next layer: its padding columns, which no row lands in (behind everything else:
-    // looked at earlier, these arguments cost every launch 0.1 us)
-    auto clear_padding = [&]() {
-        if (a.zero_from < a.zero_to && blockIdx.x == 0 && slice == 0) {
-            for (int i = tid; i < (a.zero_to - a.zero_from) * NBT; i += NT) {
-                const int b = b0 + i % NBT, c = a.zero_from + i / NBT;
-                if (b < a.batch) store_out(a.y, (long long)frag_index(b, c, a.batch, a.out_shift), 0.f, a.out_f16);
-            }
-        }
-    };
     if (nparts > 1) {
         float* mine = a.partials + (((size_t)gy * a.nchunks + slot) * SL + slice) * N;
         for (int idx = tid; idx < N; idx += NT) {
@@ -528,29 +540,36 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
             *s_flag = last;
         }
         __syncthreads();
-        if (!*s_flag) { clear_padding(); return; }
-    }
-    #pragma unroll
-    for (int k = 0; k < RowPre<BH, N, NT>::CNT; ++k) {
-        const int idx = tid + k * NT;
-        if (idx >= N) break;
-        const int j = idx / BH;
-        if (b0 + j >= a.batch) continue;
-        float s = 0.f;
-        if (nparts > 1) {
-            const float* p = a.partials + (((size_t)gy * a.nchunks + first) * SL + slice) * N + idx;
-            for (int q = 0; q < nparts; ++q) s += agent_load(p + (size_t)q * SL * N);
-        } else {
-            for (int w = 0; w < nred; ++w) s += red[w * N + idx];
+        if (!*s_flag) {
+            if (OUT == kFragOrder || (OUT == kEither && (a.out_form & kOutFrag))) clear_padding<NBT, NT>(a, b0, tid);
+            return;
         }
-        const float v = apply_act(s + rp.bias[k], a.act);
-        if ((PIVOT_ABLATE & 8) && !(v == 12345.678f)) continue;      // ablation: computed, never stored
-        if (rp.dst[k] < 0) continue;
-        const long long at = (long long)(b0 + j) * a.ldy + (long long)(rp.dst[k] >> a.out_shift) * a.out_group
-                             + (rp.dst[k] & ((1 << a.out_shift) - 1));
-        store_out(a.y, at, v, a.out_f16);
     }
-    clear_padding();
+    auto finish = [&](auto&& store) {
+        #pragma unroll
+        for (int k = 0; k < RowPre<BH, N, NT>::CNT; ++k) {
+            const int idx = tid + k * NT;
+            if (idx >= N) break;
+            const int j = idx / BH;
+            if (b0 + j >= a.batch) continue;
+            float s = 0.f;
+            if (nparts > 1) {
+                const float* p = a.partials + (((size_t)gy * a.nchunks + first) * SL + slice) * N + idx;
+                for (int q = 0; q < nparts; ++q) s += agent_load(p + (size_t)q * SL * N);
+            } else {
+                for (int w = 0; w < nred; ++w) s += red[w * N + idx];
+            }
+            const float v = apply_act(s + rp.bias[k], a.act);
+            if ((PIVOT_ABLATE & 8) && !(v == 12345.678f)) continue;      // ablation: computed, never stored
+            if (rp.dst[k] >= 0) store(b0 + j, rp.dst[k], v);
+        }
+    };
+    if (OUT == kFragOrder || (OUT == kEither && __builtin_expect(a.out_form & kOutFrag, 0))) {
+        finish([&](int b, int c, float v) { store_out(a.y, (long long)frag_index(b, c, a.batch, 2 + (a.out_form & kOutF16)), v, a.out_form); });
+        clear_padding<NBT, NT>(a, b0, tid);
+        if (OUT == kEither) __builtin_amdgcn_endpgm();
+    }
+    if (OUT != kFragOrder) finish([&](int b, int c, float v) { store_out(a.y, (long long)b * a.ldy + c, v, a.out_form); });
 }
 
 // ---------------------------------------------------------------------------
@@ -563,8 +582,8 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
 // the copy requested before the work item's descriptor has arrived (it depends on nothing); 3 = as 2 with up
 // to 16 vectors of x per thread (long inputs, LDS beyond 64 KB: a gather of single elements from a long x
 // moves a whole cache line per element, the copy moves every line once).
-template <typename WT, int BH, int BW, int NB, int NW, int XR>
-__global__ void __launch_bounds__(NW * 64) fc_gemv_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+template <typename WT, int BH, int BW, int NB, int NW, int XR, int OUT>
+__device__ __forceinline__ void fc_gemv_body(PIVOT_GEMV_PARAMS, const FcArgs& a) {
     using V = typename Elem<WT>::vec;
     constexpr int VEC = Elem<WT>::VEC;
     constexpr int NT  = NW * 64;
@@ -744,12 +763,21 @@ __global__ void __launch_bounds__(NW * 64) fc_gemv_kernel(PIVOT_GEMV_PARAMS, FcA
     }
     __syncthreads();
     PIVOT_STAMP(6);
-    finish_rows<BH, NB, NT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
+    finish_rows<BH, NB, NT, OUT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
 #ifdef PIVOT_TRACE
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // the stamp is taken when the stores have been acknowledged
 #endif
     PIVOT_STAMP(7);
     PIVOT_STAMP_FLUSH(a, NW, wave, lane);
+}
+
+template <typename WT, int BH, int BW, int NB, int NW, int XR>
+__global__ void __launch_bounds__(NW * 64) fc_gemv_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+    fc_gemv_body<WT, BH, BW, NB, NW, XR, kRows>(PIVOT_GEMV_PASS, a);
+}
+template <typename WT, int BH, int BW, int NB, int NW, int XR>
+__global__ void __launch_bounds__(NW * 64) fc_gemv_chain_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+    fc_gemv_body<WT, BH, BW, NB, NW, XR, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -795,8 +823,8 @@ template <> struct Mfma<2> : Mfma<0> {};
 // Lanes whose column is past NBS read row 0; their accumulator columns are
 // never stored.
 // ---------------------------------------------------------------------------
-template <int KIND, int BH, int BW, int NBS, int NW, int XR>
-__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+template <int KIND, int BH, int BW, int NBS, int NW, int XR, int OUT>
+__device__ __forceinline__ void fc_mfma_lds_body(PIVOT_GEMV_PARAMS, const FcArgs& a) {
     using MF = Mfma<KIND>;
     using acc_t = typename MF::acc_t;
     using WT = _Float16;
@@ -917,7 +945,16 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_kernel(PIVOT_GEMV_PARAMS,
                 red[wave * N + li * BH + rb * MR + MF::row_of(lane, v)] = acc[rb][v];
     }
     __syncthreads();
-    finish_rows<BH, NBS, NT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
+    finish_rows<BH, NBS, NT, OUT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
+}
+
+template <int KIND, int BH, int BW, int NBS, int NW, int XR>
+__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+    fc_mfma_lds_body<KIND, BH, BW, NBS, NW, XR, kRows>(PIVOT_GEMV_PASS, a);
+}
+template <int KIND, int BH, int BW, int NBS, int NW, int XR>
+__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+    fc_mfma_lds_body<KIND, BH, BW, NBS, NW, XR, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -938,8 +975,8 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_kernel(PIVOT_GEMV_PARAMS,
 // 8192 staged columns per work item; q_misc bit 31: rows are whole 16-byte
 // vectors, 16-byte aligned and densely packed (else an element-wise copy).
 // ---------------------------------------------------------------------------
-template <int KIND, int BH, int BW>
-__global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+template <int KIND, int BH, int BW, int OUT>
+__device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcArgs& a) {
     using MF = Mfma<KIND>;
     using acc_t = typename MF::acc_t;
     using WT = _Float16;
@@ -1102,7 +1139,16 @@ __global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, Fc
                 red[wave * N + li * BH + rb * MR + MF::row_of(lane, v)] = acc[rb][v];
     }
     __syncthreads();
-    finish_rows<BH, NBS, NT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
+    finish_rows<BH, NBS, NT, OUT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
+}
+
+template <int KIND, int BH, int BW>
+__global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+    fc_mfma_xrow_body<KIND, BH, BW, kRows>(PIVOT_GEMV_PASS, a);
+}
+template <int KIND, int BH, int BW>
+__global__ void __launch_bounds__(512) fc_mfma_xrow_chain_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+    fc_mfma_xrow_body<KIND, BH, BW, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
 }  // namespace pivot

@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcA
                 *reinterpret_cast<f32x4*>(red + wave * N + (nb * 16 + li) * BH + rb * 16 + lg * 4) = acc[rb][0][nb];
     }
     lds_barrier();
-    finish_rows<BH, NB, NT>(a, red, NW, br, ck.slot, ck.first, ck.nparts, rp, b0, tid, &s_flag);
+    finish_rows<BH, NB, NT, kEither>(a, red, NW, br, ck.slot, ck.first, ck.nparts, rp, b0, tid, &s_flag);
 }
 
 template <typename WT, int BH, int BW, int NBT>

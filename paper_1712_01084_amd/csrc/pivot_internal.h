@@ -26,7 +26,6 @@ constexpr int kSortSrcNone = (1 << kSortSrcBits) - 1;
 constexpr size_t frag_index(int b, int c, int batch, int shift) {
     return (((size_t)(c >> shift) * batch + b) << shift) + (c & ((1 << shift) - 1));
 }
-constexpr int frag_shift(int wdtype) { return wdtype == PIVOT_F32 ? 2 : 3; }
 
 // Which MFMA shape a row-major fp16 tile feeds: 0 = 16x16x32, 1 = 32x32x16, -1 = none.
 inline int mfma_kind(int wdtype, int bh, int bw) {
@@ -127,7 +126,7 @@ struct FcLaunch {
     void*       y; int64_t ldy;
     int out_f16;                // 1: y is fp16 (chain intermediates of F16 plans), 0: fp32
     int out_frag;               // 1: y is written in fragment order with ldy columns (chain intermediates whose consumer reads that)
-    int zero_from, zero_to;     // columns of such a y that no row lands in (the consumer's padding) and that are to be cleared
+    int out_pad;                // how many of the last columns of such a y no row lands in (the consumer's padding): they are cleared
     int batch;
     float*    partials;
     uint32_t* tickets;

@@ -238,10 +238,9 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     a.vals = L.vals; a.col_idx = L.col_idx; a.xidx = L.xidx; a.chunks = reinterpret_cast<const int4*>(L.chunks);
     a.part_base = L.part_base; a.bias_p = L.bias_p; a.scatter = L.scatter;
     a.x = L.x; a.y = L.y; a.partials = L.partials; a.tickets = L.tickets;
-    a.ldx = L.ldx; a.ldy = L.ldy; a.batch = L.batch; a.act = L.act; a.out_f16 = L.out_f16;
+    a.ldx = L.ldx; a.ldy = L.ldy; a.batch = L.batch; a.act = L.act;
     a.nchunks = L.nchunks; a.nbr = L.nbr;
-    a.out_shift = 0; a.out_group = 1; a.zero_from = L.zero_from; a.zero_to = L.zero_to;
-    if (L.out_frag) { a.out_shift = frag_shift(L.wdtype); a.out_group = L.batch << a.out_shift; a.ldy = 1 << a.out_shift; }
+    a.out_form = (L.out_f16 ? kOutF16 : 0) | (L.out_frag ? kOutFrag | L.out_pad << kOutPadShift : 0);
     a.bh_full = L.bh; a.tile_elems = L.bh * L.bw;
     a.uniform_ct = L.uniform_ct; a.uniform_parts = L.uniform_parts;
     a.T = L.T; a.chunk_tiles = L.chunk_tiles;
@@ -360,6 +359,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         a.xidx = L.xsort;
     }
     if (ml) return launch_mfma_lds_f16(a, kind, bhs, L.bw, nbt, nw, xres, grid, smem, st);
+    if (L.out_frag) return (L.wdtype == PIVOT_F32 ? launch_gemv_f32_chain : launch_gemv_f16_chain)(a, bhs, L.bw, nbt, nw, xres, grid, smem, st);
     if (L.wdtype == PIVOT_F32) return launch_gemv_f32(a, bhs, L.bw, nbt, nw, xres, grid, smem, st);
     return launch_gemv_f16(a, bhs, L.bw, nbt, nw, xres, grid, smem, st);
 }

@@ -4,21 +4,27 @@
 
 namespace pivot {
 
-template <int KIND, int BH, int BW>
-static int launch_t(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
+template <int KIND, int BH, int BW, bool CHAIN>
+static int launch_c(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
     // more than 64 KB of dynamic LDS per workgroup has to be allowed per kernel and device
     static size_t allowed[16] = {};
+    const auto kernel = CHAIN ? fc_mfma_xrow_chain_kernel<KIND, BH, BW> : fc_mfma_xrow_kernel<KIND, BH, BW>;
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     size_t& have = allowed[dev & 15];
     if (smem > 64 * 1024 && smem > have) {
-        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&fc_mfma_xrow_kernel<KIND, BH, BW>),
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         have = smem;
     }
-    hipLaunchKernelGGL((fc_mfma_xrow_kernel<KIND, BH, BW>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+    hipLaunchKernelGGL(kernel, grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
+}
+
+template <int KIND, int BH, int BW>
+static int launch_t(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
+    return (a.out_form & kOutFrag) ? launch_c<KIND, BH, BW, true>(a, grid, smem, st) : launch_c<KIND, BH, BW, false>(a, grid, smem, st);
 }
 
 int launch_mfma_xrow_f16(const FcArgs& a, int kind, int bhs, int bw, dim3 grid, size_t smem, hipStream_t st) {
