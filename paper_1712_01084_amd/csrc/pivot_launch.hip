@@ -32,6 +32,35 @@ static int mfma_lds_rows(int batch) { return batch <= 4 ? 4 : 8; }
 // one group of tiles for the rounding of the split over wavefronts.
 static int frag_wave_tiles(const FcShape& s) { return frag_cols(s.bw, 16 / elem_size(s.wdtype)) * 64 - 8; }
 
+static void frag_split(const FcShape& s, int batch, int* slices, int* blocks);
+
+// fp32, batch 2-8, x in block order: whether the vector kernel is ahead.  It streams the weights once per 4 batch rows
+// (twice at batch 5-8) but cuts a block row down to slices of 4 rows, where the fragment form stops at 16: with fewer
+// work items than compute units and long ones the fragment form leaves the chip idle.  Us for a layer behind one of 64
+// inputs, vector / fragment form, batch 2, 4, 8 (columns per work item; items of 16 rows):
+//   4096 -> 1000, 32x32, 50 % (2048; 64)   7.6 / 10.0    8.5 / 10.4   8.8 / 10.7
+//   3000 -> 1000, 16x64, 50 % (1536; 63)   7.6 / 9.1     8.2 / 9.5    9.8 / 10.0
+//   3000 -> 1000, 32x64, 10 % (320; 64)    6.6 / 7.0     7.3 / 7.3    7.8 / 7.8
+//   4096 -> 1000, 16x64, 25 % (1024; 63)   7.1 / 7.7     7.8 / 8.1    9.1 / 8.4
+//   1000 -> 1000, 64x64, 50 % (512; 64)    7.0 / 6.9     7.9 / 7.3
+//   3000 -> 4096, 32x32, 25 % (768; 256)   8.3 / 8.2     9.2 / 8.7   10.5 / 9.3
+//   9000 -> 8000, 16x32, 10 % (896; 500)  10.8 / 11.2   11.8 / 11.6  16.8 / 12.6
+//   4096 -> 8000, 8x32, 5 % (192; 1000)    7.6 / 8.8     8.1 / 9.1   10.7 / 9.9
+//   9000 -> 1000, 16x16, 25 % (2256; 63)   8.9 / 9.8    10.0 / 10.2  13.1 / 11.9
+//   9000 -> 2000, 16x16, 25 % (2256; 125) 10.3 / 9.9    11.3 / 10.2
+//   4096 -> 2000, 8x8, 50 % (2048; 250)    9.4 / 10.0   10.7 / 10.3
+// Of tiles up to 16 columns wide a step of the fragment form is at most one tile and it is ahead but for the longest.
+static bool block_order_vector(const FcShape& s, int batch) {
+    int slices, blocks;
+    frag_split(s, batch, &slices, &blocks);
+    const long long items = (long long)s.nchunks * slices;
+    const int cols = s.mean_tiles * s.bw;                // per work item
+    if (batch > 4) return s.bw >= 32 && ((cols >= 750 && items <= 32) || (cols >= 1400 && items <= 64));
+    if (s.bw < 32) return (cols >= 1400 && items <= 64) || (s.bh == 8 && batch == 2 && cols >= 1000);
+    if (items < 256) return cols >= (batch == 2 ? 200 : 700);
+    return items >= 500 && (s.bh == 8 || (batch == 2 && cols >= 400));
+}
+
 // Which kernel applies the layer:
 //   kPathVector    batch 1-2 (and whatever the others do not take): FMA / dot2 against x staged in LDS, launch rows of
 //                  at most 4 batch rows
@@ -40,8 +69,9 @@ static int frag_wave_tiles(const FcShape& s) { return frag_cols(s.bw, 16 / elem_
 //   kPathMfmaLds   fp16, batch >= 3: MFMA with the B fragments read from x staged in LDS (4 or 8 batch rows per launch row)
 //   kPathMfmaXrow  fp16, batch 5-16: MFMA with the B fragments gathered from a copy of the rows of x in LDS
 // An x that the layer or cell before produced (kXBlock) arrives in the order the kernel wants, so from batch 2 on the
-// fragment form has nothing to pay for and streams the weights once: always (three fp16 layers of 25088-4096-4096-1000
-// at 10 % kept, batch 32: 23.1 us with the LDS-fed form behind the boundaries, 17.9 with this one).  For an x from the
+// fragment form has nothing to pay for and streams the weights once (three fp16 layers of 25088-4096-4096-1000
+// at 10 % kept, batch 32: 23.1 us with the LDS-fed form behind the boundaries, 17.9 with this one).  (fp32 layers of up to
+// 8 batch rows: block_order_vector.)  For an x from the
 // caller the copy costs about 2.2 us and a second launch, and the other forms repeat work per launch row instead:
 // - fp32, and fp16 tiles no other matrix-core form takes: the vector kernel streams the weights, LDS-bound at 2-5.5
 //   TB/s, once per 4 batch rows.  4096x9216 fp32, 10 % kept (15 MB), vector / fragment form, batch 2: 6.6 / 9.3 us, 4:
@@ -67,8 +97,11 @@ int fc_path(const FcShape& s, int batch) {
     // the matrix-core kernels read A fragments from row-major (BRC) tiles only
     if (layout != PIVOT_BRC || batch < 2) return kPathVector;
     const bool frag = s.x_from != kXNoCopy && (long long)s.xrow_len * batch * elem_size(wdtype) < (1ll << 31) && s.chunk_tiles <= 4 * frag_wave_tiles(s);
-    if (frag && s.x_from == kXBlock) return kPathFrag;
     const double weight_mb = (double)s.nchunks * s.mean_tiles * bh * bw * elem_size(wdtype) * 1e-6;
+    if (frag && s.x_from == kXBlock) {
+        const bool vector = wdtype == PIVOT_F32 && batch <= 8 && block_order_vector(s, batch);
+        return vector ? kPathVector : kPathFrag;
+    }
     if (mfma_kind(wdtype, bh, bw) < 0) {
         const int launch_rows = (batch + 3) / 4;
         return frag && batch >= 3 && (launch_rows > 1 ? (launch_rows - 1) * weight_mb >= 12.0 : weight_mb >= 14.0) ? kPathFrag : kPathVector;
@@ -119,14 +152,18 @@ static void frag_split(const FcShape& s, int batch, int* slices, int* blocks) {
     *blocks = nbt;
 }
 
-// Wavefronts per work item of the batched matrix-core kernel.  Each keeps 8 KB of weights and the x that goes with
+// Wavefronts per work item of the batched matrix-core kernel.  Each keeps up to 8 KB of weights and the x that goes with
 // them in flight, so four fill a compute unit's queue, and several small workgroups per compute unit overlap one's
 // epilogue with another's loads (us per layer call, 8 / 4 / 2 wavefronts: 4096x1024 fp16 8x8 tiles, batch 32
 // 11.4 / 8.0 / 6.9; 4096x9216 fp32 10 % kept, batch 32 13.6 / 12.4 / 14.7; 8192x8192 fp16 25 % kept, batch 64
 // 19.1 / 17.6 / 18.9; 16384x16384 fp16 64x64 tiles 10 % kept, batch 8 22.1 / 19.4 / 17.6): two with fp16 weights
-// from two work items per compute unit on.
+// from two work items per compute unit on, and two where the work item has no more steps than two wavefronts request
+// at once: the other two would only load copies and wait (a layer behind one of 64 inputs, us, 4 / 2 wavefronts: 300 ->
+// 8000 fp32 8x32, 5 % kept, batch 6 11.1 / 8.6; 700 -> 8000 fp32 32x32, 10 %, batch 2 7.6 / 6.6; 700 -> 8000 fp16 32x64,
+// 10 %, batch 4 7.7 / 6.7; 1000 -> 500 fp16 32x32, 5 %, batch 4 5.9 / 5.7).
 static int frag_waves(const FcShape& s, int slices) {
-    int nw = s.wdtype == PIVOT_F16 && (long long)s.nchunks * slices >= 512 ? 2 : 4;
+    const int steps = s.mean_tiles * s.bw * elem_size(s.wdtype) / 64;
+    int nw = steps <= 16 || (s.wdtype == PIVOT_F16 && (long long)s.nchunks * slices >= 512) ? 2 : 4;
     return nw == 2 && s.chunk_tiles > 2 * frag_wave_tiles(s) ? 4 : nw;
 }
 // Batch rows one launch row covers in the kernel's epilogue and in the workspace (grid.y repeats it).

@@ -35,6 +35,17 @@ def test_every_tile_shape_behind_a_boundary(bh, bw, wdtype):
         assert err <= 1e-5 or wdtype == WL.F16
 
 
+@pytest.mark.parametrize("K,M,bh,bw,frac", [(3000, 200, 32, 32, 0.5), (3000, 100, 8, 32, 0.6), (2300, 70, 64, 16, 0.9), (400, 300, 16, 64, 0.5)])
+def test_fp32_behind_a_boundary_few_batch_rows(K, M, bh, bw, frac):
+    # batch 2-8: the vector kernel where work items are few and long, the batched one otherwise, on each side of the
+    # batches where the choice changes; intermediates in rows or in fragment order
+    for i, batch in enumerate((2, 3, 4, 5, 8, 9)):
+        probs = WL.config4(seed=60 + i, batch=batch, dims=(50, K, M), bh=bh, bw=bw, frac=frac, eliminated=bool(i % 2))
+        err, _ = _check_chain(probs)
+        print("%d -> %d %dx%d batch %d: %.3g" % (K, M, bh, bw, batch, err), flush=True)
+        assert err <= 1e-5
+
+
 @pytest.mark.parametrize("wdtype,M,K,bh,bw,batch,frac", [
     (WL.F32, 2048, 2048, 32, 32, 3, 1.0),        # the smallest batch; every wavefront runs several rounds
     (WL.F32, 1000, 1501, 8, 8, 64, 0.8),         # stacked tiles, a ragged last column, all four batch blocks
