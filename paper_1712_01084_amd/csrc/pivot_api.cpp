@@ -524,7 +524,7 @@ namespace {
 // one-launch form][inputs of all steps]
 struct LstmLayout { size_t tickets, scratch, z_off, ctl_off, part_off, xg_off, xg_step, total; };
 
-LstmLayout lstm_layout(const pivot_fc_plan_t* p, int H, int I, int steps, int batch) {
+LstmLayout lstm_layout(const pivot_fc_plan_t* p, int steps, int batch) {
     LstmLayout m{};
     m.tickets = fc_ticket_bytes(p->host);
     m.scratch = align_up(m.tickets + fc_partial_bytes(p->host, batch, kXBlock), 256);
@@ -532,7 +532,7 @@ LstmLayout lstm_layout(const pivot_fc_plan_t* p, int H, int I, int steps, int ba
     m.ctl_off = m.z_off + align_up((size_t)batch * p->host.d.M * 4, 256);
     m.part_off = m.ctl_off + kLstmCtlBytes;
     m.xg_off = m.part_off + lstm_persist_partial_bytes(p->host, batch);
-    m.xg_step = align_up(std::max((size_t)batch * p->host.K_pad * elem_size(p->host.d.wdtype), lstm_units_step_bytes(p->host, H, I, batch)), 256);
+    m.xg_step = align_up(std::max((size_t)batch * p->host.K_pad * elem_size(p->host.d.wdtype), lstm_units_step_bytes(p->host, batch)), 256);
     m.total = m.xg_off + m.xg_step * (size_t)(steps > 0 ? steps : 1);
     return m;
 }
@@ -543,7 +543,8 @@ extern "C" {
 
 size_t pivot_lstm_workspace_bytes(const pivot_fc_plan_t* plan, int H, int I, int steps, int batch) {
     if (!plan || batch < 1 || steps < 0) return 0;
-    return lstm_layout(plan, H, I, steps, batch).total;
+    (void)H; (void)I;                        // the plan's own
+    return lstm_layout(plan, steps, batch).total;
 }
 
 int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev, float* h_dev, float* c_dev,
@@ -555,7 +556,7 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
     if (H < 1 || I < 0 || h.d.M != 4 * H || h.d.K != H + I) { set_error("plan is %dx%d, expected 4H x (H+I) with H=%d I=%d", h.d.M, h.d.K, H, I); return PIVOT_E_SHAPE; }
     if (steps < 0 || batch < 1 || batch > 64) { set_error("bad steps/batch"); return PIVOT_E_SHAPE; }
     if (steps == 0) return PIVOT_OK;
-    LstmLayout m = lstm_layout(plan, H, I, steps, batch);
+    LstmLayout m = lstm_layout(plan, steps, batch);
     if (!ws_dev || ws_bytes < m.total) { set_error("workspace too small: need %zu bytes", m.total); return PIVOT_E_WORKSPACE; }
     char* ws = reinterpret_cast<char*>(ws_dev);
     float* z = reinterpret_cast<float*>(ws + m.z_off);
@@ -564,7 +565,9 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
     // (fewer than 4 steps: loading every tile into registers first does not pay yet)
     const bool always = (h.d.flags & PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS) != 0;
     const bool one_launch = !(h.d.flags & PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) && (steps >= 4 || always);
-    const bool units = one_launch && (always || steps >= lstm_units_min_steps(h)) && lstm_units_supported(h, H, I, batch, plan->device);
+    // (its vector stores take an aligned workspace, which the launch-per-step form asks for too)
+    const bool units = one_launch && (always || steps >= lstm_units_min_steps(h)) && reinterpret_cast<uintptr_t>(ws) % 16 == 0 &&
+                       lstm_units_supported(h, H, I, batch, plan->device);
     if (units || (one_launch && lstm_persist_supported(h, H, batch, plan->device, nullptr, nullptr))) {
         // one launch for the whole sequence
         LstmPersistLaunch P{};
@@ -615,7 +618,7 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
 int pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, void* stream, int* status) {
     if (!plan || !ws_dev || !status) { set_error("plan, ws_dev and status are required"); return PIVOT_E_NULL; }
     if (plan->device < 0) { set_error("host-only plan"); return PIVOT_E_NO_DEVICE; }
-    LstmLayout m = lstm_layout(plan, 0, 0, steps, batch);   // (the control words lie in front of what depends on H and I)
+    LstmLayout m = lstm_layout(plan, steps, batch);
     uint32_t word = 0;
     DeviceGuard g(plan->device);
     API_HIP(hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream)), (void)0);
@@ -626,7 +629,7 @@ int pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, const v
 
 int pivot_lstm_status_word(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, const uint32_t** word_dev) {
     if (!plan || !ws_dev || !word_dev) { set_error("plan, ws_dev and word_dev are required"); return PIVOT_E_NULL; }
-    LstmLayout m = lstm_layout(plan, 0, 0, steps, batch);   // (the control words lie in front of what depends on H and I)
+    LstmLayout m = lstm_layout(plan, steps, batch);
     *word_dev = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(ws_dev) + m.ctl_off + 1024);
     return PIVOT_OK;
 }

@@ -213,7 +213,7 @@ int    launch_lstm_persist(const LstmPersistLaunch& P);
 // The same with one exchange per step (workgroups own whole units): both weight types, every BRC tile shape, batches to 64.
 bool   lstm_units_supported(const HostPlan& hp, int H, int I, int batch, int device);
 int    lstm_units_min_steps(const HostPlan& hp);                   // shortest sequence it pays for
-size_t lstm_units_step_bytes(const HostPlan& hp, int H, int I, int batch);   // of P.xg, per step
+size_t lstm_units_step_bytes(const HostPlan& hp, int batch);       // of P.xg, per step: 0 if the plan cannot take the form
 int    launch_lstm_units(const LstmPersistLaunch& P);              // clears ctl itself; uses neither partials nor xg_step_elems
 
 // A chain of layers in one launch (BRC plans of one weight type with whole block rows per work item, batch 1).

@@ -535,28 +535,29 @@ int units_device(int device) {
     return ok ? cus : 0;
 }
 
+// Whether form f takes the sizes, and how.
+bool units_form(int wdtype, int H, int I, int batch, int f, UnitShape* out) {
+    const int sk = 64 / elem_size(wdtype);
+    const UnitForm& F = kForms[f];
+    UnitShape& s = *out;
+    s.form = f;
+    s.hsteps = (H + sk - 1) / sk; s.xsteps = (I + sk - 1) / sk;
+    if (s.hsteps > F.hs * kUW || s.xsteps > kUX * kUW) return false;
+    const int rows = F.pair ? 8 : 16 * F.nbt;
+    s.teams = (batch + rows - 1) / rows;
+    s.bt = (batch + s.teams - 1) / s.teams;
+    s.teams = (batch + s.bt - 1) / s.bt;
+    s.wgs = (H + 4 * F.rb - 1) / (4 * F.rb);
+    const size_t xw = (size_t)s.xsteps * F.rb * 1024, red = (size_t)kUW * s.bt * F.rb * 16 * 4;
+    s.slots = xw + 2 * red <= kULds ? 2 : 1;
+    s.smem = std::max((size_t)s.hsteps * 1024, xw + s.slots * red);
+    return s.smem <= kULds;
+}
+
 // The first form that takes the sizes with at most `limit` workgroups.
 bool units_shape(const HostPlan& hp, int H, int I, int batch, int limit, UnitShape* out) {
-    const int es = elem_size(hp.d.wdtype), sk = 64 / es;
-    for (int f = 0; f < kNForms; ++f) {
-        const UnitForm& F = kForms[f];
-        UnitShape s;
-        s.form = f;
-        s.hsteps = (H + sk - 1) / sk; s.xsteps = (I + sk - 1) / sk;
-        if (s.hsteps > F.hs * kUW || s.xsteps > kUX * kUW) continue;
-        const int rows = F.pair ? 8 : 16 * F.nbt;
-        s.teams = (batch + rows - 1) / rows;
-        s.bt = (batch + s.teams - 1) / s.teams;
-        s.teams = (batch + s.bt - 1) / s.bt;
-        s.wgs = (H + 4 * F.rb - 1) / (4 * F.rb);
-        if ((long long)s.teams * s.wgs > limit) continue;
-        const size_t xw = (size_t)s.xsteps * F.rb * 1024, red = (size_t)kUW * s.bt * F.rb * 16 * 4;
-        s.slots = xw + 2 * red <= kULds ? 2 : 1;
-        s.smem = std::max((size_t)s.hsteps * 1024, xw + s.slots * red);
-        if (s.smem > kULds) continue;
-        *out = s;
-        return true;
-    }
+    for (int f = 0; f < kNForms; ++f)
+        if (units_form(hp.d.wdtype, H, I, batch, f, out) && (long long)out->teams * out->wgs <= limit) return true;
     return false;
 }
 
@@ -616,11 +617,16 @@ int lstm_units_min_steps(const HostPlan& hp) {
     return (long long)hp.max_row_tiles * hp.d.bw * elem_size(hp.d.wdtype) / 16 <= 128 ? 4 : 8;
 }
 
-size_t lstm_units_step_bytes(const HostPlan& hp, int H, int I, int batch) {
-    // at most eight teams, whose last may have fewer rows; a copy of x_t
-    if (H < 1 || I < 0) return 0;
-    const int es = elem_size(hp.d.wdtype), sk = 64 / es;
-    return ((size_t)((H + sk - 1) / sk) * (batch + 7) + (size_t)((I + sk - 1) / sk) * batch) * 64;
+size_t lstm_units_step_bytes(const HostPlan& hp, int batch) {
+    // the same on every device and for a host-only plan: the largest of the forms that take the sizes
+    const int H = hp.d.M / 4, I = hp.d.K - H;
+    if (hp.d.layout != PIVOT_BRC || hp.T < 1 || (hp.d.flags & PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) || H < 1 || 4 * H != hp.d.M || I < 0) return 0;
+    size_t most = 0;
+    for (int f = 0; f < kNForms; ++f) {
+        UnitShape s;
+        if (units_form(hp.d.wdtype, H, I, batch, f, &s)) most = std::max(most, units_hx_step(s) + units_xc_step(s, batch));
+    }
+    return most;
 }
 
 int launch_lstm_units(const LstmPersistLaunch& P) {

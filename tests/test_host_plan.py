@@ -235,6 +235,30 @@ def test_workspace_holds_what_runs_take():
         B.pivot_fc_plan_destroy(plan)
 
 
+def test_recurrent_workspace_holds_what_runs_take():
+    # per step: the inputs of the launch-per-step form, or the exchange buffers (64 bytes per 16-byte group and batch row,
+    # rows of a team rounded up) and a copy of x_t of the one-launch form, where the plan can take that
+    def per_step(H, I, batch, bh=16, bw=32, dtype=B.PIVOT_F16, layout=B.PIVOT_BRC, flags=0, args=None):
+        M, K = 4 * H, H + I
+        tm = np.zeros((-(-M // bh), -(-K // bw)), np.uint8)
+        tm[:, 0] = 1
+        plan = B.pivot_fc_plan(M, K, bh, bw, dtype, np.zeros((M, K), np.float16 if dtype == B.PIVOT_F16 else np.float32), B.PIVOT_W_PIVOTED,
+                               tm, np.arange(M, dtype=np.int32), np.arange(K, dtype=np.int32), None, layout=layout, device=-1, flags=flags)
+        try:
+            a, b = (B.pivot_lstm_workspace_bytes(plan, *(args or (H, I)), n, batch) for n in (5, 6))
+            return b - a
+        finally:
+            B.pivot_fc_plan_destroy(plan)
+    up = lambda v: -(-v // 256) * 256
+    assert per_step(2048, 1024, 1) == up(3072 * 2)
+    assert per_step(2048, 1024, 8) == up(8 * 3072 * 2)
+    assert per_step(1024, 512, 17) == up(18 * 1024 * 2 + 17 * 512 * 2)          # three teams of 6 rows
+    assert per_step(2048, 1024, 8, args=(0, 0)) == up(8 * 3072 * 2)             # the sizes are the plan's
+    assert per_step(3000, 1024, 1) == up(4032 * 2)                              # too large for the form
+    assert per_step(100, 44, 9, bh=8, bw=8, dtype=B.PIVOT_F32, flags=B.PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) == up(9 * 144 * 4)
+    assert per_step(100, 44, 9, bh=8, bw=8, dtype=B.PIVOT_F32, layout=B.PIVOT_BCR) == up(9 * 144 * 4)
+
+
 def test_host_only_plan_cannot_run_and_workspace_sizes():
     p = WL.gen_fc(32, 32, 8, 8, 0.5, seed=5)
     plan = _host_plan(p, chunk_tiles=1)
