@@ -109,6 +109,10 @@ typedef struct pivot_fc_desc {
 /* ... and this one keeps the one-launch form (where the plan allows it) also for sequences of fewer than
  * 4 steps, which pivot_lstm_run otherwise runs with a launch per step (for measurements and tests). */
 #define PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS 8
+/* ... and with this one the last workgroup of a one-launch run is not launched, as if it found no room: the others
+ * wait for it until their bounded waits give up, a few tenths of a second, every one of them leaves in order and the
+ * status word reads 1 (for tests of what a caller does then). */
+#define PIVOT_PLAN_LSTM_GIVE_UP 32
 
 typedef struct pivot_fc_plan pivot_fc_plan_t;
 typedef struct pivot_mlp_plan pivot_mlp_plan_t;
@@ -355,8 +359,9 @@ int    pivot_mlp_status_word(const pivot_mlp_plan_t* plan, const uint32_t** word
  * barriers: the exchanged data carries the step it belongs to and a consumer
  * re-reads until it sees its step.  The workgroups wait for each other, so
  * nothing else should occupy the device while they run; a wait that does not
- * end within 2^18 polls gives up, every workgroup leaves, h/c are left
- * unwritten and the status word reads 1.  Every other plan (or
+ * end within 2^18 polls gives up, every workgroup leaves and the status word
+ * reads 1.  h and c are then undefined (workgroups that were through have
+ * written theirs) until pivot_lstm_restore puts them back.  Every other plan (or
  * PIVOT_PLAN_LSTM_LAUNCH_PER_STEP), and every sequence of fewer than 4 steps
  * (8 steps for the first form where a block row keeps more than 128 pieces of 16
  * bytes per row), runs one layer launch and one cell launch per step: the
@@ -369,6 +374,18 @@ int    pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, cons
  * read it on their own schedule instead of synchronising; see pivot_mlp_status_word.  The launch-per-step
  * form leaves it at 0. */
 int    pivot_lstm_status_word(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, const uint32_t** word_dev);
+/* Puts h_dev and c_dev back to what they held before the last pivot_lstm_run on
+ * this workspace (same plan, steps and batch) if that run gave up; does nothing
+ * if it completed.  Enqueues one small kernel on `stream` that looks at the
+ * status word itself, so it can follow every run without a synchronisation;
+ * nothing else may have used the workspace in between. */
+int    pivot_lstm_restore(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev,
+                          float* h_dev, float* c_dev, void* stream);
+/* Which form pivot_lstm_run takes for these steps and this batch, for a 16-byte
+ * aligned workspace: "lstm_units_kernel<type, 16-row blocks, k-steps, batch
+ * blocks, paired> teams n sums m", "lstm_persist_kernel<tile slots>" or "launch
+ * per step".  buf receives at most buf_len bytes including the terminating 0. */
+int    pivot_lstm_kernel_name(const pivot_fc_plan_t* plan, int steps, int batch, char* buf, size_t buf_len);
 int    pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev,
                       float* h_dev, float* c_dev, float* z_dbg, int steps, int batch,
                       void* ws_dev, size_t ws_bytes, void* stream);

@@ -18,6 +18,7 @@ PIVOT_PLAN_GATHER_FROM_GLOBAL = 1
 PIVOT_PLAN_LSTM_LAUNCH_PER_STEP = 2
 PIVOT_PLAN_GATHER_FROM_LDS_COPY = 4
 PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS = 8
+PIVOT_PLAN_LSTM_GIVE_UP = 32
 PIVOT_ACT_NONE, PIVOT_ACT_RELU = 0, 1
 PIVOT_W_NATURAL, PIVOT_W_PIVOTED = 0, 1
 PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER = 1
@@ -33,7 +34,7 @@ EXPORTS = [
     "pivot_fc_workspace_bytes", "pivot_workspace_init", "pivot_fc_run", "pivot_fc_run_static", "pivot_fc_kernel_name",
     "pivot_mlp_plan", "pivot_mlp_plan_host_view", "pivot_mlp_plan_destroy",
     "pivot_mlp_workspace_bytes", "pivot_mlp_run", "pivot_mlp_status", "pivot_mlp_status_word",
-    "pivot_lstm_workspace_bytes", "pivot_lstm_run", "pivot_lstm_status", "pivot_lstm_status_word",
+    "pivot_lstm_workspace_bytes", "pivot_lstm_run", "pivot_lstm_status", "pivot_lstm_status_word", "pivot_lstm_restore", "pivot_lstm_kernel_name",
     "pivot_dense_run", "pivot_csr_run", "pivot_null_run", "pivot_stream_read_run", "pivot_exchange_probe_run", "pivot_feedback_search",
 ]
 
@@ -116,6 +117,8 @@ def lib():
     L.pivot_lstm_workspace_bytes.restype = sz
     L.pivot_lstm_run.argtypes = [vp, i32, i32, vp, vp, vp, vp, i32, i32, vp, sz, vp]
     L.pivot_lstm_status.argtypes = [vp, i32, i32, vp, vp, C.POINTER(C.c_int)]
+    L.pivot_lstm_restore.argtypes = [vp, i32, i32, vp, vp, vp, vp]
+    L.pivot_lstm_kernel_name.argtypes = [vp, i32, i32, C.c_char_p, sz]
     L.pivot_dense_run.argtypes = [vp, i32, i32, i32, vp, i64, vp, vp, i64, i32, i32, vp]
     L.pivot_null_run.argtypes = [vp]
     L.pivot_stream_read_run.argtypes = [vp, sz, vp, vp]
@@ -273,6 +276,18 @@ def pivot_lstm_status_word(plan, steps, batch, ws_ptr):
     out = C.c_void_p()
     _check(lib().pivot_lstm_status_word(plan, steps, batch, ws_ptr, C.byref(out)))
     return out.value or 0
+
+
+def pivot_lstm_restore(plan, steps, batch, ws_ptr, h_ptr, c_ptr, stream=None):
+    """Puts h and c back if the last pivot_lstm_run on this workspace gave up."""
+    _check(lib().pivot_lstm_restore(plan, steps, batch, ws_ptr, h_ptr, c_ptr, stream))
+
+
+def pivot_lstm_kernel_name(plan, steps, batch):
+    """The form pivot_lstm_run takes for this plan, number of steps and batch."""
+    buf = C.create_string_buffer(256)
+    _check(lib().pivot_lstm_kernel_name(plan, steps, batch, buf, 256))
+    return buf.value.decode()
 
 
 def pivot_lstm_workspace_bytes(plan, H, I, steps, batch):

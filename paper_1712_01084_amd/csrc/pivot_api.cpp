@@ -537,6 +537,17 @@ LstmLayout lstm_layout(const pivot_fc_plan_t* p, int steps, int batch) {
     return m;
 }
 
+// The form a run takes.  `aligned`: the workspace is 16-byte aligned, which the vector stores of the units form need and
+// the launch-per-step form asks for.  (Fewer than 4 steps: placing every tile first does not pay yet.)
+enum { kLstmPerStep, kLstmPersist, kLstmUnits };
+int lstm_form(const pivot_fc_plan_t* plan, int H, int I, int steps, int batch, bool aligned) {
+    const HostPlan& h = plan->host;
+    const bool always = (h.d.flags & PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS) != 0;
+    if ((h.d.flags & PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) || (steps < 4 && !always)) return kLstmPerStep;
+    if (aligned && (always || steps >= lstm_units_min_steps(h)) && lstm_units_supported(h, H, I, batch, plan->device)) return kLstmUnits;
+    return lstm_persist_supported(h, H, batch, plan->device, nullptr, nullptr) ? kLstmPersist : kLstmPerStep;
+}
+
 }  // namespace
 
 extern "C" {
@@ -562,13 +573,8 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
     float* z = reinterpret_cast<float*>(ws + m.z_off);
     char* xg = ws + m.xg_off;
     int rc;
-    // (fewer than 4 steps: loading every tile into registers first does not pay yet)
-    const bool always = (h.d.flags & PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS) != 0;
-    const bool one_launch = !(h.d.flags & PIVOT_PLAN_LSTM_LAUNCH_PER_STEP) && (steps >= 4 || always);
-    // (its vector stores take an aligned workspace, which the launch-per-step form asks for too)
-    const bool units = one_launch && (always || steps >= lstm_units_min_steps(h)) && reinterpret_cast<uintptr_t>(ws) % 16 == 0 &&
-                       lstm_units_supported(h, H, I, batch, plan->device);
-    if (units || (one_launch && lstm_persist_supported(h, H, batch, plan->device, nullptr, nullptr))) {
+    const int form = lstm_form(plan, H, I, steps, batch, reinterpret_cast<uintptr_t>(ws) % 16 == 0);
+    if (form != kLstmPerStep) {
         // one launch for the whole sequence
         LstmPersistLaunch P{};
         P.hp = &h;
@@ -578,8 +584,10 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
         P.partials = ws + m.part_off;
         P.ctl = reinterpret_cast<uint32_t*>(ws + m.ctl_off);
         P.h = h_dev; P.c = c_dev; P.z_dbg = z_dbg;
+        P.saved = z;                     // (the one-launch forms use no gate pre-activations)
+        P.give_up = (h.d.flags & PIVOT_PLAN_LSTM_GIVE_UP) != 0;
         P.H = H; P.I = I; P.batch = batch; P.steps = steps; P.device = plan->device; P.stream = stream;
-        if (units) return launch_lstm_units(P);
+        if (form == kLstmUnits) return launch_lstm_units(P);
         // control words + the partial buffers this sequence will use
         if ((rc = launch_fill_zero(ws + m.ctl_off, (m.part_off - m.ctl_off) + lstm_persist_used_partial_bytes(h, batch, steps), stream)) != PIVOT_OK) return rc;
         return launch_lstm_persist(P);
@@ -624,6 +632,35 @@ int pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, const v
     API_HIP(hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream)), (void)0);
     API_HIP(hipMemcpy(&word, reinterpret_cast<const char*>(ws_dev) + m.ctl_off + 1024, 4, hipMemcpyDeviceToHost), (void)0);
     *status = (int)word;
+    return PIVOT_OK;
+}
+
+int pivot_lstm_restore(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, float* h_dev, float* c_dev, void* stream) {
+    if (!plan || !ws_dev || !h_dev || !c_dev) { set_error("plan, ws_dev, h_dev and c_dev are required"); return PIVOT_E_NULL; }
+    if (plan->device < 0) { set_error("host-only plan (device = -1) cannot run"); return PIVOT_E_NO_DEVICE; }
+    if (plan->host.d.M % 4 != 0 || steps < 0 || batch < 1 || batch > 64) { set_error("bad steps/batch, or no recurrent plan"); return PIVOT_E_SHAPE; }
+    if (steps == 0) return PIVOT_OK;
+    const LstmLayout m = lstm_layout(plan, steps, batch);
+    const char* ws = reinterpret_cast<const char*>(ws_dev);
+    return launch_lstm_restore(reinterpret_cast<const uint32_t*>(ws + m.ctl_off), reinterpret_cast<const float*>(ws + m.z_off), h_dev, c_dev,
+                               batch * (plan->host.d.M / 4), stream);
+}
+
+int pivot_lstm_kernel_name(const pivot_fc_plan_t* plan, int steps, int batch, char* buf, size_t buf_len) {
+    if (!plan || !buf || buf_len == 0) { set_error("plan and buf are required"); return PIVOT_E_NULL; }
+    buf[0] = 0;
+    if (plan->device < 0) { set_error("host-only plan (device = -1) cannot run"); return PIVOT_E_NO_DEVICE; }
+    const HostPlan& h = plan->host;
+    const int H = h.d.M / 4, I = h.d.K - H;
+    if (4 * H != h.d.M || H < 1 || I < 0 || steps < 1 || batch < 1 || batch > 64) { set_error("bad steps/batch, or no recurrent plan"); return PIVOT_E_SHAPE; }
+    std::string name = "launch per step";
+    int L = 0;
+    switch (lstm_form(plan, H, I, steps, batch, true)) {
+        case kLstmUnits: name = lstm_units_name(h, H, I, batch, plan->device); break;
+        case kLstmPersist: lstm_persist_supported(h, H, batch, plan->device, nullptr, &L); name = L <= 8 ? "lstm_persist_kernel<8>" : "lstm_persist_kernel<16>"; break;
+        default: break;
+    }
+    snprintf(buf, buf_len, "%s", name.c_str());
     return PIVOT_OK;
 }
 

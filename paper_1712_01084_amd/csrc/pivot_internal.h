@@ -202,6 +202,8 @@ struct LstmPersistLaunch {
     void* partials;                    // lstm_persist_partial_bytes, zeroed
     uint32_t* ctl;                     // kLstmCtlBytes, zeroed: progress word per workgroup, status word at [256]
     float* h; float* c; float* z_dbg;
+    float* saved;                      // [2][batch][H]: h_0 and c_0 (written here, for launch_lstm_restore)
+    int give_up;                       // PIVOT_PLAN_LSTM_GIVE_UP: the last workgroup is not launched
     int H, I, batch, steps, device;
     void* stream;
 };
@@ -210,8 +212,11 @@ size_t lstm_persist_partial_bytes(const HostPlan& hp, int batch);
 size_t lstm_persist_used_partial_bytes(const HostPlan& hp, int batch, int steps);
 constexpr size_t kLstmCtlBytes = 2048;
 int    launch_lstm_persist(const LstmPersistLaunch& P);
+// h and c (n elements) back to what `saved` holds if the status word ctl[256] is raised.
+int    launch_lstm_restore(const uint32_t* ctl, const float* saved, float* h, float* c, int n, void* stream);
 // The same with one exchange per step (workgroups own whole units): both weight types, every BRC tile shape, batches to 64.
 bool   lstm_units_supported(const HostPlan& hp, int H, int I, int batch, int device);
+std::string lstm_units_name(const HostPlan& hp, int H, int I, int batch, int device);
 int    lstm_units_min_steps(const HostPlan& hp);                   // shortest sequence it pays for
 size_t lstm_units_step_bytes(const HostPlan& hp, int batch);       // of P.xg, per step: 0 if the plan cannot take the form
 int    launch_lstm_units(const LstmPersistLaunch& P);              // clears ctl itself; uses neither partials nor xg_step_elems

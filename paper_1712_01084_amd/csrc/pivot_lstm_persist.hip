@@ -398,11 +398,12 @@ __global__ void __launch_bounds__(kNT) lstm_persist_kernel(PersistArgs a) {
 }  // namespace
 
 // Block-order inputs of all steps for the one-launch form: x_t and h_0 in place, zero in the padding
-// columns, the "not yet" pattern wherever a later h_t will land.
-__global__ void lstm_prepare_kernel(const _Float16* xs, const float* h0, const int32_t* pcol_pad, _Float16* xg,
+// columns, the "not yet" pattern wherever a later h_t will land.  Saves h_0 and c_0.
+__global__ void lstm_prepare_kernel(const _Float16* xs, const float* h0, const float* c0, float* saved, const int32_t* pcol_pad, _Float16* xg,
                                     size_t xg_step, int H, int I, int K_pad, int batch, size_t total) {
     size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    const size_t stride = (size_t)gridDim.x * blockDim.x, n = (size_t)batch * H;
+    for (size_t i = idx; i < n; i += stride) { saved[i] = h0[i]; saved[n + i] = c0[i]; }
     for (; idx < total; idx += stride) {
         const int c = (int)(idx % K_pad);
         const size_t tb = idx / K_pad;                   // step * batch + b
@@ -490,7 +491,7 @@ int launch_lstm_persist(const LstmPersistLaunch& P) {
         const size_t total = (size_t)P.steps * P.batch * P.hp->K_pad;
         const int blocks = (int)((total + 255) / 256 > 8192 ? 8192 : (total + 255) / 256);
         hipLaunchKernelGGL(lstm_prepare_kernel, dim3(blocks), dim3(256), 0, st, reinterpret_cast<const _Float16*>(P.xs),
-                           P.h, P.pcol_pad, reinterpret_cast<_Float16*>(P.xg), P.xg_step_elems, P.H, P.I, P.hp->K_pad,
+                           P.h, P.c, P.saved, P.pcol_pad, reinterpret_cast<_Float16*>(P.xg), P.xg_step_elems, P.H, P.I, P.hp->K_pad,
                            P.batch, total);
         HIP_TRY(hipGetLastError());
     }
@@ -502,8 +503,9 @@ int launch_lstm_persist(const LstmPersistLaunch& P) {
     a.T = P.hp->T; a.nbr = P.hp->nbr; a.H = P.H; a.I = P.I; a.K_pad = P.hp->K_pad; a.batch = P.batch; a.steps = P.steps; a.L = L;
     const size_t smem = (size_t)4 * L * kSlot * 4;
     // (that all workgroups fit on the device at once was checked by lstm_persist_supported)
-    if (L <= 8) hipLaunchKernelGGL(lstm_persist_kernel<8>, dim3(G), dim3(kNT), smem, st, a);
-    else        hipLaunchKernelGGL(lstm_persist_kernel<16>, dim3(G), dim3(kNT), smem, st, a);
+    const int grid = P.give_up && G > 1 ? G - 1 : G;
+    if (L <= 8) hipLaunchKernelGGL(lstm_persist_kernel<8>, dim3(grid), dim3(kNT), smem, st, a);
+    else        hipLaunchKernelGGL(lstm_persist_kernel<16>, dim3(grid), dim3(kNT), smem, st, a);
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

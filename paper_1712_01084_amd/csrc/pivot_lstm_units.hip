@@ -35,6 +35,7 @@
 // at most half a compute unit and every wait is bounded like those of the kernel
 // that exchanges gate sums.
 #include <algorithm>
+#include <cstdio>
 
 #include "pivot_fc_kernels.h"
 #include "pivot_frag.h"
@@ -448,16 +449,19 @@ __global__ void __launch_bounds__(kUT, 2) lstm_units_kernel(UnitArgs a) {
     }
 }
 
-// Exchange buffers: h_0 in step 0, the mark in every later step, zero past the last unit; clears the control words.
-// Where the caller's rows are not whole aligned 16-byte groups, also a zero-padded copy of them.
+// Exchange buffers: h_0 in step 0, the mark in every later step, zero past the last unit; clears the control words and
+// saves h_0 and c_0.  Where the caller's rows are not whole aligned 16-byte groups, also a zero-padded copy of them.
 template <typename WT>
-__global__ void __launch_bounds__(256) lstm_units_prepare_kernel(const WT* __restrict__ xs, const float* __restrict__ h0, char* __restrict__ hx, char* __restrict__ xc,
+__global__ void __launch_bounds__(256) lstm_units_prepare_kernel(const WT* __restrict__ xs, const float* __restrict__ h0, const float* __restrict__ c0, float* __restrict__ saved, char* __restrict__ hx, char* __restrict__ xc,
                                                                  uint32_t* __restrict__ ctl, int H, int I, int batch, int bt, int hgroups, int xcgroups,
                                                                  int teams, int steps) {
     constexpr int VEC = Elem<WT>::VEC;
     if (blockIdx.x == 0 && blockIdx.y == 0)
         for (int k = threadIdx.x; k < (int)kLstmCtlBytes / 4; k += 256) ctl[k] = 0u;
     const int first = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+    // spread over all workgroups: by those of the first step alone it cost up to 2 us
+    const int n = batch * H, all = stride * gridDim.y;
+    for (int i = blockIdx.y * stride + first; i < n; i += all) { saved[i] = h0[i]; saved[n + i] = c0[i]; }
     const int per_team = hgroups * bt, per_step = per_team * teams, per_x = xcgroups * batch;
     for (int t = blockIdx.y; t < steps; t += gridDim.y) {
         for (int i = first; i < per_step; i += stride) {
@@ -587,7 +591,7 @@ int launch_units_t(const LstmPersistLaunch& P, const UnitShape& s) {
     const int hgroups = s.hsteps * 4, xcgroups = direct ? 0 : s.xsteps * 4;
     const int per_step = std::max(hgroups * s.bt * s.teams, xcgroups * P.batch);
     const dim3 blocks((per_step + 255) / 256, std::min(P.steps, 1024));
-    hipLaunchKernelGGL(lstm_units_prepare_kernel<WT>, blocks, dim3(256), 0, st, reinterpret_cast<const WT*>(P.xs), P.h, hx, xc, P.ctl,
+    hipLaunchKernelGGL(lstm_units_prepare_kernel<WT>, blocks, dim3(256), 0, st, reinterpret_cast<const WT*>(P.xs), P.h, P.c, P.saved, hx, xc, P.ctl,
                        P.H, P.I, P.batch, s.bt, hgroups, xcgroups, s.teams, P.steps);
     HIP_TRY(hipGetLastError());
     UnitArgs a;
@@ -597,7 +601,8 @@ int launch_units_t(const LstmPersistLaunch& P, const UnitShape& s) {
     a.step_bytes = units_hx_step(s); a.team_bytes = a.step_bytes / s.teams;
     a.H = P.H; a.I = P.I; a.batch = P.batch; a.steps = P.steps; a.bt = s.bt; a.wgs = s.wgs;
     a.bh = hp.d.bh; a.bw = hp.d.bw; a.hsteps = s.hsteps; a.xsteps = s.xsteps; a.slots = s.slots;
-    hipLaunchKernelGGL(units_kernel<WT>(s.form), dim3(s.teams * s.wgs), dim3(kUT), s.smem, st, a);
+    const int grid = s.teams * s.wgs;
+    hipLaunchKernelGGL(units_kernel<WT>(s.form), dim3(P.give_up && grid > 1 ? grid - 1 : grid), dim3(kUT), s.smem, st, a);
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }
@@ -607,6 +612,16 @@ int launch_units_t(const LstmPersistLaunch& P, const UnitShape& s) {
 bool lstm_units_supported(const HostPlan& hp, int H, int I, int batch, int device) {
     UnitShape s;
     return pick(hp, H, I, batch, device, &s);
+}
+
+std::string lstm_units_name(const HostPlan& hp, int H, int I, int batch, int device) {
+    UnitShape s;
+    if (!pick(hp, H, I, batch, device, &s)) return "";
+    const UnitForm& F = kForms[s.form];
+    char buf[128];
+    snprintf(buf, sizeof buf, "lstm_units_kernel<%s, %d, %d, %d, %s> teams %d sums %d", hp.d.wdtype == PIVOT_F32 ? "float" : "_Float16", F.rb, F.hs, F.nbt,
+             F.pair ? "true" : "false", s.teams, s.slots);
+    return buf;
 }
 
 // Before the first step a wavefront goes through the tiles of its rows, 256 pieces of 16 bytes at a time, twice.  Us for

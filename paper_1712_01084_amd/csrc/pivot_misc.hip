@@ -507,6 +507,20 @@ __global__ void __launch_bounds__(256) lstm_inputs_kernel(const int32_t* __restr
     reinterpret_cast<V*>(xg)[(size_t)t * step_vecs + i] = v;
 }
 
+__global__ void __launch_bounds__(256) lstm_restore_kernel(const uint32_t* __restrict__ ctl, const float* __restrict__ saved, float* __restrict__ h,
+                                                           float* __restrict__ c, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n || ctl[256] == 0u) return;
+    h[i] = saved[i];
+    c[i] = saved[n + i];
+}
+
+int launch_lstm_restore(const uint32_t* ctl, const float* saved, float* h, float* c, int n, void* stream) {
+    hipLaunchKernelGGL(lstm_restore_kernel, dim3((n + 255) / 256), dim3(256), 0, reinterpret_cast<hipStream_t>(stream), ctl, saved, h, c, n);
+    HIP_TRY(hipGetLastError());
+    return PIVOT_OK;
+}
+
 int launch_lstm_inputs(const LstmInputsLaunch& L) {
     hipStream_t st = reinterpret_cast<hipStream_t>(L.stream);
     const int es = elem_size(L.wdtype), ngroups = L.K_pad * es / 16;

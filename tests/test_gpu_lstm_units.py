@@ -4,6 +4,7 @@ the CPU oracle, and infinities and NaNs against the launch-per-step form.
 Needs a GPU."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import pivot_oracle as O
 from paper_1712_01084_amd import binding as B
@@ -50,6 +51,61 @@ def test_sequence_against_the_oracle(H, I, batch, bh, bw, dtype):
             assert np.isfinite(z).all()
         h2, c2, z2 = _lstm_gpu(lp, plan, lp.xs, lp.h0, lp.c0)
         assert np.array_equal(h, h2) and np.array_equal(c, c2) and np.array_equal(z, z2)
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
+# (one team, eight teams, two batch blocks per team; the form that exchanges gate sums, its last workgroup with 11 tiles)
+@pytest.mark.parametrize("H,I,batch,dtype,frac", [(300, 96, 3, "f32", 0.3), (200, 96, 64, "f16", 0.3), (1000, 500, 32, "f16", 0.3),
+                                                  (512, 1100, 8, "f16", 0.313)])
+def test_a_run_that_gives_up_can_be_taken_back(H, I, batch, dtype, frac):
+    # the last workgroup is missing: those of its team give up after 2^18 polls (every kernel exits by itself), the other
+    # teams are through and have written their h and c by then
+    lp = _problem(H, I, 6, batch, 16, 32, WL.F16 if dtype == "f16" else WL.F32, frac, seed=6)
+    st = torch.cuda.current_stream().cuda_stream
+    xs, h, c = torch.from_numpy(lp.xs).cuda(), torch.from_numpy(lp.h0).cuda(), torch.from_numpy(lp.c0).cuda()
+
+    def run(flags, h, c):
+        plan = G.dev_plan(lp.fc, flags=flags)
+        try:
+            ws = G.workspace(B.pivot_lstm_workspace_bytes(plan, H, I, 6, batch))
+            B.pivot_lstm_run(plan, H, I, xs.data_ptr(), h.data_ptr(), c.data_ptr(), None, 6, batch, ws.data_ptr(), ws.numel(), st)
+            B.pivot_lstm_restore(plan, 6, batch, ws.data_ptr(), h.data_ptr(), c.data_ptr(), st)
+            return B.pivot_lstm_status(plan, 6, batch, ws.data_ptr(), st)
+        finally:
+            B.pivot_fc_plan_destroy(plan)
+    for _ in range(2):
+        assert run(B.PIVOT_PLAN_LSTM_GIVE_UP, h, c) == 1
+        assert np.array_equal(h.cpu().numpy(), lp.h0) and np.array_equal(c.cpu().numpy(), lp.c0)     # put back
+    h2, c2 = h.clone(), c.clone()
+    assert run(0, h, c) == 0 and run(B.PIVOT_PLAN_LSTM_LAUNCH_PER_STEP, h2, c2) == 0        # the caller can run it again
+    assert (h - h2).abs().max() < 2e-3 and (c - c2).abs().max() < 4e-3
+
+
+def test_four_streams_at_once():
+    # half the compute units' worth of workgroups each, half a compute unit per workgroup: four launches, as many as a
+    # process has hardware queues, are resident together and wait for none of the others
+    lp = _problem(1024, 96, 40, 32, 16, 32, WL.F16, 0.1, seed=9)
+    plan = G.dev_plan(lp.fc)
+    try:
+        xs = torch.from_numpy(lp.xs).cuda()
+        nws = B.pivot_lstm_workspace_bytes(plan, 1024, 96, 40, 32)
+        jobs = [(torch.cuda.Stream(), torch.from_numpy(lp.h0).cuda(), torch.from_numpy(lp.c0).cuda(), G.workspace(nws)) for _ in range(5)]
+        torch.cuda.synchronize()
+
+        def enqueue(job):
+            s, h, c, ws = job
+            B.pivot_lstm_run(plan, 1024, 96, xs.data_ptr(), h.data_ptr(), c.data_ptr(), None, 40, 32, ws.data_ptr(), ws.numel(), s.cuda_stream)
+        for _ in range(4):                               # the state goes on from run to run
+            for job in jobs[:4]:
+                enqueue(job)
+        torch.cuda.synchronize()
+        for _ in range(4):
+            enqueue(jobs[4])                             # alone
+            torch.cuda.synchronize()
+        for s, h, c, ws in jobs:
+            assert B.pivot_lstm_status(plan, 40, 32, ws.data_ptr(), s.cuda_stream) == 0
+            assert torch.equal(h, jobs[4][1]) and torch.equal(c, jobs[4][2])
     finally:
         B.pivot_fc_plan_destroy(plan)
 
