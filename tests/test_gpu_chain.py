@@ -353,8 +353,8 @@ def test_lstm_small(batch, per_step):
 
 
 @pytest.mark.parametrize("H,I,batch,frac", [(96, 40, 3, 0.3), (256, 128, 16, 0.2), (80, 8, 5, 1.0),
-                                             (1024, 512, 8, 0.8),     # 10 tiles per wavefront: the 16-slot kernel
-                                             (512, 256, 4, 0.5)])     # fewer workgroups than compute units
+                                             (1024, 512, 8, 0.8),     # long block rows
+                                             (512, 256, 4, 0.5)])
 def test_lstm_one_launch_ragged_shapes(H, I, batch, frac):
     # K = H+I not a multiple of the tile width (padding columns), empty and split block rows, every tile kept
     lp = WL.config5(seed=5, batch=batch, H=H, I=I, steps=13, frac=frac)
@@ -403,8 +403,7 @@ def test_lstm_one_launch_agrees_with_launch_per_step():
 @pytest.mark.parametrize("per_step", [False, True])
 def test_lstm_config5_full(per_step, seed):
     # single steps from the oracle's state, three 12-step windows inside one run (the one-launch form's step-to-step
-    # exchange: marks, the rotation through eight partial buffers, the progress check from step 8 on), and the
-    # 256-step free run
+    # exchange), and the 256-step free run
     lp = WL.config5(seed=seed)
     dh, dc = _check_lstm_steps(lp, record=(0, 1, 17, 255), tol=2e-3, per_step=per_step,
                                windows=(0, 100, 240) if seed == 0 or not per_step else (100,))

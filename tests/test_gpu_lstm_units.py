@@ -26,17 +26,31 @@ def _problem(H, I, steps, batch, bh, bw, wdtype, frac, seed=11):
     return WL.LSTMProblem(fc, H, I, xs, h0, c0)
 
 
-# (H, I, batch, bh, bw, dtype): pairs of k-steps (up to 8 rows, short and long K), single teams, several teams, two
-# batch blocks per team; H, I no multiples of anything (the copy of x), H and I at the edges of a k-step
-CASES = [(64, 32, 1, 16, 32, "f16"), (65, 33, 8, 8, 8, "f16"), (31, 1, 3, 16, 16, "f16"), (512, 256, 8, 64, 64, "f16"),
-         (1100, 40, 2, 16, 32, "f16"), (2048, 8, 7, 16, 32, "f16"), (513, 33, 12, 32, 16, "f16"), (400, 24, 40, 16, 64, "f16"),
-         (1000, 500, 32, 16, 32, "f16"), (200, 96, 64, 16, 32, "f16"),
-         (70, 13, 5, 8, 16, "f32"), (256, 128, 8, 16, 32, "f32"), (700, 4, 3, 32, 8, "f32"), (400, 24, 12, 16, 32, "f32"),
-         (250, 60, 20, 64, 64, "f32"), (300, 300, 48, 8, 8, "f32")]
+# (H, I, batch, bh, bw, dtype) and the form it takes on 256 compute units: every instantiation of both types; one or two
+# buffers of sums; up to eight teams, the last one short; H and I no multiples of anything (the copy of x), at the edges
+# of a k-step and the largest of a form
+CASES = [((64, 32, 1, 16, 32, "f16"), "2, 8, 1, true> teams 1 sums 2"), ((65, 33, 8, 8, 8, "f16"), "2, 8, 1, true> teams 1 sums 2"),
+         ((31, 1, 3, 16, 16, "f16"), "2, 8, 1, true> teams 1 sums 2"), ((512, 256, 8, 64, 64, "f16"), "2, 8, 1, true> teams 1 sums 2"),
+         ((1100, 40, 2, 16, 32, "f16"), "2, 16, 1, true> teams 1 sums 2"), ((2048, 8, 7, 16, 32, "f16"), "2, 16, 1, true> teams 1 sums 2"),
+         ((513, 33, 12, 32, 16, "f16"), "2, 8, 1, false> teams 1 sums 2"), ((1024, 1024, 16, 16, 64, "f16"), "2, 8, 1, false> teams 1 sums 1"),
+         ((400, 24, 40, 16, 64, "f16"), "4, 8, 1, false> teams 3 sums 2"), ((1000, 500, 32, 16, 32, "f16"), "2, 8, 2, false> teams 1 sums 2"),
+         ((900, 1000, 30, 8, 16, "f16"), "2, 8, 2, false> teams 1 sums 1"), ((200, 96, 64, 16, 32, "f16"), "2, 8, 1, false> teams 4 sums 2"),
+         ((70, 13, 5, 8, 16, "f32"), "2, 8, 1, true> teams 1 sums 2"), ((256, 128, 8, 16, 32, "f32"), "2, 8, 1, true> teams 1 sums 2"),
+         ((700, 4, 3, 32, 8, "f32"), "2, 16, 1, true> teams 1 sums 2"), ((1000, 500, 8, 16, 32, "f32"), "2, 16, 1, true> teams 1 sums 2"),
+         ((400, 24, 12, 16, 32, "f32"), "2, 8, 1, true> teams 2 sums 2"), ((250, 60, 20, 64, 64, "f32"), "2, 8, 1, true> teams 3 sums 2"),
+         ((300, 300, 48, 8, 8, "f32"), "2, 8, 1, false> teams 3 sums 2"), ((512, 200, 64, 16, 32, "f32"), "4, 8, 1, false> teams 4 sums 1"),
+         ((512, 300, 64, 32, 32, "f32"), "2, 8, 2, false> teams 2 sums 2"), ((512, 400, 64, 16, 16, "f32"), "2, 8, 2, false> teams 2 sums 1")]
 
 
-@pytest.mark.parametrize("H,I,batch,bh,bw,dtype", CASES)
-def test_sequence_against_the_oracle(H, I, batch, bh, bw, dtype):
+def _check_form(plan, steps, batch, form):
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert B.pivot_lstm_kernel_name(plan, steps, batch).endswith(form)
+    assert B.pivot_lstm_kernel_name(plan, steps, batch).startswith("lstm_units_kernel<")
+
+
+@pytest.mark.parametrize("sizes,form", CASES)
+def test_sequence_against_the_oracle(sizes, form):
+    H, I, batch, bh, bw, dtype = sizes
     # fp32 sums of fp16 or fp32 products in another order, sigmoids of fp32: the free-run gate of the other forms
     wdtype = WL.F16 if dtype == "f16" else WL.F32
     lp = _problem(H, I, 5, batch, bh, bw, wdtype, 0.3)
@@ -45,10 +59,10 @@ def test_sequence_against_the_oracle(H, I, batch, bh, bw, dtype):
     h_ref, c_ref, _ = O.oracle_lstm(Wd, p.bias, lp.xs, lp.h0, lp.c0, H, state_dtype=np.float16 if dtype == "f16" else np.float32)
     plan = G.dev_plan(p, flags=B.PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS)
     try:
-        for n in (5, 5):
-            h, c, z = _lstm_gpu(lp, plan, lp.xs[:n], lp.h0, lp.c0)
-            assert np.abs(h - h_ref).max() < FREE_RUN_GATE and np.abs(c - c_ref).max() < FREE_RUN_GATE
-            assert np.isfinite(z).all()
+        _check_form(plan, 5, batch, form)
+        h, c, z = _lstm_gpu(lp, plan, lp.xs, lp.h0, lp.c0)
+        assert np.abs(h - h_ref).max() < FREE_RUN_GATE and np.abs(c - c_ref).max() < FREE_RUN_GATE
+        assert np.isfinite(z).all()
         h2, c2, z2 = _lstm_gpu(lp, plan, lp.xs, lp.h0, lp.c0)
         assert np.array_equal(h, h2) and np.array_equal(c, c2) and np.array_equal(z, z2)
     finally:
@@ -110,21 +124,27 @@ def test_four_streams_at_once():
         B.pivot_fc_plan_destroy(plan)
 
 
-@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("sizes,form", [((96, 40, 3, "f16"), "2, 8, 1, true> teams 1 sums 2"), ((96, 40, 3, "f32"), "2, 8, 1, true> teams 1 sums 2"),
+                                        ((400, 24, 40, "f16"), "4, 8, 1, false> teams 3 sums 2"), ((512, 200, 64, "f32"), "4, 8, 1, false> teams 4 sums 1"),
+                                        ((900, 1000, 30, "f16"), "2, 8, 2, false> teams 1 sums 1"), ((512, 300, 64, "f32"), "2, 8, 2, false> teams 2 sums 2"),
+                                        ((1024, 1000, 16, "f16"), "2, 8, 1, false> teams 1 sums 1")])
 @pytest.mark.parametrize("what", ["inf x", "nan x", "inf h", "nan h"])
-def test_infinities_and_nans_reach_the_rows_of_kept_tiles_only(dtype, what):
+def test_infinities_and_nans_reach_the_rows_of_kept_tiles_only(sizes, form, what):
     # columns outside the kept tiles are zeros in this form's dense rows; a product with an infinity must not count
+    H, I, batch, dtype = sizes
     wdtype = WL.F16 if dtype == "f16" else WL.F32
-    lp = _problem(96, 40, 4, 3, 16, 32, wdtype, 0.25, seed=4)
+    lp = _problem(H, I, 4, batch, 16, 32, wdtype, 0.25, seed=4)
     bad = np.inf if what.startswith("inf") else np.nan
     if what.endswith("x"):
-        lp.xs[1, 2, 7], lp.xs[2, 0, 39] = bad, -bad
+        lp.xs[1, batch - 1, 7], lp.xs[2, 0, I - 1] = bad, -bad
     else:
         lp.h0[1, 5] = bad
     res = []
     for flags in (B.PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS, B.PIVOT_PLAN_LSTM_LAUNCH_PER_STEP):
         plan = G.dev_plan(lp.fc, flags=flags)
         try:
+            if flags == B.PIVOT_PLAN_LSTM_ONE_LAUNCH_ALWAYS:
+                _check_form(plan, 4, batch, form)
             # the step that meets the value, and a few behind it
             res.append([_lstm_gpu(lp, plan, lp.xs[:n], lp.h0, lp.c0) for n in (1, 2, 4)])
         finally:
