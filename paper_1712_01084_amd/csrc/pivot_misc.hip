@@ -108,11 +108,12 @@ template <typename WT>
 static int launch_gather_frag_t(const WT* x, int64_t ldx, const int32_t* pcol_pad, WT* xg, int K, int K_pad, int batch, hipStream_t st) {
     const int ngroups = K_pad / Elem<WT>::VEC;
     const size_t smem = align_up((size_t)K * sizeof(WT), 16);
-    // The copy pays for long fp16 inputs (us per call of a layer, copied / direct: 9216 columns, batch 32 6.2 / 6.4
-    // and 64 6.9 / 9.0; 25088 columns, batch 16 6.6 / 6.9, 32 8.25 / 10.1, 64 10.1 / 13.4; 4096 columns, batch 64
-    // 6.2 / 5.9).  Of fp32 rows a line holds half as many elements and the copy is twice as long: 9216 columns,
-    // batch 16 8.4 / 6.9 and 64 12.7 / 10.6, always slower.
-    if (sizeof(WT) == 2 && smem <= 64 * 1024 && (size_t)batch * K >= 256 * 1024) {
+    // The copy pays for long fp16 inputs of many elements (us per call of a layer with 1000 outputs, 16x32 tiles, 25 %
+    // kept, copied / direct: 2048 columns, batch 64 6.1 / 5.9; 3000, 64 6.5 / 7.1; 4090, 64 7.6 / 8.2; 4096, 32 6.0 / 6.2;
+    // 9216, 16 7.0 / 7.4; 12000, 17 8.3 / 9.1; 25088, 8 10.0 / 10.3; with 4096 outputs, 32x32 tiles: 2048, 64 9.1 / 9.2;
+    // 4096, 32 7.8 / 8.5; 8000, 32 9.8 / 10.3).  Of fp32 rows a line holds half as many elements and the copy is twice as
+    // long: 9216 columns, batch 16 8.4 / 6.9 and 64 12.7 / 10.6, always slower.
+    if (sizeof(WT) == 2 && smem <= 64 * 1024 && K >= 3000 && (size_t)batch * K >= 128 * 1024) {
         const int segs = 8;
         hipLaunchKernelGGL(gather_frag_kernel<WT>, dim3(segs, batch), dim3(512), smem, st, pcol_pad, x, xg, (long long)ldx, K, ngroups, batch, (ngroups + segs - 1) / segs);
     } else {
