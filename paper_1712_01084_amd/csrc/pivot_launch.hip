@@ -160,10 +160,13 @@ static void frag_split(const FcShape& s, int batch, int* slices, int* blocks) {
 // from two work items per compute unit on, and two where the work item has no more steps than two wavefronts request
 // at once: the other two would only load copies and wait (a layer behind one of 64 inputs, us, 4 / 2 wavefronts: 300 ->
 // 8000 fp32 8x32, 5 % kept, batch 6 11.1 / 8.6; 700 -> 8000 fp32 32x32, 10 %, batch 2 7.6 / 6.6; 700 -> 8000 fp16 32x64,
-// 10 %, batch 4 7.7 / 6.7; 1000 -> 500 fp16 32x32, 5 %, batch 4 5.9 / 5.7).
-static int frag_waves(const FcShape& s, int slices) {
-    const int steps = s.mean_tiles * s.bw * elem_size(s.wdtype) / 64;
-    int nw = steps <= 16 || (s.wdtype == PIVOT_F16 && (long long)s.nchunks * slices >= 512) ? 2 : 4;
+// 10 %, batch 4 7.7 / 6.7; 1000 -> 500 fp16 32x32, 5 %, batch 4 5.9 / 5.7), up to 16 steps at batch 2-8 and up to 8 beyond
+// (fp32: to batch 16), where a step's x is heavier too (4096x3000 fp32 8x32, 5 %, 5 steps, batch 64 12.2 / 12.8; 1000x2048 fp16 16x32, 25 %, 16 steps, batch 64 5.6 / 5.8; 4096 -> 2048 -> 2000 fp16 8x8,
+// 20 %, 6 steps, batch 64 13.2 / 12.1).
+static int frag_waves(const FcShape& s, int batch, int slices) {
+    const int cols = s.mean_tiles * s.bw, steps = cols * elem_size(s.wdtype) / 64;
+    const bool small = batch <= 8 ? steps <= 16 : (s.wdtype == PIVOT_F16 || batch <= 16) && (s.bh == 8 ? steps / 2 : steps) <= 8;   // (of tiles 8 high two sets make a step)
+    int nw = small || (s.wdtype == PIVOT_F16 && (long long)s.nchunks * slices >= 512) ? 2 : 4;
     return nw == 2 && s.chunk_tiles > 2 * frag_wave_tiles(s) ? 4 : nw;
 }
 // Batch rows one launch row covers in the kernel's epilogue and in the workspace (grid.y repeats it).
@@ -294,7 +297,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         if (!L.x_block_order) { set_error("internal: the batched matrix-core kernel needs x in fragment order"); return PIVOT_E_UNSUPPORTED; }
         if (L.bh > 64 || L.batch > 64) { set_error("shape outside the kernel's packed arguments"); return PIVOT_E_UNSUPPORTED; }
         a.xidx = L.col_idx; a.xs_stride = 0; a.xn_vecs = 0;
-        const int fnw = frag_waves(shape, sl);
+        const int fnw = frag_waves(shape, L.batch, sl);
         if (describe) { *describe = kernel_name("fc_frag_kernel<%s, %d, %d, %d, %d>", L.wdtype == PIVOT_F32 ? "float" : "_Float16", bhs, L.bw, nbt / 16, fnw); return PIVOT_OK; }
         using Launch = int (*)(const FcArgs&, int, int, int, dim3, hipStream_t);
         static const Launch by_height[2][3] = {{launch_frag_f32_8, launch_frag_f32_16, launch_frag_f32_32},
