@@ -77,7 +77,6 @@ int upload(pivot_fc_plan_t* p) {
         {h.xidx.data(),      h.xidx.size() * 4,             (void**)&d.xidx},
         {xblk.data(),        xblk.size() * 4,               (void**)&d.xidx_blk},
         {h.xsort.data(),     h.xsort.size() * 4,            (void**)&d.xsort},
-        {h.xsort_blk.data(), h.xsort_blk.size() * 4,        (void**)&d.xsort_blk},
         {rowid.data(),       rowid.size() * 4,              (void**)&d.rowid_pad},
         {h.row_ptr.data(),   h.row_ptr.size() * 4,          (void**)&d.row_ptr},
     };
@@ -233,7 +232,7 @@ int natural_input(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx, i
     if (fc_wants_frag(fc_shape(h, L.x_from), batch)) {
         int rc = launch_gather_frag(x_dev, ldx, plan->dev.pcol_pad, xg, h.d.K, h.K_pad, batch, h.d.wdtype, stream);
         if (rc != PIVOT_OK) return rc;
-        L.x = xg; L.ldx = h.K_pad; L.xidx = plan->dev.xidx_blk; L.xsort = plan->host.sorted_ok ? plan->dev.xsort_blk : nullptr; L.x_block_order = 1;
+        L.x = xg; L.ldx = h.K_pad; L.xidx = plan->dev.xidx_blk; L.x_block_order = 1;
     } else {
         L.x = x_dev; L.ldx = ldx; L.xidx = plan->dev.xidx; L.xsort = plan->host.sorted_ok ? plan->dev.xsort : nullptr; L.x_block_order = 0;
     }
@@ -470,7 +469,7 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
             rc = natural_input(p, x_dev, ldx, batch, ws + m.gather_off, stream, L);
             if (rc != PIVOT_OK) return rc;
         } else {
-            L.xidx = p->dev.xidx_blk; L.xsort = p->host.sorted_ok ? p->dev.xsort_blk : nullptr; L.x = ws + m.inter_off[l - 1]; L.ldx = p->host.K_pad; L.x_block_order = 1;
+            L.xidx = p->dev.xidx_blk; L.x = ws + m.inter_off[l - 1]; L.ldx = p->host.K_pad; L.x_block_order = 1;
         }
         if (l + 1 < Lc) {
             // producer-side store through the composed boundary array; identity boundaries store contiguously
@@ -607,7 +606,7 @@ int pivot_lstm_run(const pivot_fc_plan_t* plan, int H, int I, const void* xs_dev
         FcLaunch L{};
         rc = prepare(plan, batch, ws, ws + m.tickets, kXBlock, L);
         if (rc != PIVOT_OK) return rc;
-        L.xidx = plan->dev.xidx_blk; L.xsort = plan->host.sorted_ok ? plan->dev.xsort_blk : nullptr; L.x_block_order = 1;
+        L.xidx = plan->dev.xidx_blk; L.x_block_order = 1;
         L.x = xg + m.xg_step * (size_t)t; L.ldx = h.K_pad;
         L.scatter = plan->dev.prow_pad;      // gates land in natural order for the cell
         L.y = z; L.ldy = h.d.M; L.out_f16 = 0; L.stream = stream;

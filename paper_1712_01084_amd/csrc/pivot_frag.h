@@ -32,8 +32,8 @@
 
 namespace pivot {
 
-// Registers that hold the block columns of a wavefront's tiles: an item of a plan has at most 48 KB / (bw * 4 rows *
-// element size) tiles, 768 of the narrowest.
+// Registers that hold the block columns of a wavefront's tiles: an item of a device plan has at most 48 KB / (bw * 4
+// rows * element size) tiles (max_chunk_tiles), 768 of the narrowest, of which four wavefronts hold 248 each.
 constexpr int frag_cols(int bw, int vec) { return bw == 8 && vec == 8 ? 4 : 2; }
 
 template <typename WT> struct FragMfma;
@@ -65,7 +65,8 @@ __global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcA
     constexpr int RB  = BH < 16 ? 1 : BH / 16;          // row blocks
     constexpr int RT  = BH < 16 ? BH : 16;              // rows of A that come from one tile
     constexpr int TPG = TPS * RS;                       // tiles per group (what a wavefront consumes together)
-    // Steps in flight: 8 KB of weights per wavefront or more, in at most 40 fragments (160 registers)
+    // Steps in flight: 8 KB of weights per wavefront or more (4 KB for stacked tiles and 64 batch rows), in at most 40
+    // fragments (160 registers)
     constexpr int U   = (RB + RS * NBT) * 8 <= (RB < 2 ? 40 : 32) ? 8 : 4;
     constexpr int NC  = frag_cols(BW, VEC);             // registers of block columns per lane
     constexpr int NB  = 16 * NBT, N = BH * NB;

@@ -78,7 +78,6 @@ struct DevPlan {
     int32_t* xidx = nullptr;      // gather index for natural-order x
     int32_t* xidx_blk = nullptr;  // same for x already in block order: col_idx[t]*bw+c
     int32_t* xsort = nullptr;     // packed, source-ordered gather lists (see HostPlan), natural-order x
-    int32_t* xsort_blk = nullptr; // same for x in block order
     int32_t* rowid_pad = nullptr; // [M_pad] r for r < M, -1 in padding: stores that stay in block order
     int32_t* row_ptr = nullptr;   // [nbr+1] (persistent recurrent kernel: work split and piece lookup)
 };
@@ -110,7 +109,7 @@ struct FcLaunch {
     const float*   bias_p;
     const int32_t* xidx;        // [T*bw]: index into x of column c of tile t (-1 = padding): through pcol for
                                 // natural-order x, the block-space column itself for x already in block order
-    const int32_t* xsort;       // the same gather as packed source-ordered lists (LDS-fed matrix-core kernel), or NULL
+    const int32_t* xsort;       // the same gather as packed source-ordered lists (LDS-fed matrix-core kernel, x in natural order), or NULL
     const int32_t* scatter;     // [M_pad] block-space row -> index into y (-1 = padding row, not stored)
     int M_pad, K_pad, bh, bw, wdtype, layout, T, act, nchunks, nbr, chunk_tiles, wg_waves, row_slices;
     int lds_tiles;              // chunk_tiles if the plan carries the packed gather lists, else 0

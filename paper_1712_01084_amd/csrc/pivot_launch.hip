@@ -96,7 +96,7 @@ int fc_path(const FcShape& s, int batch) {
     const int layout = s.layout, wdtype = s.wdtype, bh = s.bh, bw = s.bw, lds_tiles = s.lds_tiles;
     // the matrix-core kernels read A fragments from row-major (BRC) tiles only
     if (layout != PIVOT_BRC || batch < 2) return kPathVector;
-    const bool frag = s.x_from != kXNoCopy && (long long)s.xrow_len * batch * elem_size(wdtype) < (1ll << 31) && s.chunk_tiles <= 4 * frag_wave_tiles(s);
+    const bool frag = s.x_from != kXNoCopy && (long long)s.xrow_len * batch * elem_size(wdtype) < (1ll << 31);
     const double weight_mb = (double)s.nchunks * s.mean_tiles * bh * bw * elem_size(wdtype) * 1e-6;
     if (frag && s.x_from == kXBlock) {
         const bool vector = wdtype == PIVOT_F32 && batch <= 8 && block_order_vector(s, batch);

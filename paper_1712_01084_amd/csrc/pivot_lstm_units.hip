@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(kUT, 2) lstm_units_kernel(UnitArgs a) {
         return (((ks * blocks + rb) * 64) + (kr / VEC) * 16 + r) * VEC + kr % VEC;
     };
     const int hsteps = a.hsteps, xsteps = a.xsteps;
-    const int nh = hsteps > wave ? (hsteps - wave + kUW - 1) / kUW : 0;     // k-steps wave, wave + 8, ...
+    const int nh = hsteps > wave ? (hsteps - wave + kUW - 1) / kUW : 0;     // k-steps wave, wave + 4, ...
     const int nx = xsteps > wave ? (xsteps - wave + kUW - 1) / kUW : 0;
     V w[HS][RB];
     #pragma unroll
