@@ -154,7 +154,7 @@ typedef struct pivot_plan_view {
                                   MFMA shape, K_pad < 2^19 - 1 and at most 8192 columns per piece: what the
                                   batch 3..16 kernel reads, so that neighbouring lanes gather neighbouring
                                   addresses */
-    const int32_t* xsort_blk;  /* same for an input already in block order (source = col_idx[t]*bw+c, all
+    const int32_t* xsort_blk;  /* host view only: the same for an input already in block order (source = col_idx[t]*bw+c, all
                                   ones for a padding column, i.e. one at or past K) */
 } pivot_plan_view;
 
@@ -223,7 +223,8 @@ int    pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream);
  *          much more than once (F32 and small F16 tiles: 12 MB of weights
  *          times further groups of four batch rows); chains and the
  *          recurrent loop, whose kernels produce that order, use it behind
- *          every boundary from batch 2 on.
+ *          every boundary from batch 2 on (F32 at batch 2 to 8: but for few
+ *          and long work items).
  *          Batch 5..16 with at most 4096 input columns, from a quarter of
  *          them staged per work item on: the rows of x are copied into
  *          LDS and the fragments gathered from there (fastest when x is
@@ -244,8 +245,10 @@ int  pivot_fc_kernel_name(const pivot_fc_plan_t* plan, int batch, char* buf, siz
 /*
  * pivot_fc_run_static - pivot_fc_run for callers that cannot allocate device
  * memory and have no workspace to hand over: code under HIP graph capture,
- * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
- * kernels, same result bits as pivot_fc_run without the workspace: the scratch
+ * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, and
+ * where the scratch fits same kernels and result bits as pivot_fc_run (else the
+ * batched form with launch rows of 16 batch rows, or the forms that need no copy
+ * of x, whose sums are in another order), without the workspace: the scratch
  * of the run (arrival counters and partial sums of split block rows, the
  * copy of x of the batched matrix-core form, where it fits) is a fixed
  * array in device memory that belongs to the library, PIVOT_STATIC_COUNTER_BYTES
@@ -349,24 +352,30 @@ int    pivot_mlp_status_word(const pivot_mlp_plan_t* plan, const uint32_t** word
  *
  * Three forms.  Two run the whole sequence in ONE launch, the weights in
  * registers and LDS for all steps.  In the first a workgroup owns whole units
- * and per step only h moves: BRC plans of both types, H up to 512 (F32) or 1024
- * (F16; 1024 or 2048 with the conditions of the second form), I up to 512 or
- * 1024, where the batch leaves at least 4 launches' workgroups room on the
- * device (half as many workgroups as compute units, half a compute unit each).
- * In the second h and the gate sums move: fp16 16x32 BRC tiles, batch <= 8, at
- * most 15 kept tiles per wavefront of a full-device grid (one workgroup per
- * compute unit, all co-resident) and K_pad/32 <= that grid.  There are no grid
- * barriers: the exchanged data carries the step it belongs to and a consumer
- * re-reads until it sees its step.  The workgroups wait for each other, so
- * nothing else should occupy the device while they run; a wait that does not
- * end within 2^18 polls gives up, every workgroup leaves and the status word
- * reads 1.  h and c are then undefined (workgroups that were through have
- * written theirs) until pivot_lstm_restore puts them back.  Every other plan (or
- * PIVOT_PLAN_LSTM_LAUNCH_PER_STEP), and every sequence of fewer than 4 steps
- * (8 steps for the first form where a block row keeps more than 128 pieces of 16
- * bytes per row), runs one layer launch and one cell launch per step: the
- * one-launch forms place every kept tile first.  pivot_lstm_status synchronises the stream and returns the status
- * word of the last pivot_lstm_run on this workspace (0 = completed).
+ * and per step only h moves: BRC plans of both types, H up to 512 (F32; 1024 at
+ * batch <= 8) or 1024 (F16; 2048 at batch <= 8 for plans the second form takes),
+ * I up to 512 (F32) or 1024 (F16), where the batch leaves the grid at most half
+ * as many workgroups as compute units (all of them for plans the second form
+ * takes), half a compute unit each.  In the second h and the gate sums move: fp16
+ * 16x32 BRC tiles, batch <= 8, at most 15 kept tiles per wavefront of a
+ * full-device grid (one workgroup per compute unit, all co-resident) and
+ * K_pad/32 <= that grid.  There are no grid barriers: the exchanged data carries
+ * the step it belongs to and a consumer re-reads until it sees its step.  The
+ * workgroups wait for each other: a launch needs its share of the device.  Four
+ * launches of the first form with half the compute units each are resident
+ * together; beside more of them (other processes, a process with more than four
+ * hardware queues), larger grids or a one-launch chain, a plan should ask for
+ * PIVOT_PLAN_LSTM_LAUNCH_PER_STEP.  A wait that does not end within 2^18 polls
+ * gives up, every workgroup leaves and the status word reads 1.  h and c are then
+ * undefined (workgroups that were through have written theirs) until
+ * pivot_lstm_restore puts them back.  Every other plan, every plan with
+ * PIVOT_PLAN_LSTM_LAUNCH_PER_STEP and every sequence of
+ * fewer than 4 steps, runs one layer launch and one cell launch per step: the
+ * one-launch forms place every kept tile first.  Sequences of 4 to 7 steps where
+ * a block row keeps more than 128 pieces of 16 bytes per row do not take the
+ * first form (the second where it fits, else launches per step).
+ * pivot_lstm_status synchronises the stream and returns the status word of the
+ * last pivot_lstm_run on this workspace (0 = completed).
  */
 size_t pivot_lstm_workspace_bytes(const pivot_fc_plan_t* plan, int H, int I, int steps, int batch);
 int    pivot_lstm_status(const pivot_fc_plan_t* plan, int steps, int batch, const void* ws_dev, void* stream, int* status);
