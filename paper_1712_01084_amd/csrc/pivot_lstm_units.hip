@@ -35,6 +35,7 @@
 // at most half a compute unit and every wait is bounded like those of the kernel
 // that exchanges gate sums.
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
 
 #include "pivot_fc_kernels.h"
@@ -519,9 +520,11 @@ struct UnitShape { int form, teams, bt, wgs, hsteps, xsteps, slots; size_t smem;
 // Compute units of a device, or 0; makes the LDS of the kernels available and checks that two workgroups of each fit
 // a compute unit.  Asked once per device.
 int units_device(int device) {
-    static int known[16] = {};                          // 0 unknown, -1 unusable, else compute units
-    int& k = known[device & 15];
-    if (k != 0) return k > 0 ? k : 0;
+    constexpr int kMaxDevices = 64;
+    static std::atomic<int> known[kMaxDevices];         // 0 unknown, -1 unusable, else compute units
+    if (device < 0 || device >= kMaxDevices) return 0;
+    std::atomic<int>& k = known[device];
+    if (const int v = k.load(std::memory_order_acquire)) return v > 0 ? v : 0;
     int prev = -1, cus = 0;
     if (hipGetDevice(&prev) != hipSuccess) { (void)hipGetLastError(); return 0; }
     if (prev != device && hipSetDevice(device) != hipSuccess) { (void)hipGetLastError(); return 0; }
@@ -535,7 +538,7 @@ int units_device(int device) {
         }
     if (!ok) (void)hipGetLastError();
     if (prev != device) (void)hipSetDevice(prev);
-    k = ok ? cus : -1;
+    k.store(ok ? cus : -1, std::memory_order_release);
     return ok ? cus : 0;
 }
 
