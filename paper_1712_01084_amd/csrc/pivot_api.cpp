@@ -68,7 +68,6 @@ int upload(pivot_fc_plan_t* p) {
         {h.vals.data(),      h.vals.size(),                 (void**)&d.vals},
         {h.col_idx.data(),   h.col_idx.size() * 4,          (void**)&d.col_idx},
         {chunks8.data(),     chunks8.size() * 4,            (void**)&d.chunks},
-        {h.part_base.data(), h.part_base.size() * 4,        (void**)&d.part_base},
         {h.bias_p.data(),    h.bias_p.size() * 4,           (void**)&d.bias_p},
         {h.prow_pad.data(),  h.prow_pad.size() * 4,         (void**)&d.prow_pad},
         {h.pcol_pad.data(),  h.pcol_pad.size() * 4,         (void**)&d.pcol_pad},
@@ -210,7 +209,7 @@ int prepare(const pivot_fc_plan_t* plan, int batch, void* tickets, void* partial
     if ((fc_ticket_bytes(h) > 0 && !tickets) || (fc_partial_bytes(h, batch, x_from) > 0 && !partials)) { set_error("workspace missing"); return PIVOT_E_WORKSPACE; }
     if (reinterpret_cast<uintptr_t>(tickets) % 16 != 0 || reinterpret_cast<uintptr_t>(partials) % 16 != 0) { set_error("workspace must be 16-byte aligned"); return PIVOT_E_WORKSPACE; }
     const DevPlan& d = plan->dev;
-    L.vals = d.vals; L.col_idx = d.col_idx; L.chunks = d.chunks; L.part_base = d.part_base; L.bias_p = d.bias_p;
+    L.vals = d.vals; L.col_idx = d.col_idx; L.chunks = d.chunks; L.bias_p = d.bias_p;
     L.K = h.d.K; L.x_resident = (h.d.flags & PIVOT_PLAN_GATHER_FROM_GLOBAL) ? 0 : ((h.d.flags & PIVOT_PLAN_GATHER_FROM_LDS_COPY) ? 2 : 1);
     L.M_pad = h.M_pad; L.K_pad = h.K_pad; L.bh = h.d.bh; L.bw = h.d.bw; L.wdtype = h.d.wdtype; L.layout = h.d.layout; L.T = h.T; L.act = h.d.act;
     L.nchunks = h.nchunks; L.nbr = h.nbr; L.chunk_tiles = h.chunk_tiles; L.wg_waves = h.wg_waves;

@@ -16,7 +16,7 @@
 namespace pivot {
 
 template <typename WT, int LAYOUT, int BH, int BW, int NW>
-__global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_LEAD_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_GEMV_PARAMS, int T, FcTail a) {
     using V = typename Elem<WT>::vec;
     constexpr int VEC = Elem<WT>::VEC;
     constexpr int NT  = NW * 64;
@@ -34,7 +34,9 @@ __global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_LEAD_PARAMS,
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = blockIdx.y;
-    const Chunk ck = load_chunk(a.uniform_ct, a.uniform_parts, p_chunks, p_part_base);
+    const int q_uniform_parts = q_ct_parts >> 16, q_uniform_ct = q_uniform_parts > 0 ? (q_ct_parts & 0xFFFF) : 0;
+    const int q_xs_stride = (q_ct_parts & 0xFFFF) * BW + VEC;
+    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks);
     const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles, slot = ck.slot;
     const int first = ck.first, nparts = ck.nparts;
     const int row0 = br * BH;
@@ -64,7 +66,7 @@ __global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_LEAD_PARAMS,
             const int tl = (i - c * ntg) * G + cs;
             const int tc = tl < ntiles ? tl : (ntiles > 0 ? ntiles - 1 : 0);
             const int cc = c < BW ? c : BW - 1;
-            off = ((size_t)cc * a.T + tile_begin + tc) * BH + rq * VEC;
+            off = ((size_t)cc * T + tile_begin + tc) * BH + rq * VEC;
             xi = tc * BW + cc;
             return tl < ntiles && c < BW;
         }
@@ -81,7 +83,7 @@ __global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_LEAD_PARAMS,
     #pragma unroll
     for (int u = 0; u < U; ++u) fill(u, wave + u * NW);
 
-    xst.template gather<false>(a.batch, a.ldx, 0, a.xs_stride, p_idx, reinterpret_cast<const WT*>(p_x), xs, tile_begin, ncols, b0, tid);
+    xst.template gather<false>((q_misc >> 7) & 0x7F, a.ldx, 0, q_xs_stride, p_idx, reinterpret_cast<const WT*>(p_x), xs, tile_begin, ncols, b0, tid);
     lds_barrier();
 
     float acc[VEC];
@@ -122,8 +124,8 @@ __global__ void __launch_bounds__(NW * 64) fc_colmajor_kernel(PIVOT_LEAD_PARAMS,
 
 template <typename WT, int LAYOUT, int BH, int BW>
 static int launch_t(const FcArgs& a, int nw, dim3 grid, size_t smem, hipStream_t st) {
-    if (nw >= 8) hipLaunchKernelGGL((fc_colmajor_kernel<WT, LAYOUT, BH, BW, 8>), grid, dim3(8 * 64), smem, st, PIVOT_LEAD_ARGS(a, a.xidx), a);
-    else         hipLaunchKernelGGL((fc_colmajor_kernel<WT, LAYOUT, BH, BW, 4>), grid, dim3(4 * 64), smem, st, PIVOT_LEAD_ARGS(a, a.xidx), a);
+    if (nw >= 8) hipLaunchKernelGGL((fc_colmajor_kernel<WT, LAYOUT, BH, BW, 8>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a.T, fc_tail(a));
+    else         hipLaunchKernelGGL((fc_colmajor_kernel<WT, LAYOUT, BH, BW, 4>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), a.T, fc_tail(a));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

@@ -33,13 +33,12 @@ namespace pivot {
 
 static constexpr int kTicketStride = 64;   // uint32 words between arrival counters (one per 256-byte line)
 
-// Arguments of the layer kernels (passed by value).
+// What the launchers need of a layer call.
 struct FcArgs {
     const void*    vals;
-    const int32_t* col_idx;     // [T] block column of every kept tile (matrix kernel)
-    const int32_t* xidx;        // [T*bw] index into x of every kept tile's columns, -1 = padding (vector kernel)
+    const int32_t* xidx;        // [T*bw] index into x of every kept tile's columns, -1 = padding (vector kernel); the
+                                // batched matrix-core kernel: [T] block column of every kept tile
     const int4*    chunks;
-    const int32_t* part_base;
     const float*   bias_p;
     const int32_t* scatter;     // [M_pad] destination of every block-space row, -1 = not stored
     const void*    x;
@@ -47,17 +46,58 @@ struct FcArgs {
     float*         partials;
     uint32_t*      tickets;
     long long ldx, ldy;
-    int batch, act, out_form, nchunks, nbr, xs_stride;   // out_form: kOutF16 | kOutFrag | padding columns << kOutPadShift
+    int batch, act, out_form, nchunks, nbr;   // out_form: kOutF16 | kOutFrag
+    int out_pad;                // how many of the last columns of a y in fragment order no row lands in
+    int slices;                 // row slices (gridDim.z)
     int bh_full;                // rows of a whole tile (the kernels' BH is the height of one row slice)
-    int tile_elems;             // bh_full * bw
     int uniform_ct;             // > 0: every chunk has exactly this many tiles and chunk i starts at tile i*uniform_ct,
     int uniform_parts;          //      uniform_parts chunks per block row: the descriptor is computed, not loaded
     int T;                      // kept tiles in the whole plan (the CBR layout strides by it)
     int chunk_tiles;            // the plan's chunk size (vector kernel: fixes the LDS row stride)
-    int xn_vecs;                // x-resident vector kernel: 16-byte vectors per row of x (row length / VEC)
-    int xn_stride;              //   elements between the LDS copies of consecutive batch rows (the row length)
+    int xn_vecs;                // x-resident forms: 16-byte vectors per row of x
+    int xn_missing;             //   elements the last of them has too many
     long long* trace;           // timeline builds only (PIVOT_TRACE): eight time stamps per wavefront, else unused
 };
+
+// The part of them that a kernel takes behind its leading arguments.  All arguments of a layer kernel together stay
+// within 112 bytes, and no kernel asks for its grid size (which would come as 256 bytes of hidden arguments): the host
+// writes a launch's arguments to device memory and waits for the last of them to arrive, up to 112 bytes in 2.3-2.7 us a
+// launch, beyond in 2.4-3.5 (0.07-0.7 us more, depending on the host; 500 bytes the same).
+// form: kOutF16 | kOutFrag | ReLU << 2 | row slices << 3 | batch << 7 | padding columns of y << 14 | xn_missing << 21.
+// (Packed: with four bytes of padding behind `form` the compiler loads sixteen bytes, finds the last register unused and
+// waits at the start of the kernel before it gives it to something else.)
+struct __attribute__((packed, aligned(4))) FcTail {
+    void*     y;
+    float*    partials;
+    uint32_t* tickets;
+    long long ldx, ldy;
+    int       nchunks, nbr;
+    uint32_t  form;
+#ifdef PIVOT_TRACE
+    long long* trace;
+#endif
+};
+// FcTail::form taken apart.  Opaque, so that the compiler takes it apart here: hoisted to the start of the kernel it
+// waited there for the argument block (4096x4096 fp16, 25 % kept, batch 16 5.93 -> 6.12 us).
+struct FcForm {
+    uint32_t form;
+    __device__ __forceinline__ explicit FcForm(const FcTail& a) : form(a.form) { asm volatile("" : "+s"(form)); }
+    __device__ __forceinline__ int out() const { return form & 3; }
+    __device__ __forceinline__ int act() const { return (form >> 2) & 1; }
+    __device__ __forceinline__ int slices() const { return (form >> 3) & 15; }
+    __device__ __forceinline__ int batch() const { return (form >> 7) & 127; }
+    __device__ __forceinline__ int out_pad() const { return (form >> 14) & 127; }
+    __device__ __forceinline__ int xn_missing() const { return (form >> 21) & 7; }
+};
+inline FcTail fc_tail(const FcArgs& a) {
+    FcTail t{};
+    t.y = a.y; t.partials = a.partials; t.tickets = a.tickets; t.ldx = a.ldx; t.ldy = a.ldy; t.nchunks = a.nchunks; t.nbr = a.nbr;
+    t.form = (uint32_t)a.out_form | (uint32_t)a.act << 2 | (uint32_t)a.slices << 3 | (uint32_t)a.batch << 7 | (uint32_t)a.out_pad << 14 | (uint32_t)a.xn_missing << 21;
+#ifdef PIVOT_TRACE
+    t.trace = a.trace;
+#endif
+    return t;
+}
 
 // Timeline builds (-DPIVOT_TRACE, see bench_timeline.py): the vector kernel records the constant 100 MHz
 // clock at eight points per wavefront: 0 start, 1 every load issued, 2 copy of x stored to LDS, 3 past the
@@ -90,20 +130,12 @@ struct FcArgs {
 #define PIVOT_STAMP_FLUSH(a, nw, wave, lane) do {} while (0)
 #endif
 
-// The seven pointers every wavefront needs first are separate leading kernel
-// arguments: with kernel-argument preloading they arrive in SGPRs with the
-// wave, so the first dependent load can be issued at once.
-#define PIVOT_LEAD_PARAMS const int4* __restrict__ p_chunks, const int32_t* __restrict__ p_part_base, \
-    const int32_t* __restrict__ p_idx, const void* __restrict__ p_vals, const float* __restrict__ p_bias, \
-    const int32_t* __restrict__ p_scatter, const void* __restrict__ p_x
-#define PIVOT_LEAD_ARGS(a, idx) (a).chunks, (a).part_base, (idx), (a).vals, (a).bias_p, (a).scatter, (a).x
-
-// The vector kernel goes further: everything it needs before and while its
-// loads are issued (six pointers and two packed scalars = the 14 dwords that
-// are preloaded into SGPRs) comes first, so that nothing on the way to the
-// first FMA waits for a fetch of the argument block; the rest of FcArgs is
-// first touched in the epilogue (the row stride of x, needed only with more
-// than one batch row, also comes from there).
+// Everything a kernel needs before and while its loads are issued (six pointers
+// and two packed scalars = the 14 dwords that kernel-argument preloading puts
+// into SGPRs) comes first, so that nothing on the way to the first FMA waits for
+// a fetch of the argument block; FcTail is first touched in the epilogue (the
+// row stride of x, needed only with more than one batch row, also comes from
+// there).
 // q_ct_parts = tiles per chunk | uniform_parts << 16 (uniform_parts 0: the schedule is not regular, the low half
 //              is then the plan's chunk size); q_misc = bh_full | batch << 7 | xn_vecs << 14.
 #define PIVOT_GEMV_PARAMS const int4* __restrict__ p_chunks, const int32_t* __restrict__ p_idx, \
@@ -158,7 +190,6 @@ __device__ __forceinline__ float dot_vec(const f16x8& w, const f16x8& x, float a
 
 constexpr int kOutF16 = 1;     // y is fp16, else fp32
 constexpr int kOutFrag = 2;    // y is in fragment order (frag_index) with ldy columns, else rows of ldy elements
-constexpr int kOutPadShift = 2;   // above: how many of the last columns of a y in fragment order no row lands in
 __device__ __forceinline__ void store_out(void* y, long long idx, float v, int out_form) {
     if (out_form & kOutF16) reinterpret_cast<_Float16*>(y)[idx] = (_Float16)v;
     else         reinterpret_cast<float*>(y)[idx] = v;
@@ -466,7 +497,7 @@ struct XRes {
 // schedule is uniform (balanced pruning: every block row keeps the same
 // number of tiles), which takes one dependent load off the critical path.
 struct Chunk { int br, tile_begin, ntiles, slot, first, nparts; };
-__device__ __forceinline__ Chunk load_chunk(int uniform_ct, int uniform_parts, const int4* chunks, const int32_t* part_base) {
+__device__ __forceinline__ Chunk load_chunk(int uniform_ct, int uniform_parts, const int4* chunks) {
     Chunk c;
     if (uniform_ct > 0) {
         c.br = blockIdx.x / uniform_parts;
@@ -483,7 +514,6 @@ __device__ __forceinline__ Chunk load_chunk(int uniform_ct, int uniform_parts, c
         c.br = cd.x; c.tile_begin = cd.y; c.ntiles = cd.z - cd.y; c.slot = cd.w;
         c.first = ce.x;
         c.nparts = ce.y;
-        (void)part_base;
     }
     return c;
 }
@@ -491,12 +521,12 @@ __device__ __forceinline__ Chunk load_chunk(int uniform_ct, int uniform_parts, c
 // A y in fragment order is the input of the next layer: its padding columns, which no row lands in.  (They are told
 // by what the epilogue has loaded anyway; two more arguments were fetched in the middle of the staging.)
 template <int NBT, int NT>
-__device__ __forceinline__ void clear_padding(const FcArgs& a, int b0, int tid) {
+__device__ __forceinline__ void clear_padding(const FcTail& a, const FcForm& f, int b0, int tid) {
     if (blockIdx.x != 0 || blockIdx.z != 0) return;
-    const int npad = a.out_form >> kOutPadShift, first = (int)a.ldy - npad;
+    const int npad = f.out_pad(), first = (int)a.ldy - npad;
     for (int i = tid; i < npad * NBT; i += NT) {
         const int b = b0 + i % NBT, c = first + i / NBT;
-        if (b < a.batch) store_out(a.y, (long long)frag_index(b, c, a.batch, 2 + (a.out_form & kOutF16)), 0.f, a.out_form);
+        if (b < f.batch()) store_out(a.y, (long long)frag_index(b, c, f.batch(), 2 + (f.out() & kOutF16)), 0.f, f.out());
     }
 }
 
@@ -511,11 +541,12 @@ __device__ __forceinline__ void clear_padding(const FcArgs& a, int b0, int tid) 
 // a chain fetches the code of both (4096-4096-1000 fp32 32x64, batch 3 11.8 / 12.3).
 enum { kRows = 0, kFragOrder = 1, kEither = 2 };
 template <int BH, int NBT, int NT, int OUT>
-__device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, int nred, int br, int slot,
+__device__ __forceinline__ void finish_rows(const FcTail& a, const float* red, int nred, int br, int slot,
                                             int first, int nparts, const RowPre<BH, BH * NBT, NT>& rp,
                                             int b0, int tid, int* s_flag) {
     constexpr int N = BH * NBT;
-    const int gy = blockIdx.y, slice = blockIdx.z, SL = gridDim.z;
+    const FcForm f(a);
+    const int gy = blockIdx.y, slice = blockIdx.z, SL = f.slices();
     if (nparts > 1) {
         float* mine = a.partials + (((size_t)gy * a.nchunks + slot) * SL + slice) * N;
         for (int idx = tid; idx < N; idx += NT) {
@@ -541,7 +572,7 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
         }
         __syncthreads();
         if (!*s_flag) {
-            if (OUT == kFragOrder || (OUT == kEither && (a.out_form & kOutFrag))) clear_padding<NBT, NT>(a, b0, tid);
+            if (OUT == kFragOrder || (OUT == kEither && (f.out() & kOutFrag))) clear_padding<NBT, NT>(a, f, b0, tid);
             return;
         }
     }
@@ -551,7 +582,7 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
             const int idx = tid + k * NT;
             if (idx >= N) break;
             const int j = idx / BH;
-            if (b0 + j >= a.batch) continue;
+            if (b0 + j >= f.batch()) continue;
             float s = 0.f;
             if (nparts > 1) {
                 const float* p = a.partials + (((size_t)gy * a.nchunks + first) * SL + slice) * N + idx;
@@ -559,17 +590,17 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
             } else {
                 for (int w = 0; w < nred; ++w) s += red[w * N + idx];
             }
-            const float v = apply_act(s + rp.bias[k], a.act);
+            const float v = apply_act(s + rp.bias[k], f.act());
             if ((PIVOT_ABLATE & 8) && !(v == 12345.678f)) continue;      // ablation: computed, never stored
             if (rp.dst[k] >= 0) store(b0 + j, rp.dst[k], v);
         }
     };
-    if (OUT == kFragOrder || (OUT == kEither && __builtin_expect(a.out_form & kOutFrag, 0))) {
-        finish([&](int b, int c, float v) { store_out(a.y, (long long)frag_index(b, c, a.batch, 2 + (a.out_form & kOutF16)), v, a.out_form); });
-        clear_padding<NBT, NT>(a, b0, tid);
+    if (OUT == kFragOrder || (OUT == kEither && __builtin_expect(f.out() & kOutFrag, 0))) {
+        finish([&](int b, int c, float v) { store_out(a.y, (long long)frag_index(b, c, f.batch(), 2 + (f.out() & kOutF16)), v, f.out()); });
+        clear_padding<NBT, NT>(a, f, b0, tid);
         if (OUT == kEither) __builtin_amdgcn_endpgm();
     }
-    if (OUT != kFragOrder) finish([&](int b, int c, float v) { store_out(a.y, (long long)b * a.ldy + c, v, a.out_form); });
+    if (OUT != kFragOrder) finish([&](int b, int c, float v) { store_out(a.y, (long long)b * a.ldy + c, v, f.out()); });
 }
 
 // ---------------------------------------------------------------------------
@@ -583,7 +614,7 @@ __device__ __forceinline__ void finish_rows(const FcArgs& a, const float* red, i
 // to 16 vectors of x per thread (long inputs, LDS beyond 64 KB: a gather of single elements from a long x
 // moves a whole cache line per element, the copy moves every line once).
 template <typename WT, int BH, int BW, int NB, int NW, int XR, int OUT>
-__device__ __forceinline__ void fc_gemv_body(PIVOT_GEMV_PARAMS, const FcArgs& a) {
+__device__ __forceinline__ void fc_gemv_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
     using V = typename Elem<WT>::vec;
     constexpr int VEC = Elem<WT>::VEC;
     constexpr int NT  = NW * 64;
@@ -619,7 +650,7 @@ __device__ __forceinline__ void fc_gemv_body(PIVOT_GEMV_PARAMS, const FcArgs& a)
     XRes<WT, NB, NT, (XR == 3) ? 16 : 8> xres;
     constexpr bool kLoadX = !(PIVOT_ABLATE & (1 | 4)), kStageX = !(PIVOT_ABLATE & (1 | 2));
     if constexpr (XR >= 2 && kLoadX) xres.load(q_batch, q_ldx, q_xn_vecs, p_x, b0, tid);
-    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks, a.part_base);
+    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks);
     const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles, slot = ck.slot;
     const int first = ck.first, nparts = ck.nparts;
     const int ngroups = (ntiles + TPL - 1) / TPL;
@@ -772,11 +803,11 @@ __device__ __forceinline__ void fc_gemv_body(PIVOT_GEMV_PARAMS, const FcArgs& a)
 }
 
 template <typename WT, int BH, int BW, int NB, int NW, int XR>
-__global__ void __launch_bounds__(NW * 64) fc_gemv_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(NW * 64) fc_gemv_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_gemv_body<WT, BH, BW, NB, NW, XR, kRows>(PIVOT_GEMV_PASS, a);
 }
 template <typename WT, int BH, int BW, int NB, int NW, int XR>
-__global__ void __launch_bounds__(NW * 64) fc_gemv_chain_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(NW * 64) fc_gemv_chain_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_gemv_body<WT, BH, BW, NB, NW, XR, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
@@ -824,7 +855,7 @@ template <> struct Mfma<2> : Mfma<0> {};
 // never stored.
 // ---------------------------------------------------------------------------
 template <int KIND, int BH, int BW, int NBS, int NW, int XR, int OUT>
-__device__ __forceinline__ void fc_mfma_lds_body(PIVOT_GEMV_PARAMS, const FcArgs& a) {
+__device__ __forceinline__ void fc_mfma_lds_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
     using MF = Mfma<KIND>;
     using acc_t = typename MF::acc_t;
     using WT = _Float16;
@@ -856,7 +887,7 @@ __device__ __forceinline__ void fc_mfma_lds_body(PIVOT_GEMV_PARAMS, const FcArgs
     const long long q_ldx = (XR != 0) ? (long long)q_xn_vecs * VEC : a.ldx;
     XRes<WT, NBS, NT> xres;
     if constexpr (XR != 0) xres.load(q_batch, q_ldx, q_xn_vecs, p_x, b0, tid);
-    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks, a.part_base);
+    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks);
     const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles, slot = ck.slot;
     const int first = ck.first, nparts = ck.nparts;
     const int row0 = br * q_bh_full + slice * BH;
@@ -949,11 +980,11 @@ __device__ __forceinline__ void fc_mfma_lds_body(PIVOT_GEMV_PARAMS, const FcArgs
 }
 
 template <int KIND, int BH, int BW, int NBS, int NW, int XR>
-__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_mfma_lds_body<KIND, BH, BW, NBS, NW, XR, kRows>(PIVOT_GEMV_PASS, a);
 }
 template <int KIND, int BH, int BW, int NBS, int NW, int XR>
-__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_mfma_lds_body<KIND, BH, BW, NBS, NW, XR, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
@@ -976,7 +1007,7 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_P
 // vectors, 16-byte aligned and densely packed (else an element-wise copy).
 // ---------------------------------------------------------------------------
 template <int KIND, int BH, int BW, int OUT>
-__device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcArgs& a) {
+__device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
     using MF = Mfma<KIND>;
     using acc_t = typename MF::acc_t;
     using WT = _Float16;
@@ -1023,7 +1054,7 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcArg
         #pragma unroll
         for (int k = 0; k < 2 * XV; ++k) xload(k);
     }
-    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks, a.part_base);
+    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks);
     const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles, slot = ck.slot;
     const int first = ck.first, nparts = ck.nparts;
     const int row0 = br * q_bh_full + slice * BH;
@@ -1076,11 +1107,12 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcArg
             }
         }
     } else {
-        // rows that are not whole aligned vectors: element by element (a.xn_stride = elements per row)
+        // rows that are not whole aligned vectors: element by element
         const WT* x = reinterpret_cast<const WT*>(p_x);
+        const int xlen = q_xn_vecs * 8 - FcForm(a).xn_missing();
         for (int b = wave; b < NBS; b += NW) {
             if (b0 + b >= q_batch) continue;
-            for (int c = lane; c < a.xn_stride; c += 64)
+            for (int c = lane; c < xlen; c += 64)
                 *reinterpret_cast<WT*>(smem + b * row_bytes + c * 2) = x[(long long)(b0 + b) * a.ldx + c];
         }
     }
@@ -1143,11 +1175,11 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcArg
 }
 
 template <int KIND, int BH, int BW>
-__global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_mfma_xrow_body<KIND, BH, BW, kRows>(PIVOT_GEMV_PASS, a);
 }
 template <int KIND, int BH, int BW>
-__global__ void __launch_bounds__(512) fc_mfma_xrow_chain_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(512) fc_mfma_xrow_chain_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_mfma_xrow_body<KIND, BH, BW, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 

@@ -52,7 +52,7 @@ template <> struct FragMfma<float> {
 
 // BH: rows of this launch's slice (8, 16 or 32), NBT: blocks of 16 batch rows per launch row, NW: wavefronts (2 or 4).
 template <typename WT, int BH, int BW, int NBT, int NW>
-__global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcArgs a) {
+__global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     using V = typename Elem<WT>::vec;
     using MF = FragMfma<WT>;
     constexpr int VEC = Elem<WT>::VEC;
@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcA
     const int b0 = blockIdx.y * NB, slice = blockIdx.z;
     const int q_uniform_parts = q_ct_parts >> 16, q_uniform_ct = q_uniform_parts > 0 ? (q_ct_parts & 0xFFFF) : 0;
     const int q_bh_full = q_misc & 0x7F, q_batch = (q_misc >> 7) & 0x7F;
-    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks, a.part_base);
+    const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks);
     const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles;
     const int row0 = br * q_bh_full + slice * BH;
     const int tile_elems = q_bh_full * BW;
@@ -242,8 +242,8 @@ __global__ void __launch_bounds__(NW * 64) fc_frag_kernel(PIVOT_GEMV_PARAMS, FcA
 template <typename WT, int BH, int BW, int NBT>
 static int launch_frag_t(const FcArgs& a, int nw, dim3 grid, hipStream_t st) {
     const size_t smem = (size_t)nw * BH * 16 * NBT * 4;
-    if (nw == 2) hipLaunchKernelGGL((fc_frag_kernel<WT, BH, BW, NBT, 2>), grid, dim3(128), smem, st, PIVOT_GEMV_ARGS(a), a);
-    else         hipLaunchKernelGGL((fc_frag_kernel<WT, BH, BW, NBT, 4>), grid, dim3(256), smem, st, PIVOT_GEMV_ARGS(a), a);
+    if (nw == 2) hipLaunchKernelGGL((fc_frag_kernel<WT, BH, BW, NBT, 2>), grid, dim3(128), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
+    else         hipLaunchKernelGGL((fc_frag_kernel<WT, BH, BW, NBT, 4>), grid, dim3(256), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

@@ -19,16 +19,16 @@ static int launch_t(const FcArgs& a, int nw, dim3 grid, size_t smem, hipStream_t
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
             have = smem;
         }
-        hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+        hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     }
-    else if (nw == 16) hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 16, XR>), grid, dim3(16 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
-    else if (nw == 8)  hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+    else if (nw == 16) hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 16, XR>), grid, dim3(16 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
+    else if (nw == 8)  hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     else if (nw == 1) {
         // one wavefront per work item: batch 1, gather from global memory only (the launcher asks for nothing else)
-        if constexpr (NB == 1 && XR == 0) hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, 1, 1, 0>), grid, dim3(64), smem, st, PIVOT_GEMV_ARGS(a), a);
+        if constexpr (NB == 1 && XR == 0) hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, 1, 1, 0>), grid, dim3(64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
         else { set_error("internal: one-wavefront work items at batch %d, copy form %d", NB, XR); return PIVOT_E_UNSUPPORTED; }
     }
-    else               hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 4, XR>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+    else               hipLaunchKernelGGL((fc_gemv_kernel<WT, BH, BW, NB, 4, XR>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }
@@ -45,9 +45,9 @@ static int launch_nb(const FcArgs& a, int nb, int nw, int xres, dim3 grid, size_
 // y in fragment order: batches from 2 on (launch rows of 2 or 4 batch rows), no one-wavefront work items
 template <typename WT, int BH, int BW, int NB, int XR>
 static int launch_chain_t(const FcArgs& a, int nw, dim3 grid, size_t smem, hipStream_t st) {
-    if (nw == 16)     hipLaunchKernelGGL((fc_gemv_chain_kernel<WT, BH, BW, NB, 16, XR>), grid, dim3(16 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
-    else if (nw == 8) hipLaunchKernelGGL((fc_gemv_chain_kernel<WT, BH, BW, NB, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
-    else              hipLaunchKernelGGL((fc_gemv_chain_kernel<WT, BH, BW, NB, 4, XR>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+    if (nw == 16)     hipLaunchKernelGGL((fc_gemv_chain_kernel<WT, BH, BW, NB, 16, XR>), grid, dim3(16 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
+    else if (nw == 8) hipLaunchKernelGGL((fc_gemv_chain_kernel<WT, BH, BW, NB, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
+    else              hipLaunchKernelGGL((fc_gemv_chain_kernel<WT, BH, BW, NB, 4, XR>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

@@ -69,7 +69,6 @@ struct DevPlan {
     void*    vals = nullptr;
     int32_t* col_idx = nullptr;
     int32_t* chunks = nullptr;
-    int32_t* part_base = nullptr;
     float*   bias_p = nullptr;
     int32_t* prow_pad = nullptr;
     int32_t* pcol_pad = nullptr;
@@ -105,7 +104,6 @@ struct FcLaunch {
     const void*    vals;
     const int32_t* col_idx;
     const int32_t* chunks;      // eight ints per chunk: (block_row, tile_begin, tile_end, slot, first slot of the row, pieces, 0, 0)
-    const int32_t* part_base;
     const float*   bias_p;
     const int32_t* xidx;        // [T*bw]: index into x of column c of tile t (-1 = padding): through pcol for
                                 // natural-order x, the block-space column itself for x already in block order

@@ -275,13 +275,13 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     const int es = elem_size(L.wdtype);
 
     FcArgs a;
-    a.vals = L.vals; a.col_idx = L.col_idx; a.xidx = L.xidx; a.chunks = reinterpret_cast<const int4*>(L.chunks);
-    a.part_base = L.part_base; a.bias_p = L.bias_p; a.scatter = L.scatter;
+    a.vals = L.vals; a.xidx = L.xidx; a.chunks = reinterpret_cast<const int4*>(L.chunks);
+    a.bias_p = L.bias_p; a.scatter = L.scatter;
     a.x = L.x; a.y = L.y; a.partials = L.partials; a.tickets = L.tickets;
     a.ldx = L.ldx; a.ldy = L.ldy; a.batch = L.batch; a.act = L.act;
     a.nchunks = L.nchunks; a.nbr = L.nbr;
-    a.out_form = (L.out_f16 ? kOutF16 : 0) | (L.out_frag ? kOutFrag | L.out_pad << kOutPadShift : 0);
-    a.bh_full = L.bh; a.tile_elems = L.bh * L.bw;
+    a.out_form = (L.out_f16 ? kOutF16 : 0) | (L.out_frag ? kOutFrag : 0); a.out_pad = L.out_frag ? L.out_pad : 0;
+    a.slices = sl; a.bh_full = L.bh; a.xn_vecs = a.xn_missing = 0;
     a.uniform_ct = L.uniform_ct; a.uniform_parts = L.uniform_parts;
     a.T = L.T; a.chunk_tiles = L.chunk_tiles;
     a.trace = nullptr;
@@ -296,7 +296,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     if (path == kPathFrag) {
         if (!L.x_block_order) { set_error("internal: the batched matrix-core kernel needs x in fragment order"); return PIVOT_E_UNSUPPORTED; }
         if (L.bh > 64 || L.batch > 64) { set_error("shape outside the kernel's packed arguments"); return PIVOT_E_UNSUPPORTED; }
-        a.xidx = L.col_idx; a.xs_stride = 0; a.xn_vecs = 0;
+        a.xidx = L.col_idx;
         const int fnw = frag_waves(shape, L.batch, sl);
         if (describe) { *describe = kernel_name("fc_frag_kernel<%s, %d, %d, %d, %d>", L.wdtype == PIVOT_F32 ? "float" : "_Float16", bhs, L.bw, nbt / 16, fnw); return PIVOT_OK; }
         using Launch = int (*)(const FcArgs&, int, int, int, dim3, hipStream_t);
@@ -312,7 +312,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         const int vecs = (xlen + 7) / 8;
         // rows copied with 16-byte loads when they are whole aligned vectors, densely packed; else element by element
         const bool vec_rows = xlen % 8 == 0 && L.ldx == xlen && (reinterpret_cast<uintptr_t>(L.x) & 15) == 0;
-        a.xn_vecs = vecs | (vec_rows ? (1 << 17) : 0); a.xn_stride = xlen; a.xs_stride = 0;
+        a.xn_vecs = vecs | (vec_rows ? (1 << 17) : 0); a.xn_missing = vecs * 8 - xlen;
         const size_t steps_cols = ((size_t)(a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) + 1) * L.bw;
         size_t smem = (size_t)16 * (vecs * 16 + 16) + steps_cols * 4;
         const size_t red_bytes = (size_t)8 * bhs * 16 * 4;
@@ -322,13 +322,13 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         return launch_mfma_xrow_f16(a, kind, bhs, L.bw, grid, smem, st);
     }
     // staged x: nbt rows of (tiles per chunk)*bw elements, plus 16 bytes whose last element is the dump slot
-    // (the vector kernel derives the same stride from its preloaded arguments)
+    // (the kernels derive the same stride from their preloaded arguments)
     // the LDS-fed matrix-core kernel takes slices that are not whole 32-row blocks of 16-column tiles as pairs
     // of tiles (16x16x32 MFMA) and keeps 16 zeroed columns after the last staged tile
     int kind = mfma_kind(L.wdtype, L.bh, L.bw);
     if (ml && kind == 1 && L.bw == 16 && bhs % 32 != 0) kind = 2;
-    a.xs_stride = (a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) * L.bw + (ml && kind == 2 ? 16 : 0) + 16 / es;
-    size_t xs_bytes = (size_t)nbt * a.xs_stride * es;
+    const int xs_stride = (a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) * L.bw + (ml && kind == 2 ? 16 : 0) + 16 / es;
+    size_t xs_bytes = (size_t)nbt * xs_stride * es;
     size_t red_bytes = (size_t)nw * bhs * nbt * 4;
     // x-resident variant: every work item first copies the whole of x (nbt rows) into LDS with independent
     // coalesced loads and gathers from there.  Taken when the rows are 16-byte vectors (densely packed if there
@@ -374,7 +374,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
             red_bytes = (size_t)nw * bhs * nbt * 4;
         }
     }
-    a.xn_vecs = xres ? xlen / vec : 0; a.xn_stride = xlen;
+    a.xn_vecs = xres ? xlen / vec : 0;
     size_t smem = xres ? xn_bytes + xs_bytes : xs_bytes;
     smem = align_up(smem > red_bytes ? smem : red_bytes, 16);
     if (smem > (size_t)(xres == 3 ? 150 : 64) * 1024) { set_error("chunk does not fit in LDS (%zu bytes)", smem); return PIVOT_E_UNSUPPORTED; }

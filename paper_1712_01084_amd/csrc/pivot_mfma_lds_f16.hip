@@ -6,8 +6,8 @@ namespace pivot {
 template <int KIND, int BH, int BW, int NBS, int XR>
 static int launch_w(const FcArgs& a, int nw, dim3 grid, size_t smem, hipStream_t st) {
     const bool chain = (a.out_form & kOutFrag) != 0;
-    if (nw >= 8) hipLaunchKernelGGL((chain ? fc_mfma_lds_chain_kernel<KIND, BH, BW, NBS, 8, XR> : fc_mfma_lds_kernel<KIND, BH, BW, NBS, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
-    else         hipLaunchKernelGGL((chain ? fc_mfma_lds_chain_kernel<KIND, BH, BW, NBS, 4, XR> : fc_mfma_lds_kernel<KIND, BH, BW, NBS, 4, XR>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+    if (nw >= 8) hipLaunchKernelGGL((chain ? fc_mfma_lds_chain_kernel<KIND, BH, BW, NBS, 8, XR> : fc_mfma_lds_kernel<KIND, BH, BW, NBS, 8, XR>), grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
+    else         hipLaunchKernelGGL((chain ? fc_mfma_lds_chain_kernel<KIND, BH, BW, NBS, 4, XR> : fc_mfma_lds_kernel<KIND, BH, BW, NBS, 4, XR>), grid, dim3(4 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

@@ -17,7 +17,7 @@ static int launch_c(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         have = smem;
     }
-    hipLaunchKernelGGL(kernel, grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), a);
+    hipLaunchKernelGGL(kernel, grid, dim3(8 * 64), smem, st, PIVOT_GEMV_ARGS(a), fc_tail(a));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }
