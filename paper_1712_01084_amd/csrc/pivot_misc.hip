@@ -46,39 +46,28 @@ __global__ void __launch_bounds__(512) gather_frag_kernel(const int32_t* __restr
     using V = typename Elem<WT>::vec;
     constexpr int VEC = Elem<WT>::VEC, NT = 512;
     extern __shared__ __align__(16) char smem[];
-    WT* row = reinterpret_cast<WT*>(smem);
     const int tid = threadIdx.x, b = blockIdx.y;
+    // whole aligned 16-byte pieces, from the one that holds the row's first element to the one that holds its last
     const WT* xr = x + (long long)b * ldx;
-    // whole vectors from the first 16-byte boundary of the row on, single elements in front and behind
-    const int head0 = (int)((16 - (reinterpret_cast<uintptr_t>(xr) & 15)) & 15) / (int)sizeof(WT);
-    const int head = head0 < K ? head0 : K;
-    const int nvec = (K - head) / VEC;
-    const V* xv = reinterpret_cast<const V*>(xr + head);
+    const int shift = (int)(reinterpret_cast<uintptr_t>(xr) & 15) / (int)sizeof(WT);
+    const int nvec = (shift + K + VEC - 1) / VEC;
+    const V* xv = reinterpret_cast<const V*>(xr - shift);
     const int g0 = blockIdx.x * seg_groups, g1 = g0 + seg_groups < ngroups ? g0 + seg_groups : ngroups;
-    V v[8];                                             // 64 KB by 512 threads: the whole row at once
-    #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int i = u * NT + tid;
-        if (i < nvec) v[u] = xv[i];
-    }
-    const int tail = head + nvec * VEC + tid;
-    const WT first = xr[tid < head ? tid : 0], last = xr[tail < K ? tail : 0];
     GroupIdx<WT> gi;
     gi.load(pcol_pad, g0 + tid < g1 ? g0 + tid : 0);
+    // straight into LDS: no register waits for another piece (kept in registers behind a test per piece, the compiler
+    // waited for the second piece before it asked for the third)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < 8; ++u) {                       // 64 KB by 512 threads: the whole row at once
         const int i = u * NT + tid;
-        if (i < nvec) {
-            if (head == 0) *reinterpret_cast<V*>(row + i * VEC) = v[u];
-            else {
-                #pragma unroll
-                for (int e = 0; e < VEC; ++e) row[head + i * VEC + e] = v[u][e];
-            }
-        }
+        if (i < nvec)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xv + i),
+                                             (__attribute__((address_space(3))) void*)(smem + (u * NT + wave * 64) * 16), 16, 0, 0);
     }
-    if (tid < head) row[tid] = first;
-    if (tail < K) row[tail] = last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    const WT* row = reinterpret_cast<const WT*>(smem) + shift;
     for (int g = g0 + tid; g < g1; g += NT) {
         if (g != g0 + tid) gi.load(pcol_pad, g);
         reinterpret_cast<V*>(xg)[(size_t)g * batch + b] = gi.gather(row);
@@ -107,7 +96,7 @@ __global__ void __launch_bounds__(256) gather_frag_far_kernel(const int32_t* __r
 template <typename WT>
 static int launch_gather_frag_t(const WT* x, int64_t ldx, const int32_t* pcol_pad, WT* xg, int K, int K_pad, int batch, hipStream_t st) {
     const int ngroups = K_pad / Elem<WT>::VEC;
-    const size_t smem = align_up((size_t)K * sizeof(WT), 16);
+    const size_t smem = align_up((size_t)K * sizeof(WT), 16) + 16;
     // The copy pays for long fp16 inputs of many elements (us per call of a layer with 1000 outputs, 16x32 tiles, 25 %
     // kept, copied / direct: 2048 columns, batch 64 6.1 / 5.9; 3000, 64 6.5 / 7.1; 4090, 64 7.6 / 8.2; 4096, 32 6.0 / 6.2;
     // 9216, 16 7.0 / 7.4; 12000, 17 8.3 / 9.1; 25088, 8 10.0 / 10.3; with 4096 outputs, 32x32 tiles: 2048, 64 9.1 / 9.2;
