@@ -227,9 +227,8 @@ int    pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream);
  *          and long work items).
  *          Batch 5..16 with at most 4096 input columns, from a quarter of
  *          them staged per work item on: the rows of x are copied into
- *          LDS and the fragments gathered from there (fastest when x is
- *          16-byte aligned, K a multiple of 8 and ldx == K; anything else
- *          gives the same results through an element-wise copy).
+ *          LDS and the fragments gathered from there, whatever their alignment
+ *          and stride.
  */
 int  pivot_fc_run(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx,
                   void* y_dev, int64_t ldy, int batch,

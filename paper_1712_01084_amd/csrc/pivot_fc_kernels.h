@@ -87,7 +87,7 @@ struct FcForm {
     __device__ __forceinline__ int slices() const { return (form >> 3) & 15; }
     __device__ __forceinline__ int batch() const { return (form >> 7) & 127; }
     __device__ __forceinline__ int out_pad() const { return (form >> 14) & 127; }
-    __device__ __forceinline__ int xn_missing() const { return (form >> 21) & 7; }
+    __device__ __forceinline__ int xn_missing() const { return (form >> 21) & 15; }
 };
 inline FcTail fc_tail(const FcArgs& a) {
     FcTail t{};
@@ -1002,9 +1002,10 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_P
 // the sixteen lanes that read the same column of different rows hit different
 // banks.  Index -1 (padding column) and the partner of a last, single tile
 // of the paired form point at the zeroed 16 bytes behind the row.
-// Needs 8 wavefronts (each copies two rows), at most 512 vectors per row and
-// 8192 staged columns per work item; q_misc bit 31: rows are whole 16-byte
-// vectors, 16-byte aligned and densely packed (else an element-wise copy).
+// Needs 8 wavefronts (each copies two rows), at most 512 vectors per row (513
+// where they are not aligned) and 8192 staged columns per work item; q_misc bit
+// 31: rows are whole 16-byte vectors, 16-byte aligned and densely packed (else
+// their address and length come from the rest of the arguments).
 // ---------------------------------------------------------------------------
 template <int KIND, int BH, int BW, int OUT>
 __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
@@ -1042,18 +1043,43 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     // to HBM (weights first: 0.6-0.9 us slower on 4096x4096 at every density; interleaved with them: 0.2-0.5 us
     // slower; twice the weights in flight: 0.6-1.0 us slower).  Wavefront w takes rows w and w + 8, lane l
     // vectors l, l + 64, ... of each.
-    f16x8 xv_[2][XV];
-    auto xload = [&](int k) {                           // k-th of the thread's 2 * XV vectors
-        const int r = k / XV, j = k % XV;
-        const int b = wave + r * NW;
-        const f16x8* src = reinterpret_cast<const f16x8*>(p_x) + (long long)(b0 + b) * q_xn_vecs;
-        const int i = lane + j * 64;
-        if (i < q_xn_vecs && b0 + b < q_batch) xv_[r][j] = load16<f16x8>(reinterpret_cast<const WT*>(src + i));
-    };
-    if (q_vec_rows) {
-        #pragma unroll
-        for (int k = 0; k < 2 * XV; ++k) xload(k);
+    // A row comes in whole aligned 16-byte pieces, from the one with its first element to the one with its last, so a row
+    // that is not aligned starts some elements late in its LDS copy and may have one piece more.
+    long long at[2];                                    // bytes from x to the rows this wavefront copies
+    int pieces[2], late = 0;                            // late: of the row this lane reads
+    #pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int b = b0 + wave + r * NW;
+        pieces[r] = b < q_batch ? q_xn_vecs : 0;
+        at[r] = (long long)b * q_xn_vecs * 16;
     }
+    f16x8 x_last = f16x8(0);
+    bool have_last = false;
+    if (!q_vec_rows) {
+        const int xlen = q_xn_vecs * 8 - FcForm(a).xn_missing();
+        const int x_late = (int)(reinterpret_cast<uintptr_t>(p_x) & 15) / 2;
+        auto row_of = [&](int b, int& l) {              // (past the last row: of that)
+            const long long first = (long long)(b0 + b < q_batch ? b0 + b : q_batch - 1) * a.ldx;
+            l = (int)((first + x_late) & 7);
+            return (first - l) * 2;
+        };
+        int l;
+        #pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            at[r] = row_of(wave + r * NW, l);
+            pieces[r] = pieces[r] > 0 ? (l + xlen + 7) / 8 : 0;
+        }
+        const long long mine = row_of(tid & (NBS - 1), l);
+        have_last = tid < NBS && b0 + tid < q_batch && (l + xlen + 7) / 8 > XV * 64;
+        if (have_last) x_last = load16<f16x8>(reinterpret_cast<const char*>(p_x) + mine + XV * 64 * 16);
+        (void)row_of(lane % MR < NBS ? lane % MR : 0, late);
+    }
+    f16x8 xv_[2][XV];
+    #pragma unroll
+    for (int r = 0; r < 2; ++r)
+        #pragma unroll
+        for (int j = 0; j < XV; ++j)
+            if (lane + j * 64 < pieces[r]) xv_[r][j] = load16<f16x8>(reinterpret_cast<const char*>(p_x) + at[r] + (lane + j * 64) * 16);
     const Chunk ck = load_chunk(q_uniform_ct, q_uniform_parts, p_chunks);
     const int br = ck.br, tile_begin = ck.tile_begin, ntiles = ck.ntiles, slot = ck.slot;
     const int first = ck.first, nparts = ck.nparts;
@@ -1096,26 +1122,15 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     __builtin_amdgcn_sched_barrier(0);                  // every load above is issued before anything below waits
 
     // x and the indices into LDS (they were requested first, so they arrive first)
-    if (q_vec_rows) {
+    #pragma unroll
+    for (int r = 0; r < 2; ++r) {
         #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int b = wave + r * NW;
-            #pragma unroll
-            for (int j = 0; j < XV; ++j) {
-                const int i = lane + j * 64;
-                if (i < q_xn_vecs && b0 + b < q_batch) *reinterpret_cast<f16x8*>(smem + b * row_bytes + i * 16) = xv_[r][j];
-            }
-        }
-    } else {
-        // rows that are not whole aligned vectors: element by element
-        const WT* x = reinterpret_cast<const WT*>(p_x);
-        const int xlen = q_xn_vecs * 8 - FcForm(a).xn_missing();
-        for (int b = wave; b < NBS; b += NW) {
-            if (b0 + b >= q_batch) continue;
-            for (int c = lane; c < xlen; c += 64)
-                *reinterpret_cast<WT*>(smem + b * row_bytes + c * 2) = x[(long long)(b0 + b) * a.ldx + c];
+        for (int j = 0; j < XV; ++j) {
+            const int i = lane + j * 64;
+            if (i < pieces[r]) *reinterpret_cast<f16x8*>(smem + (wave + r * NW) * row_bytes + i * 16) = xv_[r][j];
         }
     }
+    if (have_last) *reinterpret_cast<f16x8*>(smem + tid * row_bytes + XV * 64 * 16) = x_last;
     if (tid < NBS * 4) *reinterpret_cast<int*>(smem + (tid >> 2) * row_bytes + zero_off + (tid & 3) * 4) = 0;
     #pragma unroll
     for (int j = 0; j < IV; ++j) {
@@ -1133,7 +1148,7 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     acc_t acc[RB];
     #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb] = acc_t(0);
-    const char* xrow = smem + (li < NBS ? li : 0) * row_bytes;
+    const char* xrow = smem + (li < NBS ? li : 0) * row_bytes + late * 2;   // (its zero entry: still inside the zeroed 16 bytes)
     const int* xi_l = xi_lds + lg * 8;
     auto consume = [&](int u, int t) {
         #pragma unroll

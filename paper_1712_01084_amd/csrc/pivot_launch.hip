@@ -309,15 +309,15 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         const int xlen = L.x_block_order ? L.K_pad : L.K;
         int kind = mfma_kind(L.wdtype, L.bh, L.bw);
         if (kind == 1 && L.bw == 16 && bhs % 32 != 0) kind = 2;
-        const int vecs = (xlen + 7) / 8;
-        // rows copied with 16-byte loads when they are whole aligned vectors, densely packed; else element by element
+        // rows that are not whole aligned vectors, densely packed, start anywhere in their first piece of 16 bytes
         const bool vec_rows = xlen % 8 == 0 && L.ldx == xlen && (reinterpret_cast<uintptr_t>(L.x) & 15) == 0;
+        const int vecs = vec_rows ? xlen / 8 : (xlen + 7 + 7) / 8;
         a.xn_vecs = vecs | (vec_rows ? (1 << 17) : 0); a.xn_missing = vecs * 8 - xlen;
         const size_t steps_cols = ((size_t)(a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) + 1) * L.bw;
         size_t smem = (size_t)16 * (vecs * 16 + 16) + steps_cols * 4;
         const size_t red_bytes = (size_t)8 * bhs * 16 * 4;
         smem = align_up(smem > red_bytes ? smem : red_bytes, 16);
-        if (vecs > 512 || steps_cols > 8192 || smem > 158 * 1024) { set_error("internal: x does not fit the LDS copy (%zu bytes)", smem); return PIVOT_E_UNSUPPORTED; }
+        if (vecs > 513 || steps_cols > 8192 || smem > 158 * 1024) { set_error("internal: x does not fit the LDS copy (%zu bytes)", smem); return PIVOT_E_UNSUPPORTED; }
         if (describe) { *describe = kernel_name("fc_mfma_xrow_kernel<%d, %d, %d>", kind, bhs, L.bw); return PIVOT_OK; }
         return launch_mfma_xrow_f16(a, kind, bhs, L.bw, grid, smem, st);
     }
