@@ -225,7 +225,7 @@ int    pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream);
  *          recurrent loop, whose kernels produce that order, use it behind
  *          every boundary from batch 2 on (F32 at batch 2 to 8: but for few
  *          and long work items).
- *          Batch 5..16 with at most 4096 input columns, from a quarter of
+ *          Batch 5..16 (and 33..64, of few work items) with at most 4096 input columns, from a quarter of
  *          them staged per work item on: the rows of x are copied into
  *          LDS and the fragments gathered from there, whatever their alignment
  *          and stride.

@@ -989,7 +989,7 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_P
 }
 
 // ---------------------------------------------------------------------------
-// batch 5..16, fp16 weights: matrix cores with the B fragments gathered from a
+// batch 5..16 and 33..64, fp16 weights: matrix cores with the B fragments gathered from a
 // copy of x in LDS (Listing 1: the group fetch through P_col, done where the
 // fragment is formed).  Staging the x-segments of 16 batch rows element by
 // element costs a work item more than streaming its weights (16 rows x tiles x
@@ -998,15 +998,18 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_P
 // independent 16-byte loads, the item's gather indices are copied beside them
 // as byte offsets, and the lane that supplies B[k 8g..8g+7][column n] reads
 // its eight indices with two 16-byte LDS reads and its eight values with eight
-// 2-byte LDS reads from row n.  Rows are 16 bytes apart from a power of two, so
-// the sixteen lanes that read the same column of different rows hit different
-// banks.  Index -1 (padding column) and the partner of a last, single tile
+// 2-byte LDS reads from row n.  Rows are an odd number of 16-byte pieces apart
+// (xrow_bytes), so the sixteen lanes that read the same column of different rows
+// hit different banks (an even number: 1872x696, 32x16 tiles, 45 % kept, batch 41
+// 6.9 us, with an odd one 5.0; 1000x4090 16x32 50 %, batch 16 7.4 -> 6.5).  Index -1 (padding column) and the partner of a last, single tile
 // of the paired form point at the zeroed 16 bytes behind the row.
 // Needs 8 wavefronts (each copies two rows), at most 512 vectors per row (513
 // where they are not aligned) and 8192 staged columns per work item; q_misc bit
 // 31: rows are whole 16-byte vectors, 16-byte aligned and densely packed (else
 // their address and length come from the rest of the arguments).
 // ---------------------------------------------------------------------------
+// Bytes of a row of `vecs` pieces in LDS: the row, 16 zeroed bytes, and what makes it an odd number of pieces.
+__host__ __device__ constexpr int xrow_bytes(int vecs) { return ((vecs + 1) | 1) * 16; }
 template <int KIND, int BH, int BW, int OUT>
 __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
     using MF = Mfma<KIND>;
@@ -1030,7 +1033,7 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     const int q_uniform_parts = q_ct_parts >> 16, q_uniform_ct = q_uniform_parts > 0 ? (q_ct_parts & 0xFFFF) : 0;
     const int q_bh_full = q_misc & 0x7F, q_batch = (q_misc >> 7) & 0x7F, q_xn_vecs = (q_misc >> 14) & 0x1FFFF;
     const bool q_vec_rows = q_misc < 0;
-    const int row_bytes = q_xn_vecs * 16 + 16;          // a row of x and 16 zeroed bytes
+    const int row_bytes = xrow_bytes(q_xn_vecs);
     const int zero_off = q_xn_vecs * 16;
     int* xi_lds = reinterpret_cast<int*>(smem + NBS * row_bytes);
     float* red = reinterpret_cast<float*>(smem);        // reused after the stream phase: NW * N floats

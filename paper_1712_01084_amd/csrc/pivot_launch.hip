@@ -61,13 +61,21 @@ static bool block_order_vector(const FcShape& s, int batch) {
     return items >= 500 && (s.bh == 8 || (batch == 2 && cols >= 400));
 }
 
+// Row slices <= want of whole MFMA row blocks: 16 rows (tiles 16 columns wide are then taken in pairs) or 32.
+static int mfma_slices(const FcShape& s, int want) {
+    const int mr = (mfma_kind(s.wdtype, s.bh, s.bw) == 0 || s.bw == 16) ? 16 : 32;
+    int sl = want < 1 ? 1 : want;
+    while (sl > 1 && (s.bh % sl != 0 || (s.bh / sl) % mr != 0)) sl /= 2;
+    return sl;
+}
+
 // Which kernel applies the layer:
 //   kPathVector    batch 1-2 (and whatever the others do not take): FMA / dot2 against x staged in LDS, launch rows of
 //                  at most 4 batch rows
 //   kPathFrag      both types, every tile shape: MFMA with the B fragments read from an x in fragment order, the
 //                  weights streamed once for up to 64 batch rows; a natural-order x is copied by a launch of its own
 //   kPathMfmaLds   fp16, batch >= 3: MFMA with the B fragments read from x staged in LDS (4 or 8 batch rows per launch row)
-//   kPathMfmaXrow  fp16, batch 5-16: MFMA with the B fragments gathered from a copy of the rows of x in LDS
+//   kPathMfmaXrow  fp16, batch 5-16 and 33-64: MFMA with the B fragments gathered from a copy of the rows of x in LDS
 // An x that the layer or cell before produced (kXBlock) arrives in the order the kernel wants, so from batch 2 on the
 // fragment form has nothing to pay for and streams the weights once (three fp16 layers of 25088-4096-4096-1000
 // at 10 % kept, batch 32: 23.1 us with the LDS-fed form behind the boundaries, 17.9 with this one).  (fp32 layers of up to
@@ -107,29 +115,44 @@ int fc_path(const FcShape& s, int batch) {
         return frag && batch >= 3 && (launch_rows > 1 ? (launch_rows - 1) * weight_mb >= 12.0 : weight_mb >= 14.0) ? kPathFrag : kPathVector;
     }
     if (batch < 3) return kPathVector;
-    if (batch >= 5 && batch <= 16 && s.xrow_len > 0 && s.chunk_tiles > 0) {
-        // 16 rows of x (each with 16 zeroed bytes behind it) and the work item's gather indices in LDS; a lane
-        // copies at most 8 vectors of a row, a thread at most 4 int4 of indices
-        const size_t vecs = ((size_t)s.xrow_len + 7) / 8;
-        const size_t cols = ((size_t)s.chunk_tiles + 1) * bw;
-        const size_t lds = 16 * (vecs * 16 + 16) + cols * 4;
-        // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few
-        // long block rows among many short ones most work items copy all of x for a handful of tiles, which the
-        // 8-row LDS-fed form does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and
-        // wins at batch 5-8; batch 9-16 keeps the rule it was measured with).
-        const size_t rule_cols = batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols;
-        if (vecs <= 512 && cols <= 8192 && lds <= 156 * 1024 && rule_cols * 4 >= (size_t)s.xrow_len) return kPathMfmaXrow;
-    }
+    bool lds = false;
+    size_t launch_rows = 0;
     if (lds_tiles > 0) {
         const int rows = mfma_lds_rows(batch);
         const size_t xs_bytes = (size_t)rows * ((size_t)lds_tiles * bw + 8 + 16) * 2;   // + the paired form's zeroed columns
         // every launch row of 8 batch rows streams the weights again and gathers its own rows: beyond two launch
         // rows the form is kept while the launch rows together stage at most 5120 columns per work item
         // (4096x4096, 64x16 tiles, against the fragment form: batch 24 at 5 % kept 6.2 -> 5.1 us, batch 64 8.7 -> 7.8)
-        const size_t launch_rows = (size_t)(batch + rows - 1) / rows;
+        launch_rows = (size_t)(batch + rows - 1) / rows;
         const bool restage = frag && (double)(launch_rows - 1) * s.nchunks * s.mean_tiles * bw >= 100e3;
-        if (!restage && xs_bytes <= 48 * 1024 && (launch_rows <= 2 || launch_rows * lds_tiles * bw <= 5120)) return kPathMfmaLds;
+        lds = !restage && xs_bytes <= 48 * 1024 && (launch_rows <= 2 || launch_rows * lds_tiles * bw <= 5120);
     }
+    if (batch >= 5 && (batch <= 16 || batch > 32) && s.xrow_len > 0 && s.chunk_tiles > 0) {
+        // 16 rows of x (each with 16 zeroed bytes behind it) and the work item's gather indices in LDS; a lane
+        // copies at most 8 vectors of a row, a thread at most 4 int4 of indices
+        const size_t vecs = ((size_t)s.xrow_len + 7) / 8;
+        const size_t cols = ((size_t)s.chunk_tiles + 1) * bw;
+        const size_t copy_bytes = (size_t)16 * xrow_bytes((int)vecs) + cols * 4;
+        // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few
+        // long block rows among many short ones most work items copy all of x for a handful of tiles, which the
+        // 8-row LDS-fed form does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and
+        // wins at batch 5-8; batch 9-16 keeps the rule it was measured with).
+        const size_t rule_cols = batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols;
+        // Beyond batch 32 three or four launch rows of it are ahead of the fragment form and its copy of x while every
+        // work item of them has a compute unit to itself and stages at most 2048 columns (us, 16x32 tiles, batch 64,
+        // fragment form / this one: 1000x4090 25 % kept 7.5 / 7.1, 1000x2000 25 % 5.6 / 4.7, 1000x4096 10 % 6.0 / 5.1 and
+        // 50 % (2048 columns) 8.6 / 8.4, 300x4000 64x64 50 % 8.3 / 6.8, 500x1000 32x32 dense 5.3 / 5.0; with more work
+        // items, 2000x1000 10 % 6.0 / 6.9 and 2000x4090 32x32 25 % 9.7 / 12.3; with longer ones, 129x3594 rows by a Zipf
+        // law 6.8 / 8.0); at batch 17-32 it is not (250x4090 25 % 4.9 / 5.7, 1000x2000 4.3 / 4.4).  The LDS-fed form is
+        // left alone while its five to eight launch rows are resident at once too (605x891 46 %, 38 block rows: batch
+        // 48 3.9 / 4.5, batch 64 5.3 / 4.5) or stage little (1066x349 14 %, 67 block rows, batch 41: 3.8 / 4.2).
+        const bool pays = batch <= 16 ? rule_cols * 4 >= (size_t)s.xrow_len
+                                      : cols <= 2048 + (size_t)bw && (long long)s.nchunks * mfma_slices(s, s.row_slices) * ((batch + 15) / 16) <= 256 &&
+                                            !(lds && (launch_rows * lds_tiles * bw <= 1536 ||
+                                                      (long long)s.nchunks * mfma_slices(s, s.row_slices < 2 ? 1 : 2) * (long long)launch_rows <= 256));
+        if (vecs <= 512 && cols <= 8192 && copy_bytes <= 156 * 1024 && pays) return kPathMfmaXrow;
+    }
+    if (lds) return kPathMfmaLds;
     return frag && batch >= 8 ? kPathFrag : kPathVector;
 }
 
@@ -194,22 +217,11 @@ int fc_row_slices(const FcShape& s, int batch, int want) {
     // us; 25 % kept, batch 24 / 32: 10.8 -> 9.3, 12.7 -> 10.2; one slice: 6.6 at batch 16; up to batch 8 four
     // slices are the faster, 4.9 against 5.3 us).
     if (sl > 2 && batch > 8 && fc_path(s, batch) == kPathMfmaLds) sl = 2;
+    if (fc_path(s, batch) != kPathVector) return mfma_slices(s, sl);
+    const int vec = 16 / elem_size(wdtype), rpw = 64 / (bw / vec > 0 ? bw / vec : 1);
     while (sl > 1) {
-        bool ok = (bh % sl == 0);
         const int bhs = bh / sl;
-        if (ok) {
-            const int path = fc_path(s, batch);
-            if (path != kPathVector) {
-                // whole MFMA row blocks: 16 rows (tiles 16 columns wide are then taken in pairs)
-                const int mr = (mfma_kind(wdtype, bh, bw) == 0 || bw == 16) ? 16 : 32;
-                ok = (bhs % mr == 0);
-            } else {
-                const int vec = 16 / elem_size(wdtype);
-                const int rpw = 64 / (bw / vec > 0 ? bw / vec : 1);
-                ok = bhs >= 8 && (bhs % rpw == 0 || rpw % bhs == 0);
-            }
-        }
-        if (ok) break;
+        if (bh % sl == 0 && bhs >= 8 && (bhs % rpw == 0 || rpw % bhs == 0)) break;
         sl /= 2;
     }
     return sl;
@@ -260,7 +272,7 @@ static std::string kernel_name(const char* fmt, A... args) {
 }
 
 int launch_fc(const FcLaunch& L, std::string* describe) {
-    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from};
+    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from, L.row_slices};
     const int path = fc_path(shape, L.batch);
     const bool ml = path == kPathMfmaLds, mx = path == kPathMfmaXrow;
     const int nbt = fc_batch_tile(shape, L.batch);
@@ -314,7 +326,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         const int vecs = vec_rows ? xlen / 8 : (xlen + 7 + 7) / 8;
         a.xn_vecs = vecs | (vec_rows ? (1 << 17) : 0); a.xn_missing = vecs * 8 - xlen;
         const size_t steps_cols = ((size_t)(a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) + 1) * L.bw;
-        size_t smem = (size_t)16 * (vecs * 16 + 16) + steps_cols * 4;
+        size_t smem = (size_t)16 * xrow_bytes(vecs) + steps_cols * 4;
         const size_t red_bytes = (size_t)8 * bhs * 16 * 4;
         smem = align_up(smem > red_bytes ? smem : red_bytes, 16);
         if (vecs > 513 || steps_cols > 8192 || smem > 158 * 1024) { set_error("internal: x does not fit the LDS copy (%zu bytes)", smem); return PIVOT_E_UNSUPPORTED; }

@@ -1,4 +1,4 @@
-// Matrix-core layer kernel whose B fragments are gathered from a copy of x in LDS (fp16 weights, batch 5..16):
+// Matrix-core layer kernel whose B fragments are gathered from a copy of x in LDS (fp16 weights, batch 5..16 and 33..64):
 // instantiations and dispatch.
 #include "pivot_fc_kernels.h"
 

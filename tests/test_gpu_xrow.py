@@ -14,9 +14,10 @@ import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K,bh,bw,batch", [(100, 4096, 16, 32, 16), (70, 4095, 64, 16, 5), (64, 4089, 32, 16, 13), (33, 1, 16, 64, 7), (40, 9, 16, 32, 16)])
+@pytest.mark.parametrize("M,K,bh,bw,batch", [(100, 4096, 16, 32, 16), (70, 4095, 64, 16, 5), (64, 4089, 32, 16, 13), (33, 1, 16, 64, 7), (40, 9, 16, 32, 16),
+                                               (1000, 4090, 16, 32, 64), (200, 4095, 64, 16, 33), (300, 4000, 64, 64, 47)])   # several launch rows, the last one short
 def test_rows_of_any_alignment(M, K, bh, bw, batch):
-    p = WL.gen_fc(M, K, bh, bw, 0.6, seed=5, wdtype=WL.F16, batch=batch, act=WL.ACT_NONE)
+    p = WL.gen_fc(M, K, bh, bw, 0.6 if batch <= 16 else 0.35, seed=5, wdtype=WL.F16, batch=batch, act=WL.ACT_NONE)
     y_ref, D = O.oracle_fc(p.Wp, p.tile_mask, p.prow, p.pcol, p.bias, p.x, bh, bw, p.act, return_scale=True)
     plan = G.dev_plan(p)
     try:
