@@ -55,7 +55,6 @@ struct FcArgs {
     int T;                      // kept tiles in the whole plan (the CBR layout strides by it)
     int chunk_tiles;            // the plan's chunk size (vector kernel: fixes the LDS row stride)
     int xn_vecs;                // x-resident forms: 16-byte vectors per row of x
-    int xn_missing;             //   elements the last of them has too many
     long long* trace;           // timeline builds only (PIVOT_TRACE): eight time stamps per wavefront, else unused
 };
 
@@ -63,7 +62,7 @@ struct FcArgs {
 // within 112 bytes, and no kernel asks for its grid size (which would come as 256 bytes of hidden arguments): the host
 // writes a launch's arguments to device memory and waits for the last of them to arrive, up to 112 bytes in 2.3-2.7 us a
 // launch, beyond in 2.4-3.5 (0.07-0.7 us more, depending on the host; 500 bytes the same).
-// form: kOutF16 | kOutFrag | ReLU << 2 | row slices << 3 | batch << 7 | padding columns of y << 14 | xn_missing << 21.
+// form: kOutF16 | kOutFrag | ReLU << 2 | row slices << 3 | batch << 7 | padding columns of y << 14.
 // (Packed: with four bytes of padding behind `form` the compiler loads sixteen bytes, finds the last register unused and
 // waits at the start of the kernel before it gives it to something else.)
 struct __attribute__((packed, aligned(4))) FcTail {
@@ -87,12 +86,11 @@ struct FcForm {
     __device__ __forceinline__ int slices() const { return (form >> 3) & 15; }
     __device__ __forceinline__ int batch() const { return (form >> 7) & 127; }
     __device__ __forceinline__ int out_pad() const { return (form >> 14) & 127; }
-    __device__ __forceinline__ int xn_missing() const { return (form >> 21) & 15; }
 };
 inline FcTail fc_tail(const FcArgs& a) {
     FcTail t{};
     t.y = a.y; t.partials = a.partials; t.tickets = a.tickets; t.ldx = a.ldx; t.ldy = a.ldy; t.nchunks = a.nchunks; t.nbr = a.nbr;
-    t.form = (uint32_t)a.out_form | (uint32_t)a.act << 2 | (uint32_t)a.slices << 3 | (uint32_t)a.batch << 7 | (uint32_t)a.out_pad << 14 | (uint32_t)a.xn_missing << 21;
+    t.form = (uint32_t)a.out_form | (uint32_t)a.act << 2 | (uint32_t)a.slices << 3 | (uint32_t)a.batch << 7 | (uint32_t)a.out_pad << 14;
 #ifdef PIVOT_TRACE
     t.trace = a.trace;
 #endif
@@ -989,7 +987,7 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_P
 }
 
 // ---------------------------------------------------------------------------
-// batch 5..16 and 33..64, fp16 weights: matrix cores with the B fragments gathered from a
+// batch 5..64, fp16 weights: matrix cores with the B fragments gathered from a
 // copy of x in LDS (Listing 1: the group fetch through P_col, done where the
 // fragment is formed).  Staging the x-segments of 16 batch rows element by
 // element costs a work item more than streaming its weights (16 rows x tiles x
@@ -1003,14 +1001,20 @@ __global__ void __launch_bounds__(NW * 64) fc_mfma_lds_chain_kernel(PIVOT_GEMV_P
 // hit different banks (an even number: 1872x696, 32x16 tiles, 45 % kept, batch 41
 // 6.9 us, with an odd one 5.0; 1000x4090 16x32 50 %, batch 16 7.4 -> 6.5).  Index -1 (padding column) and the partner of a last, single tile
 // of the paired form point at the zeroed 16 bytes behind the row.
-// Needs 8 wavefronts (each copies two rows), at most 512 vectors per row (513
-// where they are not aligned) and 8192 staged columns per work item; q_misc bit
-// 31: rows are whole 16-byte vectors, 16-byte aligned and densely packed (else
-// their address and length come from the rest of the arguments).
+// Needs 8 wavefronts (each copies two rows), at most 64 * XV vectors per row (one
+// more where they are not aligned) and 8192 staged columns per work item.  q_misc
+// holds bh_full and batch as elsewhere, vectors per row << 14, elements the last
+// of them has too many << 24, rows densely packed << 30, and in bit 31: rows are
+// whole 16-byte vectors, 16-byte aligned and densely packed.
 // ---------------------------------------------------------------------------
 // Bytes of a row of `vecs` pieces in LDS: the row, 16 zeroed bytes, and what makes it an odd number of pieces.
 __host__ __device__ constexpr int xrow_bytes(int vecs) { return ((vecs + 1) | 1) * 16; }
-template <int KIND, int BH, int BW, int OUT>
+// xn_vecs of a launch, and what the row's pieces need but for one of rows that are not aligned, which has a load of its own.
+inline int xrow_pack(int vecs, int missing, bool packed, bool vec_rows) { return vecs | missing << 10 | (packed ? 1 << 16 : 0) | (vec_rows ? 1 << 17 : 0); }
+inline int xrow_xv(int xn_vecs) { return (xn_vecs & 0x3FF) - ((xn_vecs >> 17) & 1 ? 0 : 1) <= 256 ? 4 : 8; }
+// XV: vectors of one row a lane copies (2 rows per wavefront): with 4 (rows of at most 2048 elements) two workgroups fit the
+// registers of a compute unit, with 8 one does.
+template <int KIND, int BH, int BW, int XV, int OUT>
 __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
     using MF = Mfma<KIND>;
     using acc_t = typename MF::acc_t;
@@ -1024,15 +1028,14 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     constexpr int U  = (LT >= 8) ? 1 : 8 / LT;          // tiles (pairs) in flight per wave (16 KB: slower throughout)
     constexpr int N  = BH * NBS;
     constexpr int STEP = PAIR ? 2 * BW : BW;            // staged columns per MFMA step along the block row
-    constexpr int XV = 8;                               // vectors of one row a lane copies (2 rows per wavefront)
     constexpr int IV = 4;                               // int4 of gather indices a thread copies
     static_assert(BH % MR == 0 && (PAIR ? BW * 2 == MK : BW % MK == 0), "tile shape does not fit this MFMA");
 
     extern __shared__ __align__(16) char smem[];
     __shared__ int s_flag;
     const int q_uniform_parts = q_ct_parts >> 16, q_uniform_ct = q_uniform_parts > 0 ? (q_ct_parts & 0xFFFF) : 0;
-    const int q_bh_full = q_misc & 0x7F, q_batch = (q_misc >> 7) & 0x7F, q_xn_vecs = (q_misc >> 14) & 0x1FFFF;
-    const bool q_vec_rows = q_misc < 0;
+    const int q_bh_full = q_misc & 0x7F, q_batch = (q_misc >> 7) & 0x7F, q_xn_vecs = (q_misc >> 14) & 0x3FF;
+    const bool q_vec_rows = q_misc < 0, q_packed = (q_misc >> 30) & 1;
     const int row_bytes = xrow_bytes(q_xn_vecs);
     const int zero_off = q_xn_vecs * 16;
     int* xi_lds = reinterpret_cast<int*>(smem + NBS * row_bytes);
@@ -1059,10 +1062,12 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     f16x8 x_last = f16x8(0);
     bool have_last = false;
     if (!q_vec_rows) {
-        const int xlen = q_xn_vecs * 8 - FcForm(a).xn_missing();
+        const int xlen = q_xn_vecs * 8 - ((q_misc >> 24) & 15);
+        long long ldx = xlen;
+        if (!q_packed) { ldx = a.ldx; asm volatile("" : "+s"(ldx)); }    // (a branch: else every launch waits for the argument block here)
         const int x_late = (int)(reinterpret_cast<uintptr_t>(p_x) & 15) / 2;
         auto row_of = [&](int b, int& l) {              // (past the last row: of that)
-            const long long first = (long long)(b0 + b < q_batch ? b0 + b : q_batch - 1) * a.ldx;
+            const long long first = (long long)(b0 + b < q_batch ? b0 + b : q_batch - 1) * ldx;
             l = (int)((first + x_late) & 7);
             return (first - l) * 2;
         };
@@ -1192,13 +1197,13 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
     finish_rows<BH, NBS, NT, OUT>(a, red, NW, br, slot, first, nparts, rp, b0, tid, &s_flag);
 }
 
-template <int KIND, int BH, int BW>
+template <int KIND, int BH, int BW, int XV>
 __global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
-    fc_mfma_xrow_body<KIND, BH, BW, kRows>(PIVOT_GEMV_PASS, a);
+    fc_mfma_xrow_body<KIND, BH, BW, XV, kRows>(PIVOT_GEMV_PASS, a);
 }
-template <int KIND, int BH, int BW>
+template <int KIND, int BH, int BW, int XV>
 __global__ void __launch_bounds__(512) fc_mfma_xrow_chain_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
-    fc_mfma_xrow_body<KIND, BH, BW, kFragOrder>(PIVOT_GEMV_PASS, a);
+    fc_mfma_xrow_body<KIND, BH, BW, XV, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
 }  // namespace pivot

@@ -75,7 +75,7 @@ static int mfma_slices(const FcShape& s, int want) {
 //   kPathFrag      both types, every tile shape: MFMA with the B fragments read from an x in fragment order, the
 //                  weights streamed once for up to 64 batch rows; a natural-order x is copied by a launch of its own
 //   kPathMfmaLds   fp16, batch >= 3: MFMA with the B fragments read from x staged in LDS (4 or 8 batch rows per launch row)
-//   kPathMfmaXrow  fp16, batch 5-16 and 33-64: MFMA with the B fragments gathered from a copy of the rows of x in LDS
+//   kPathMfmaXrow  fp16, batch 5 on, rows of at most 4096 columns: MFMA with the B fragments gathered from a copy of the rows of x in LDS
 // An x that the layer or cell before produced (kXBlock) arrives in the order the kernel wants, so from batch 2 on the
 // fragment form has nothing to pay for and streams the weights once (three fp16 layers of 25088-4096-4096-1000
 // at 10 % kept, batch 32: 23.1 us with the LDS-fed form behind the boundaries, 17.9 with this one).  (fp32 layers of up to
@@ -127,29 +127,43 @@ int fc_path(const FcShape& s, int batch) {
         const bool restage = frag && (double)(launch_rows - 1) * s.nchunks * s.mean_tiles * bw >= 100e3;
         lds = !restage && xs_bytes <= 48 * 1024 && (launch_rows <= 2 || launch_rows * lds_tiles * bw <= 5120);
     }
-    if (batch >= 5 && (batch <= 16 || batch > 32) && s.xrow_len > 0 && s.chunk_tiles > 0) {
+    if (batch >= 5 && s.xrow_len > 0 && s.chunk_tiles > 0) {
         // 16 rows of x (each with 16 zeroed bytes behind it) and the work item's gather indices in LDS; a lane
         // copies at most 8 vectors of a row, a thread at most 4 int4 of indices
         const size_t vecs = ((size_t)s.xrow_len + 7) / 8;
         const size_t cols = ((size_t)s.chunk_tiles + 1) * bw;
         const size_t copy_bytes = (size_t)16 * xrow_bytes((int)vecs) + cols * 4;
-        // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few
-        // long block rows among many short ones most work items copy all of x for a handful of tiles, which the
-        // 8-row LDS-fed form does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and
-        // wins at batch 5-8; batch 9-16 keeps the rule it was measured with).
-        const size_t rule_cols = batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols;
-        // Beyond batch 32 three or four launch rows of it are ahead of the fragment form and its copy of x while every
-        // work item of them has a compute unit to itself and stages at most 2048 columns (us, 16x32 tiles, batch 64,
-        // fragment form / this one: 1000x4090 25 % kept 7.5 / 7.1, 1000x2000 25 % 5.6 / 4.7, 1000x4096 10 % 6.0 / 5.1 and
-        // 50 % (2048 columns) 8.6 / 8.4, 300x4000 64x64 50 % 8.3 / 6.8, 500x1000 32x32 dense 5.3 / 5.0; with more work
-        // items, 2000x1000 10 % 6.0 / 6.9 and 2000x4090 32x32 25 % 9.7 / 12.3; with longer ones, 129x3594 rows by a Zipf
-        // law 6.8 / 8.0); at batch 17-32 it is not (250x4090 25 % 4.9 / 5.7, 1000x2000 4.3 / 4.4).  The LDS-fed form is
-        // left alone while its five to eight launch rows are resident at once too (605x891 46 %, 38 block rows: batch
-        // 48 3.9 / 4.5, batch 64 5.3 / 4.5) or stage little (1066x349 14 %, 67 block rows, batch 41: 3.8 / 4.2).
-        const bool pays = batch <= 16 ? rule_cols * 4 >= (size_t)s.xrow_len
-                                      : cols <= 2048 + (size_t)bw && (long long)s.nchunks * mfma_slices(s, s.row_slices) * ((batch + 15) / 16) <= 256 &&
-                                            !(lds && (launch_rows * lds_tiles * bw <= 1536 ||
-                                                      (long long)s.nchunks * mfma_slices(s, s.row_slices < 2 ? 1 : 2) * (long long)launch_rows <= 256));
+        const long long items = (long long)s.nchunks * mfma_slices(s, s.row_slices) * ((batch + 15) / 16);
+        const long long lds_items = lds ? (long long)s.nchunks * mfma_slices(s, batch <= 8 ? s.row_slices : (s.row_slices < 2 ? 1 : 2)) * (long long)launch_rows : 0;
+        const size_t lds_cols = launch_rows * (size_t)lds_tiles * bw;
+        bool pays;
+        if (s.xrow_len <= 2048) {
+            // Rows of at most 2048 columns, of which a compute unit holds two work items: up to batch 16 always (us, the
+            // rule for longer rows / this one, batch 8: 2000x1000 16x32 10 % 4.1 / 3.7, 4096x2048 32x32 10 % 4.2 / 3.9,
+            // 600x600 32x32 40 % 4.0 / 3.7), beyond while all work items are resident at once (batch 32: 2000x1000 4.8 /
+            // 4.1, 300x1800 16x64 50 % 5.6 / 4.6; batch 64: 2000x696 32x32 45 % 6.5 / 5.4; but 8000x1000 32x32 20 %,
+            // 1000 of them, batch 32 7.5 / 9.1).  Rows that are not whole 16-byte vectors cost it 0.3 us and the LDS-fed
+            // form, which gathers them from memory, nothing: where that takes them, of few and short work items, it is left
+            // alone (LDS-fed / this one: 605x891 16x32 46 % batch 8 3.65 / 3.9 and 48 3.9 / 4.25, 1000x1514 30 % batch 8
+            // 3.9 / 4.0, 231x1913 64x16 23 % batch 11 3.6 / 4.55, 1129x681 64x16 41 % batch 60 4.6 / 4.9).
+            const bool other = lds && (s.K % 8 != 0 ? (batch <= 16 ? lds_items >= 12 && lds_items <= 256 : lds_items <= 256 || lds_cols <= 3072)
+                                                    : batch > 16 && lds_cols <= 512);    // (222x128 32x64 24 %, batch 45: 3.8 / 4.0)
+            pays = !other && (batch <= 16 || (cols <= 2048 + (size_t)bw && items < 512));
+        } else if (batch <= 16) {
+            // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few
+            // long block rows among many short ones most work items copy all of x for a handful of tiles, which the
+            // 8-row LDS-fed form does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and
+            // wins at batch 5-8; batch 9-16 keeps the rule it was measured with).
+            pays = (batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols) * 4 >= (size_t)s.xrow_len;
+        } else {
+            // Longer rows, beyond batch 32: three or four launch rows of it are ahead of the fragment form and its copy of x
+            // while every work item of them has a compute unit to itself and stages at most 2048 columns (us, 16x32
+            // tiles, batch 64, fragment form / this one: 1000x4090 25 % kept 7.5 / 7.0, 1000x4096 10 % 6.0 / 5.1 and 50 %
+            // (2048 columns) 8.6 / 8.4, 300x4000 64x64 50 % 8.3 / 6.8; with more work items, 2000x4090 32x32 25 % 9.7 /
+            // 12.3; with longer ones, 129x3594 rows by a Zipf law 6.8 / 8.0); at batch 17-32 it is not (250x4090 25 % 4.9 /
+            // 5.3).  The LDS-fed form is left alone where it is resident at once too or stages little.
+            pays = batch > 32 && cols <= 2048 + (size_t)bw && items <= 256 && !(lds && (lds_cols <= 1536 || lds_items <= 256));
+        }
         if (vecs <= 512 && cols <= 8192 && copy_bytes <= 156 * 1024 && pays) return kPathMfmaXrow;
     }
     if (lds) return kPathMfmaLds;
@@ -272,7 +286,7 @@ static std::string kernel_name(const char* fmt, A... args) {
 }
 
 int launch_fc(const FcLaunch& L, std::string* describe) {
-    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from, L.row_slices};
+    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from, L.row_slices, L.K};
     const int path = fc_path(shape, L.batch);
     const bool ml = path == kPathMfmaLds, mx = path == kPathMfmaXrow;
     const int nbt = fc_batch_tile(shape, L.batch);
@@ -293,7 +307,7 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     a.ldx = L.ldx; a.ldy = L.ldy; a.batch = L.batch; a.act = L.act;
     a.nchunks = L.nchunks; a.nbr = L.nbr;
     a.out_form = (L.out_f16 ? kOutF16 : 0) | (L.out_frag ? kOutFrag : 0); a.out_pad = L.out_frag ? L.out_pad : 0;
-    a.slices = sl; a.bh_full = L.bh; a.xn_vecs = a.xn_missing = 0;
+    a.slices = sl; a.bh_full = L.bh; a.xn_vecs = 0;
     a.uniform_ct = L.uniform_ct; a.uniform_parts = L.uniform_parts;
     a.T = L.T; a.chunk_tiles = L.chunk_tiles;
     a.trace = nullptr;
@@ -324,13 +338,13 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
         // rows that are not whole aligned vectors, densely packed, start anywhere in their first piece of 16 bytes
         const bool vec_rows = xlen % 8 == 0 && L.ldx == xlen && (reinterpret_cast<uintptr_t>(L.x) & 15) == 0;
         const int vecs = vec_rows ? xlen / 8 : (xlen + 7 + 7) / 8;
-        a.xn_vecs = vecs | (vec_rows ? (1 << 17) : 0); a.xn_missing = vecs * 8 - xlen;
+        a.xn_vecs = xrow_pack(vecs, vecs * 8 - xlen, L.ldx == xlen, vec_rows);
         const size_t steps_cols = ((size_t)(a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) + 1) * L.bw;
         size_t smem = (size_t)16 * xrow_bytes(vecs) + steps_cols * 4;
         const size_t red_bytes = (size_t)8 * bhs * 16 * 4;
         smem = align_up(smem > red_bytes ? smem : red_bytes, 16);
         if (vecs > 513 || steps_cols > 8192 || smem > 158 * 1024) { set_error("internal: x does not fit the LDS copy (%zu bytes)", smem); return PIVOT_E_UNSUPPORTED; }
-        if (describe) { *describe = kernel_name("fc_mfma_xrow_kernel<%d, %d, %d>", kind, bhs, L.bw); return PIVOT_OK; }
+        if (describe) { *describe = kernel_name("fc_mfma_xrow_kernel<%d, %d, %d, %d>", kind, bhs, L.bw, xrow_xv(a.xn_vecs)); return PIVOT_OK; }
         return launch_mfma_xrow_f16(a, kind, bhs, L.bw, grid, smem, st);
     }
     // staged x: nbt rows of (tiles per chunk)*bw elements, plus 16 bytes whose last element is the dump slot

@@ -1,14 +1,14 @@
-// Matrix-core layer kernel whose B fragments are gathered from a copy of x in LDS (fp16 weights, batch 5..16 and 33..64):
+// Matrix-core layer kernel whose B fragments are gathered from a copy of x in LDS (fp16 weights, batch 5..64):
 // instantiations and dispatch.
 #include "pivot_fc_kernels.h"
 
 namespace pivot {
 
-template <int KIND, int BH, int BW, bool CHAIN>
+template <int KIND, int BH, int BW, int XV, bool CHAIN>
 static int launch_c(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
     // more than 64 KB of dynamic LDS per workgroup has to be allowed per kernel and device
     static size_t allowed[16] = {};
-    const auto kernel = CHAIN ? fc_mfma_xrow_chain_kernel<KIND, BH, BW> : fc_mfma_xrow_kernel<KIND, BH, BW>;
+    const auto kernel = CHAIN ? fc_mfma_xrow_chain_kernel<KIND, BH, BW, XV> : fc_mfma_xrow_kernel<KIND, BH, BW, XV>;
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
     size_t& have = allowed[dev & 15];
@@ -24,7 +24,9 @@ static int launch_c(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
 
 template <int KIND, int BH, int BW>
 static int launch_t(const FcArgs& a, dim3 grid, size_t smem, hipStream_t st) {
-    return (a.out_form & kOutFrag) ? launch_c<KIND, BH, BW, true>(a, grid, smem, st) : launch_c<KIND, BH, BW, false>(a, grid, smem, st);
+    const bool short_rows = xrow_xv(a.xn_vecs) == 4;
+    if (a.out_form & kOutFrag) return short_rows ? launch_c<KIND, BH, BW, 4, true>(a, grid, smem, st) : launch_c<KIND, BH, BW, 8, true>(a, grid, smem, st);
+    return short_rows ? launch_c<KIND, BH, BW, 4, false>(a, grid, smem, st) : launch_c<KIND, BH, BW, 8, false>(a, grid, smem, st);
 }
 
 int launch_mfma_xrow_f16(const FcArgs& a, int kind, int bhs, int bw, dim3 grid, size_t smem, hipStream_t st) {

@@ -14,10 +14,10 @@ import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K,bh,bw,batch", [(100, 4096, 16, 32, 16), (70, 4095, 64, 16, 5), (64, 4089, 32, 16, 13), (33, 1, 16, 64, 7), (40, 9, 16, 32, 16),
+@pytest.mark.parametrize("M,K,bh,bw,batch", [(100, 4096, 16, 32, 16), (90, 2048, 16, 32, 16), (60, 2047, 32, 32, 16), (70, 2056, 64, 64, 9), (500, 600, 32, 16, 29), (70, 4095, 64, 16, 5), (64, 4089, 32, 16, 13), (2100, 33, 16, 64, 13), (4200, 9, 16, 32, 7),
                                                (1000, 4090, 16, 32, 64), (200, 4095, 64, 16, 33), (300, 4000, 64, 64, 47)])   # several launch rows, the last one short
 def test_rows_of_any_alignment(M, K, bh, bw, batch):
-    p = WL.gen_fc(M, K, bh, bw, 0.6 if batch <= 16 else 0.35, seed=5, wdtype=WL.F16, batch=batch, act=WL.ACT_NONE)
+    p = WL.gen_fc(M, K, bh, bw, 0.6 if batch <= 16 else 0.3, seed=5, wdtype=WL.F16, batch=batch, act=WL.ACT_NONE)
     y_ref, D = O.oracle_fc(p.Wp, p.tile_mask, p.prow, p.pcol, p.bias, p.x, bh, bw, p.act, return_scale=True)
     plan = G.dev_plan(p)
     try:
@@ -35,3 +35,15 @@ def test_rows_of_any_alignment(M, K, bh, bw, batch):
                 assert O.max_scaled_error(y.cpu().numpy(), y_ref, D) <= G.TOL[p.wdtype], (ldx, off)
     finally:
         B.pivot_fc_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("M,K,bh,bw,frac,batch", [(300, 3000, 16, 32, 0.1, 8), (300, 3001, 64, 16, 0.08, 12), (400, 891, 16, 32, 0.4, 16), (200, 2100, 32, 64, 0.1, 33)])
+def test_layers_that_stay_with_the_other_lds_form(M, K, bh, bw, frac, batch):
+    # long rows of which little is staged, and short rows that are no whole vectors
+    p = WL.gen_fc(M, K, bh, bw, frac, seed=8, wdtype=WL.F16, batch=batch, act=WL.ACT_RELU)
+    plan = G.dev_plan(p)
+    try:
+        assert "fc_mfma_lds_kernel" in B.pivot_fc_kernel_name(plan, batch)
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+    G.check_fc(p)
