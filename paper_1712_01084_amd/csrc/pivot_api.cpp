@@ -335,6 +335,15 @@ int pivot_mlp_plan(pivot_fc_plan_t* const* layers, int Lcount, int flags, pivot_
             total += align_up(chain_persist_ctl_bytes(), 256);
             for (int l = 0; l + 1 < Lcount; ++l) total += align_up((size_t)layers[l + 1]->host.K_pad * 8, 256);
         }
+        const size_t group_off = total;
+        try {
+            mp->group_ok = mp->persist_ok && chain_group_build(hps, mp->dst, (flags & PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER) != 0, mp->group);
+        } catch (const std::bad_alloc&) {
+            delete mp;
+            set_error("out of host memory");
+            return PIVOT_E_ALLOC;
+        }
+        if (mp->group_ok) total += mp->group.meta.size() * 4 + mp->group.vals.size();     // (multiples of 16 KB)
         void* base = nullptr;
         hipError_t e = hipMalloc(&base, total);
         if (e != hipSuccess) { set_error("hipMalloc(%zu) failed: %s", total, hipGetErrorString(e)); delete mp; return PIVOT_E_ALLOC; }
@@ -347,7 +356,7 @@ int pivot_mlp_plan(pivot_fc_plan_t* const* layers, int Lcount, int flags, pivot_
             off += align_up(v.size() * 4, 256);
         }
         if (mp->persist_ok) {
-            e = hipMemset(mp->dev_base + persist_off, 0, total - persist_off);
+            e = hipMemset(mp->dev_base + persist_off, 0, group_off - persist_off);
             if (e != hipSuccess) { set_error("hipMemset failed: %s", hipGetErrorString(e)); (void)hipFree(base); delete mp; return PIVOT_E_HIP; }
             off = persist_off;
             mp->persist_ctl = reinterpret_cast<uint32_t*>(mp->dev_base + off);
@@ -356,6 +365,16 @@ int pivot_mlp_plan(pivot_fc_plan_t* const* layers, int Lcount, int flags, pivot_
                 mp->persist_pairs.push_back(reinterpret_cast<unsigned long long*>(mp->dev_base + off));
                 off += align_up((size_t)layers[l + 1]->host.K_pad * 8, 256);
             }
+        }
+        if (mp->group_ok) {
+            ChainGroup& cg = mp->group;
+            char* meta = mp->dev_base + group_off;
+            char* vals = meta + cg.meta.size() * 4;
+            e = hipMemcpy(meta, cg.meta.data(), cg.meta.size() * 4, hipMemcpyHostToDevice);
+            if (e == hipSuccess) e = hipMemcpy(vals, cg.vals.data(), cg.vals.size(), hipMemcpyHostToDevice);
+            if (e != hipSuccess) { set_error("hipMemcpy failed: %s", hipGetErrorString(e)); (void)hipFree(base); delete mp; return PIVOT_E_HIP; }
+            cg.dev_meta = meta; cg.dev_vals = vals;
+            cg.meta = {}; cg.vals = {};
         }
     }
     *out = mp;
@@ -436,6 +455,8 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
     const pivot_fc_plan_t* last = plan->layers[Lc - 1];
     if (ldx < plan->layers[0]->host.d.K || ldy < (keep ? last->host.M_pad : last->host.d.M)) { set_error("ldx/ldy too small"); return PIVOT_E_SHAPE; }
     char* ws = reinterpret_cast<char*>(ws_dev);
+    if (batch == 1 && plan->group_ok)
+        return launch_chain_group(plan->group, x_dev, plan->layers[0]->dev.pcol_pad, reinterpret_cast<float*>(y_dev), stream);
     if (batch == 1 && plan->persist_ok) {
         // the whole chain in one launch; intermediates are the plan's own (value, tag) pairs
         ChainPersistLaunch C;

@@ -237,6 +237,19 @@ size_t chain_persist_ctl_bytes();
 int    chain_persist_status_offset();  // byte offset of the status word inside the control block
 int    launch_chain_persist(const ChainPersistLaunch& C);
 
+// A chain in one workgroup (batch 1): the image that its kernel reads and what its launch is told.
+constexpr int kChainGroupSlots = 8;    // wave-loads of 1 KB per wavefront, all layers together
+struct ChainGroup {
+    int nslots = 0, K = 0, K_pad = 0, act_vecs = 0, wdtype = 0, bw = 0;
+    uint32_t layer_ends = 0;
+    size_t smem = 0;
+    std::vector<int32_t> meta;         // host copies, dropped once they are on the device
+    std::vector<uint8_t> vals;
+    const void* dev_meta = nullptr; const void* dev_vals = nullptr;
+};
+bool   chain_group_build(const std::vector<const HostPlan*>& layers, const std::vector<std::vector<int32_t>>& dst, bool keep, ChainGroup& g);
+int    launch_chain_group(const ChainGroup& g, const void* x, const int32_t* pcol_pad, float* y, void* stream);
+
 }  // namespace pivot
 
 namespace pivot {
@@ -270,4 +283,7 @@ struct pivot_mlp_plan {
     size_t persist_smem = 0, persist_smem_copy = 0;
     uint32_t* persist_ctl = nullptr;
     std::vector<unsigned long long*> persist_pairs;
+    // one-workgroup form of chains whose weights fit its registers, image in dev_base
+    bool group_ok = false;
+    pivot::ChainGroup group;
 };

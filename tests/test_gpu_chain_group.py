@@ -1,0 +1,75 @@
+"""Chains small enough for one workgroup (batch 1) against the CPU oracle, at
+the edges of what that form takes.  Needs a GPU."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1712_01084_amd import binding as B
+from paper_1712_01084_amd import workloads as WL
+
+import gpu_util as G
+from test_gpu_chain import _check_chain, _run_chain
+
+pytestmark = pytest.mark.gpu
+
+
+def _in_one_workgroup(probs):
+    """Whether a run takes the form: it leaves the other one-launch form's launch counters (4096 bytes in front of
+    the status word) alone."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+    plans = [G.dev_plan(p) for p in probs]
+    mlp = B.pivot_mlp_plan(plans, 0)
+    try:
+        st = torch.cuda.current_stream().cuda_stream
+        xd = torch.from_numpy(probs[0].x).cuda()
+        yd = torch.empty((1, probs[-1].M), dtype=torch.float32, device="cuda")
+        ws = G.workspace(B.pivot_mlp_workspace_bytes(mlp, 1))
+        B.pivot_mlp_run(mlp, xd.data_ptr(), probs[0].K, yd.data_ptr(), probs[-1].M, 1, ws.data_ptr(), ws.numel(), st)
+        torch.cuda.synchronize()
+        counters = (ctypes.c_uint32 * 1024)()
+        assert hip.hipMemcpy(counters, ctypes.c_void_p(B.pivot_mlp_status_word(mlp) - 4096), 4096, 2) == 0
+        return not any(counters)
+    finally:
+        B.pivot_mlp_plan_destroy(mlp)
+        for h in plans:
+            B.pivot_fc_plan_destroy(h)
+
+
+# (tile height, width, sizes, kept): tiles of fewer rows than a wave-load covers (several tiles a load), of one and of several
+# wave-loads; ragged sizes; inputs beyond 1024 columns; 2 to 5 layers; units that take turns on the wavefronts
+@pytest.mark.parametrize("bh,bw,dims,kept,taken", [
+    (16, 16, (256, 256, 256, 256), 1 / 16, True), (16, 16, (100, 90, 50), 0.3, True), (8, 16, (61, 75, 33), 0.4, True),
+    (32, 32, (97, 130, 40), 0.3, True), (64, 64, (130, 70, 65), 0.4, None), (8, 64, (260, 72, 40, 24), 0.3, True),
+    (64, 16, (150, 64, 64), 0.2, None), (16, 32, (3001, 40, 40, 19), 0.03, True), (16, 16, (2049, 40, 19), 0.02, False), (16, 16, (1025, 300, 10), 0.03, True),
+    (16, 16, (17, 500, 33, 20), 0.1, True), (16, 16, (64, 48, 48, 48, 48, 20), 0.4, True),
+    (32, 32, (1024, 1024, 1024), 0.2, False)])
+@pytest.mark.parametrize("eliminated", [False, True])
+@pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
+def test_chain_in_one_workgroup(wdtype, eliminated, bh, bw, dims, kept, taken):
+    probs = WL.config4(seed=51 + bh + len(dims), dims=dims, eliminated=eliminated, bh=bh, bw=bw, frac=kept, wdtype=wdtype)
+    _check_chain(probs, want_one_launch=True, repeats=3)
+    _check_chain(probs, flags=B.PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER, want_one_launch=True)
+    if taken is not None:
+        assert _in_one_workgroup(probs) == taken
+
+
+@pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
+def test_empty_block_rows_and_infinite_inputs(wdtype):
+    # a layer without kept tiles, a block row without any; an infinite input reaches the rows that read it and no
+    # other (padding of a wave-load meets no x), as with a launch per layer
+    probs = WL.config4(seed=52, dims=(80, 90, 70, 33), bh=16, bw=16, frac=0.3, wdtype=wdtype)
+    probs[0].tile_mask[1, :] = 0
+    probs[2].tile_mask[:] = 0
+    assert _in_one_workgroup(probs)
+    _check_chain(probs, want_one_launch=True)
+    probs = WL.config4(seed=53, dims=(80, 90, 70), bh=16, bw=16, frac=0.2, wdtype=wdtype)
+    assert _in_one_workgroup(probs)
+    probs[0].x[0, 5] = np.inf
+    one = _run_chain(probs, want_one_launch=True)
+    per_layer = _run_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER, want_one_launch=False)
+    for special in (np.isnan, np.isposinf, np.isneginf):
+        assert (special(one) == special(per_layer)).all()
+    assert not np.isfinite(one).all() and np.isfinite(one).any()
