@@ -237,7 +237,7 @@ size_t chain_persist_ctl_bytes();
 int    chain_persist_status_offset();  // byte offset of the status word inside the control block
 int    launch_chain_persist(const ChainPersistLaunch& C);
 
-// A chain in one workgroup (batch 1): the image that its kernel reads and what its launch is told.
+// A chain in one workgroup per batch row: the image that its kernel reads and what its launch is told.
 constexpr int kChainGroupSlots = 8;    // wave-loads of 1 KB per wavefront, all layers together
 struct ChainGroup {
     int nslots = 0, K = 0, K_pad = 0, act_vecs = 0, wdtype = 0, bw = 0;
@@ -248,7 +248,7 @@ struct ChainGroup {
     const void* dev_meta = nullptr; const void* dev_vals = nullptr;
 };
 bool   chain_group_build(const std::vector<const HostPlan*>& layers, const std::vector<std::vector<int32_t>>& dst, bool keep, ChainGroup& g);
-int    launch_chain_group(const ChainGroup& g, const void* x, const int32_t* pcol_pad, float* y, void* stream);
+int    launch_chain_group(const ChainGroup& g, const void* x, int64_t ldx, const int32_t* pcol_pad, float* y, int64_t ldy, int batch, void* stream);
 
 }  // namespace pivot
 

@@ -1,8 +1,11 @@
-// A chain of a few tens of KB of weights at batch 1 in ONE workgroup.  The
+// A chain of a few tens of KB of weights in ONE workgroup per batch row.  The
 // one-launch form over many workgroups (pivot_mlp_persist.hip) pays a
-// device-wide exchange of about 1.8 us per boundary; of a chain this small the
-// whole stream fits the registers of one workgroup, and a boundary is an LDS
-// barrier.
+// device-wide exchange of about 1.8 us per boundary, a launch per layer, which
+// larger batches of larger chains take, an empty launch's turnaround and a
+// trip; of a chain this small the whole stream fits the registers of one
+// workgroup, and a boundary is an LDS barrier.  Batch rows meet only in the
+// caches: each has a compute unit of its own, which reads the weights at the
+// rate it would read them alone.
 //
 // The chain plan holds the tile values once more, in the order in which the
 // sixteen wavefronts take them: slot k of wavefront w is the 1 KB at
@@ -17,7 +20,9 @@
 // What bounds it: the launch and one trip to memory; beyond about 64 KB the rate of one compute unit.  Us per run in
 // replayed graphs, many workgroups / one: 256-256-256-256 block-diagonal 16x16 fp32 (48 KB) 6.1 / 2.65 (eager calls 6.2 /
 // 3.7, the host's), eight such layers (128 KB) 13.0 / 4.9; 512-512-512-512 fp16 6 % kept (96 KB) 6.5 / 4.2, 512-512-512
-// 32x32 fp16 10 % (128 KB) 4.9 / 4.15, 200-200-200 fp16 4.8 / 2.45.
+// 32x32 fp16 10 % (128 KB) 4.9 / 4.15, 200-200-200 fp16 4.8 / 2.45.  Of several batch rows, a launch per layer / this form,
+// batch 2, 8, 64: the first 6.9 / 2.8, 7.3 / 2.8, 7.9 / 2.9 (eager calls 13.5 / 3.9), the 128 KB fp16 chain 5.5 / 4.4, 6.1 /
+// 4.5, 6.7 / 4.7, 500-500-500 64x64 fp16 10 % 4.86 / 4.87, 7.6 / 4.95, 6.5 / 5.0.
 #include <algorithm>
 #include <cstring>
 
@@ -34,10 +39,12 @@ enum { kSlotEnd = 1, kSlotRelu = 2, kSlotLast = 4 };    // flags of a slot; from
 
 // q_layer_ends: bit k set = a layer ends with slot k.  q_k0 = columns of x | padded << 16; q_act_vecs: 16-byte pieces of LDS in
 // front of the natural-order x (the layers' inputs in block order, one behind the other, the first one the chain's).
+// The arguments that the first loads need come first (preloaded).
 template <typename WT, int BW, int NS>
 __global__ void __launch_bounds__(kGroupNT) mlp_group_kernel(const int4* __restrict__ p_meta, const char* __restrict__ p_vals,
                                                              const WT* __restrict__ p_x, const int32_t* __restrict__ p_pcol,
-                                                             float* __restrict__ p_y, int q_k0, int q_act_vecs, uint32_t q_layer_ends) {
+                                                             long long q_ldx, int q_k0, int q_act_vecs, uint32_t q_layer_ends,
+                                                             float* __restrict__ p_y, long long q_ldy) {
     using V = typename Elem<WT>::vec;
     constexpr int VEC = Elem<WT>::VEC, LPR = BW / VEC;
     extern __shared__ __align__(16) char smem[];
@@ -46,6 +53,8 @@ __global__ void __launch_bounds__(kGroupNT) mlp_group_kernel(const int4* __restr
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int K = q_k0 & 0xFFFF, kpad = (int)((uint32_t)q_k0 >> 16);
+    p_x += (long long)blockIdx.x * q_ldx;
+    p_y += (long long)blockIdx.x * q_ldy;
 
     // x first: the first thing that is waited for
     const WT x0 = p_x[tid < K ? tid : K - 1];
@@ -91,12 +100,13 @@ __global__ void __launch_bounds__(kGroupNT) mlp_group_kernel(const int4* __restr
     }
 }
 
-using GroupLaunch = void (*)(const ChainGroup&, const void*, const int32_t*, float*, hipStream_t);
+using GroupLaunch = void (*)(const ChainGroup&, const void*, int64_t, const int32_t*, float*, int64_t, int, hipStream_t);
 template <typename WT, int BW, int NS>
-void launch_group_t(const ChainGroup& g, const void* x, const int32_t* pcol_pad, float* y, hipStream_t st) {
-    hipLaunchKernelGGL((mlp_group_kernel<WT, BW, NS>), dim3(1), dim3(kGroupNT), g.smem, st,
+void launch_group_t(const ChainGroup& g, const void* x, int64_t ldx, const int32_t* pcol_pad, float* y, int64_t ldy, int batch, hipStream_t st) {
+    hipLaunchKernelGGL((mlp_group_kernel<WT, BW, NS>), dim3(batch), dim3(kGroupNT), g.smem, st,
                        reinterpret_cast<const int4*>(g.dev_meta), reinterpret_cast<const char*>(g.dev_vals),
-                       reinterpret_cast<const WT*>(x), pcol_pad, y, (int)((uint32_t)g.K | ((uint32_t)g.K_pad << 16)), g.act_vecs, g.layer_ends);
+                       reinterpret_cast<const WT*>(x), pcol_pad, (long long)ldx, (int)((uint32_t)g.K | ((uint32_t)g.K_pad << 16)),
+                       g.act_vecs, g.layer_ends, y, (long long)ldy);
 }
 template <typename WT, int BW>
 GroupLaunch group_launch_of(int ns) {
@@ -196,11 +206,11 @@ bool chain_group_build(const std::vector<const HostPlan*>& layers, const std::ve
     return true;
 }
 
-int launch_chain_group(const ChainGroup& g, const void* x, const int32_t* pcol_pad, float* y, void* stream) {
+int launch_chain_group(const ChainGroup& g, const void* x, int64_t ldx, const int32_t* pcol_pad, float* y, int64_t ldy, int batch, void* stream) {
     GroupLaunch run = nullptr;
     if (g.wdtype == PIVOT_F32) run = g.bw == 16 ? group_launch_of<float, 16>(g.nslots) : (g.bw == 32 ? group_launch_of<float, 32>(g.nslots) : group_launch_of<float, 64>(g.nslots));
     else run = g.bw == 16 ? group_launch_of<_Float16, 16>(g.nslots) : (g.bw == 32 ? group_launch_of<_Float16, 32>(g.nslots) : group_launch_of<_Float16, 64>(g.nslots));
-    run(g, x, pcol_pad, y, reinterpret_cast<hipStream_t>(stream));
+    run(g, x, ldx, pcol_pad, y, ldy, batch, reinterpret_cast<hipStream_t>(stream));
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }

@@ -1,4 +1,4 @@
-"""Chains small enough for one workgroup (batch 1) against the CPU oracle, at
+"""Chains small enough for one workgroup per batch row against the CPU oracle, at
 the edges of what that form takes.  Needs a GPU."""
 import ctypes
 
@@ -73,3 +73,31 @@ def test_empty_block_rows_and_infinite_inputs(wdtype):
     for special in (np.isnan, np.isposinf, np.isneginf):
         assert (special(one) == special(per_layer)).all()
     assert not np.isfinite(one).all() and np.isfinite(one).any()
+
+
+@pytest.mark.parametrize("batch", [2, 17, 64])
+@pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
+def test_batch_rows_equal_single_runs(wdtype, batch):
+    # a workgroup per batch row: row for row the bits of runs of one, whatever lies between the rows of x and y
+    probs = WL.config4(seed=54, batch=batch, dims=(203, 130, 75), bh=16, bw=16, frac=0.15, wdtype=wdtype)
+    _check_chain(probs, want_one_launch=True)
+    plans = [G.dev_plan(p) for p in probs]
+    mlp = B.pivot_mlp_plan(plans, 0)
+    try:
+        st = torch.cuda.current_stream().cuda_stream
+        K, M, ldx, ldy = probs[0].K, probs[-1].M, probs[0].K + 3, probs[-1].M + 5
+        x = torch.full((batch, ldx), float("nan")).to(torch.from_numpy(probs[0].x).dtype)
+        x[:, :K] = torch.from_numpy(probs[0].x)
+        xd = x.cuda()
+        yd = torch.full((batch, ldy), 7.0, dtype=torch.float32, device="cuda")
+        one = torch.zeros(batch, M, dtype=torch.float32, device="cuda")
+        ws = G.workspace(B.pivot_mlp_workspace_bytes(mlp, batch))
+        B.pivot_mlp_run(mlp, xd.data_ptr(), ldx, yd.data_ptr(), ldy, batch, ws.data_ptr(), ws.numel(), st)
+        for b in range(batch):
+            B.pivot_mlp_run(mlp, xd[b].data_ptr(), ldx, one[b].data_ptr(), M, 1, ws.data_ptr(), ws.numel(), st)
+        torch.cuda.synchronize()
+        assert torch.equal(yd[:, :M], one) and bool((yd[:, M:] == 7.0).all())
+    finally:
+        B.pivot_mlp_plan_destroy(mlp)
+        for h in plans:
+            B.pivot_fc_plan_destroy(h)
