@@ -297,11 +297,12 @@ int  pivot_fc_run_static(const pivot_fc_plan_t* plan, const void* x_dev, int64_t
  * for each other.  A wait that does not end within 2^18 polls gives up, the
  * status word reads 1 and y_dev is undefined; pivot_mlp_status synchronises
  * the stream, returns the status of the launches since its last call and
- * clears it.  Of those, a chain of at most 128 KB of weights whose inputs
- * fit beside each other in LDS runs in one workgroup per batch row, at every
- * batch, from a copy of the weights that the chain plan holds: none of its
- * runs waits for anything and the status stays 0.  Every other chain and batch (or PIVOT_MLP_LAUNCH_PER_LAYER)
- * runs one launch per layer.
+ * clears it.  Of those, a chain of at most 128 (two layers) or 256 KB of
+ * weights that sixteen wavefronts can share out, whose inputs fit beside each
+ * other in LDS, runs in one workgroup per batch row, at every batch, from a
+ * copy of the weights that the chain plan holds: none of its runs waits for
+ * anything and the status stays 0.  Every other chain and batch (or
+ * PIVOT_MLP_LAUNCH_PER_LAYER) runs one launch per layer.
  */
 #define PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER 1
 #define PIVOT_MLP_LAUNCH_PER_LAYER       2

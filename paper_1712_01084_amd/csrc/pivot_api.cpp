@@ -455,7 +455,7 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
     const pivot_fc_plan_t* last = plan->layers[Lc - 1];
     if (ldx < plan->layers[0]->host.d.K || ldy < (keep ? last->host.M_pad : last->host.d.M)) { set_error("ldx/ldy too small"); return PIVOT_E_SHAPE; }
     char* ws = reinterpret_cast<char*>(ws_dev);
-    if (plan->group_ok)
+    if (plan->group_ok && batch >= plan->group.batch_from)
         return launch_chain_group(plan->group, x_dev, ldx, plan->layers[0]->dev.pcol_pad, reinterpret_cast<float*>(y_dev), ldy, batch, stream);
     if (batch == 1 && plan->persist_ok) {
         // the whole chain in one launch; intermediates are the plan's own (value, tag) pairs

@@ -238,9 +238,10 @@ int    chain_persist_status_offset();  // byte offset of the status word inside 
 int    launch_chain_persist(const ChainPersistLaunch& C);
 
 // A chain in one workgroup per batch row: the image that its kernel reads and what its launch is told.
-constexpr int kChainGroupSlots = 8;    // wave-loads of 1 KB per wavefront, all layers together
+constexpr int kChainGroupSlots = 16;    // wave-loads of 1 KB per wavefront, all layers together
 struct ChainGroup {
     int nslots = 0, K = 0, K_pad = 0, act_vecs = 0, wdtype = 0, bw = 0;
+    int batch_from = 1;                // smallest batch that takes the form
     uint32_t layer_ends = 0;
     size_t smem = 0;
     std::vector<int32_t> meta;         // host copies, dropped once they are on the device

@@ -1,4 +1,4 @@
-// A chain of a few tens of KB of weights in ONE workgroup per batch row.  The
+// A chain of at most 256 KB of weights in ONE workgroup per batch row.  The
 // one-launch form over many workgroups (pivot_mlp_persist.hip) pays a
 // device-wide exchange of about 1.8 us per boundary, a launch per layer, which
 // larger batches of larger chains take, an empty launch's turnaround and a
@@ -59,14 +59,17 @@ __global__ void __launch_bounds__(kGroupNT) mlp_group_kernel(const int4* __restr
     // x first: the first thing that is waited for
     const WT x0 = p_x[tid < K ? tid : K - 1];
     const int src0 = p_pcol[tid < kpad ? tid : kpad - 1];
-    int4 m[NS];
-    V w[NS];
-    #pragma unroll
-    for (int k = 0; k < NS; ++k) {
+    // Eight slots are in flight (their registers); a later one is asked for when the one eight before it is consumed.
+    constexpr int NF = NS < 8 ? NS : 8;
+    int4 m[NF];
+    V w[NF];
+    auto ask = [&](int k) {
         const int at = (k * kGroupNW + wave) * 64 + lane;
-        m[k] = p_meta[at];
-        w[k] = load16<V>(p_vals + (size_t)at * 16);
-    }
+        m[k % NF] = p_meta[at];
+        w[k % NF] = load16<V>(p_vals + (size_t)at * 16);
+    };
+    #pragma unroll
+    for (int k = 0; k < NF; ++k) ask(k);
     __builtin_amdgcn_sched_barrier(0);                  // every load above is issued before anything below waits
     // padding columns of the later layers' inputs are never stored to
     for (int i = kpad / VEC + tid; i < q_act_vecs; i += kGroupNT) reinterpret_cast<V*>(act)[i] = V(0);
@@ -83,16 +86,21 @@ __global__ void __launch_bounds__(kGroupNT) mlp_group_kernel(const int4* __restr
     float acc = 0.f;
     #pragma unroll
     for (int k = 0; k < NS; ++k) {
-        const V xv = *reinterpret_cast<const V*>(act + (m[k].x > 0 ? m[k].x : 0));
-        acc = dot_vec(w[k], m[k].x >= 0 ? xv : V(0), acc);
-        const int f = __builtin_amdgcn_readfirstlane(m[k].w);
+        const int4 mk = m[k % NF];
+        const V xv = *reinterpret_cast<const V*>(act + (mk.x > 0 ? mk.x : 0));
+        acc = dot_vec(w[k % NF], mk.x >= 0 ? xv : V(0), acc);
+        if (k + NF < NS) {
+            ask(k + NF);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int f = __builtin_amdgcn_readfirstlane(mk.w);
         if (f & kSlotEnd) {
             float v = group_sum<LPR>(acc);
             for (int o = f >> 8; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-            v = apply_act(v + __int_as_float(m[k].z), (f & kSlotRelu) ? 1 : 0);
-            if (m[k].y >= 0) {
-                if (f & kSlotLast) p_y[m[k].y] = v;
-                else act[m[k].y] = WT(v);
+            v = apply_act(v + __int_as_float(mk.z), (f & kSlotRelu) ? 1 : 0);
+            if (mk.y >= 0) {
+                if (f & kSlotLast) p_y[mk.y] = v;
+                else act[mk.y] = WT(v);
             }
             acc = 0.f;
         }
@@ -114,7 +122,9 @@ GroupLaunch group_launch_of(int ns) {
         case 3: return launch_group_t<WT, BW, 3>;
         case 4: return launch_group_t<WT, BW, 4>;
         case 6: return launch_group_t<WT, BW, 6>;
-        default: return launch_group_t<WT, BW, 8>;
+        case 8: return launch_group_t<WT, BW, 8>;
+        case 12: return launch_group_t<WT, BW, 12>;
+        default: return launch_group_t<WT, BW, 16>;
     }
 }
 
@@ -139,6 +149,12 @@ bool chain_group_build(const std::vector<const HostPlan*>& layers, const std::ve
         act += hp->K_pad;
         if ((act + f.d.K) * es > kGroupLds) return false;
     }
+    // Every four slots beyond 8 cost 0.6-0.9 us (a compute unit's 64 bytes a clock), every boundary of the forms it replaces
+    // 1.2-1.8 at batch 1 and 2.2 beyond.  Us, batch 1 / 8, the other forms and this one: two layers, 12 slots, 640x3 16x16 fp16
+    // 10 % 5.1, 5.2 / 5.4, 5.3, 800x3 5 % 5.2, 6.1 / 5.4, 6.3, 512x3 32x32 fp32 10 % 5.1, 6.0 / 5.4, 6.1; three layers, 9-12
+    // slots, 512x4 16x16 fp32 6 % 6.4, 5.0 / 7.7, 5.2, 784-128-64-10 32x32 fp16 40 % 5.8, 5.7 / 7.9, 5.8; 13-16 slots,
+    // 600-400-200-100 64x64 fp32 10 % 5.7, 6.05 / 8.0, 6.2; four layers, 300x5 32x32 fp16 15 % 8.0, 5.9 / 11.0, 6.0.
+    const int most = Lc == 2 ? 8 : kChainGroupSlots;
     // units of a layer: the rows of one wave-load of a block row (all of it where the tile has fewer), to the least loaded
     // wavefront, longest first
     struct Unit { int br, piece, loads, wave, pos; };
@@ -160,10 +176,11 @@ bool chain_group_build(const std::vector<const HostPlan*>& layers, const std::ve
             load[u.wave] += u.loads;
         }
         first[l + 1] = first[l] + *std::max_element(load, load + kGroupNW);
-        if (first[l + 1] > kChainGroupSlots) return false;
+        if (first[l + 1] > most) return false;
     }
     const int used = first[Lc];
-    g.nslots = used <= 3 ? 3 : (used <= 4 ? 4 : (used <= 6 ? 6 : 8));
+    g.nslots = used <= 3 ? 3 : (used <= 4 ? 4 : (used <= 6 ? 6 : (used <= 8 ? 8 : (used <= 12 ? 12 : 16))));
+    g.batch_from = Lc == 3 && used > 12 ? 2 : 1;
     g.layer_ends = 0;
     for (int l = 0; l + 1 < Lc; ++l) g.layer_ends |= 1u << (first[l + 1] - 1);      // (nothing reads the last layer's outputs)
     g.meta.assign((size_t)g.nslots * kGroupNT * 4, 0);

@@ -45,6 +45,7 @@ def _in_one_workgroup(probs):
     (32, 32, (97, 130, 40), 0.3, True), (64, 64, (130, 70, 65), 0.4, None), (8, 64, (260, 72, 40, 24), 0.3, True),
     (64, 16, (150, 64, 64), 0.2, None), (16, 32, (3001, 40, 40, 19), 0.03, True), (16, 16, (2049, 40, 19), 0.02, False), (16, 16, (1025, 300, 10), 0.03, True),
     (16, 16, (17, 500, 33, 20), 0.1, True), (16, 16, (64, 48, 48, 48, 48, 20), 0.4, True),
+    (16, 16, (512, 512, 512, 512), 1 / 16, True), (32, 32, (300, 300, 300, 300, 300), 0.15, None),
     (32, 32, (1024, 1024, 1024), 0.2, False)])
 @pytest.mark.parametrize("eliminated", [False, True])
 @pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
@@ -81,6 +82,8 @@ def test_batch_rows_equal_single_runs(wdtype, batch):
     # a workgroup per batch row: row for row the bits of runs of one, whatever lies between the rows of x and y
     probs = WL.config4(seed=54, batch=batch, dims=(203, 130, 75), bh=16, bw=16, frac=0.15, wdtype=wdtype)
     _check_chain(probs, want_one_launch=True)
+    # three layers of 13-16 wave-loads a wavefront (fp32): from batch 2 on
+    _check_chain(WL.config4(seed=55, batch=batch, dims=(600, 400, 200, 100), bh=64, bw=64, frac=0.1, wdtype=wdtype), want_one_launch=True)
     plans = [G.dev_plan(p) for p in probs]
     mlp = B.pivot_mlp_plan(plans, 0)
     try:
