@@ -27,6 +27,13 @@ constexpr size_t frag_index(int b, int c, int batch, int shift) {
     return (((size_t)(c >> shift) * batch + b) << shift) + (c & ((1 << shift) - 1));
 }
 
+// Copy of x to fragment order: bytes of LDS that a row of K elements needs there, in whole aligned 16-byte pieces (a row
+// that starts inside its first piece may have one more), 0 = longer than the 64 KB a workgroup copies.
+inline size_t gather_row_lds(uintptr_t x, int64_t ldx, int K, int es) {
+    const size_t late = ldx * es % 16 == 0 ? (x & 15) : 16 - (size_t)es;
+    return (size_t)K * es <= 64 * 1024 ? align_up(late + (size_t)K * es, 16) : 0;
+}
+
 // Which MFMA shape a row-major fp16 tile feeds: 0 = 16x16x32, 1 = 32x32x16, -1 = none.
 inline int mfma_kind(int wdtype, int bh, int bw) {
     if (wdtype != PIVOT_F16) return -1;

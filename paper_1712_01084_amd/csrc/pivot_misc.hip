@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(512) gather_frag_kernel(const int32_t* __restr
     // waited for the second piece before it asked for the third)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     #pragma unroll
-    for (int u = 0; u < 8; ++u) {                       // 64 KB by 512 threads: the whole row at once
+    for (int u = 0; u < 9; ++u) {                       // 64 KB by 512 threads (and one piece): the whole row at once
         const int i = u * NT + tid;
         if (i < nvec)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xv + i),
@@ -96,14 +96,17 @@ __global__ void __launch_bounds__(256) gather_frag_far_kernel(const int32_t* __r
 template <typename WT>
 static int launch_gather_frag_t(const WT* x, int64_t ldx, const int32_t* pcol_pad, WT* xg, int K, int K_pad, int batch, hipStream_t st) {
     const int ngroups = K_pad / Elem<WT>::VEC;
-    const size_t smem = align_up((size_t)K * sizeof(WT), 16) + 16;
+    const size_t smem = gather_row_lds(reinterpret_cast<uintptr_t>(x), ldx, K, sizeof(WT));
     // The copy pays for long fp16 inputs of many elements (us per call of a layer with 1000 outputs, 16x32 tiles, 25 %
     // kept, copied / direct: 2048 columns, batch 64 6.1 / 5.9; 3000, 64 6.5 / 7.1; 4090, 64 7.6 / 8.2; 4096, 32 6.0 / 6.2;
     // 9216, 16 7.0 / 7.4; 12000, 17 8.3 / 9.1; 25088, 8 10.0 / 10.3; with 4096 outputs, 32x32 tiles: 2048, 64 9.1 / 9.2;
     // 4096, 32 7.8 / 8.5; 8000, 32 9.8 / 10.3).  Of fp32 rows a line holds half as many elements and the copy is twice as
-    // long: 9216 columns, batch 16 8.4 / 6.9 and 64 12.7 / 10.6, always slower.
-    if (sizeof(WT) == 2 && smem <= 64 * 1024 && K >= 3000 && (size_t)batch * K >= 128 * 1024) {
+    // long: 9216 columns, batch 16 8.4 / 6.9 and 64 12.7 / 10.6, always slower.  To the longest row that fits, aligned or
+    // not: 32768, 32x32 tiles, 10 %, batch 64 13.3 / 17.4, 32 unaligned 9.6 / 12.1.
+    if (sizeof(WT) == 2 && smem > 0 && K >= 3000 && (size_t)batch * K >= 128 * 1024) {
         const int segs = 8;
+        if (smem > 64 * 1024)                           // (unaligned rows of 32761 to 32768 columns)
+            HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(gather_frag_kernel<WT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         hipLaunchKernelGGL(gather_frag_kernel<WT>, dim3(segs, batch), dim3(512), smem, st, pcol_pad, x, xg, (long long)ldx, K, ngroups, batch, (ngroups + segs - 1) / segs);
     } else {
         hipLaunchKernelGGL(gather_frag_far_kernel<WT>, dim3((ngroups + 31) / 32, (batch + 7) / 8), dim3(256), 0, st, pcol_pad, x, xg, (long long)ldx, ngroups, batch);

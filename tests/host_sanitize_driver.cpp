@@ -95,6 +95,15 @@ int main() {
         REQUIRE(pivot::build_host_plan(d, W.data(), PIVOT_W_PIVOTED, mask, id.data(), id.data(), nullptr, hp) == PIVOT_E_UNSUPPORTED);
         REQUIRE(std::strlen(pivot::last_error()) > 0);
     }
+    // copy of x to fragment order: fp16 rows of up to 32768 columns fit the LDS copy wherever they start
+    for (int K : {3000, 32760, 32761, 32767, 32768, 32769})
+        for (int64_t ldx : {(int64_t)K, (int64_t)K + 1, (int64_t)K + 8})
+            for (uintptr_t x : {4096, 4098, 4110})
+                for (int b = 0; b < 9; ++b) {
+                    const size_t late = (x + (size_t)b * ldx * 2) & 15, have = pivot::gather_row_lds(x, ldx, K, 2);
+                    REQUIRE(K > 32768 ? have == 0 : have >= pivot::align_up(late + (size_t)K * 2, 16) && have <= 64 * 1024 + 16);
+                    REQUIRE(K > 32768 || x % 16 || ldx % 8 || have <= 64 * 1024);
+                }
     // feed-back search: ragged sizes, more levels than the matrix can be halved, bad starts
     for (auto mk : {std::pair<int, int>{1, 1}, {5, 3}, {37, 53}, {64, 48}}) {
         const int M = mk.first, K = mk.second;

@@ -53,6 +53,9 @@ def test_fp32_behind_a_boundary_few_batch_rows(K, M, bh, bw, frac):
     (WL.F32, 500, 30000, 16, 16, 17, 0.12),
     (WL.F16, 64, 16390, 8, 8, 64, 1.0),          # items of 768 tiles; rows of x copied into LDS
     (WL.F16, 200, 33000, 64, 32, 20, 0.5),       # rows of x too long for the copy
+    (WL.F16, 100, 32768, 32, 32, 20, 0.2),       # the longest that is copied
+    (WL.F16, 100, 32761, 32, 32, 20, 0.2),
+    (WL.F16, 64, 32769, 16, 32, 9, 0.2),
     (WL.F16, 4096, 4100, 32, 32, 40, 0.2),
 ])
 def test_natural_input(wdtype, M, K, bh, bw, batch, frac):
