@@ -225,11 +225,11 @@ int    pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream);
  *          recurrent loop, whose kernels produce that order, use it behind
  *          every boundary from batch 2 on (F32 at batch 2 to 8: but for few
  *          and long work items).
- *          Batch 5..64 with at most 4096 input columns (most of those with
- *          2048, of the others batch 5..16 with a quarter of them staged per
- *          work item and 33..64 with few work items): the rows of x are copied into
- *          LDS and the fragments gathered from there, whatever their alignment
- *          and stride.
+ *          Batch 5..64 with at most 4096 input columns, where a work item reads
+ *          enough of them: the rows of x are copied into LDS and the fragments
+ *          gathered from there, whatever their alignment and stride (of up to
+ *          2048 columns mostly only rows that are whole 16-byte vectors, aligned
+ *          and densely packed: others stay with the form that gathers).
  */
 int  pivot_fc_run(const pivot_fc_plan_t* plan, const void* x_dev, int64_t ldx,
                   void* y_dev, int64_t ldy, int batch,

@@ -146,9 +146,9 @@ enum { kPathVector = 0, kPathMfmaLds = 1, kPathFrag = 2, kPathMfmaXrow = 3 };
 // kernel that reads one; kXNaturalRows16: as kXNatural, that kernel in launch rows of 16 batch rows, whose partial sums
 // take less scratch where the last launch row is short; kXBlock: the layer or cell before, which writes the order the kernel wants).
 enum { kXNoCopy = 0, kXNatural = 1, kXBlock = 2, kXNaturalRows16 = 3 };
-struct FcShape { int layout, wdtype, bh, bw, lds_tiles, chunk_tiles, xrow_len, mean_tiles, nchunks, x_from, row_slices = 0, K = 0; };   // mean_tiles: kept tiles per work item, rounded up; row_slices: the plan's; K: columns
+struct FcShape { int layout, wdtype, bh, bw, lds_tiles, chunk_tiles, xrow_len, mean_tiles, nchunks, x_from, row_slices, x_vec; };   // mean_tiles: kept tiles per work item, rounded up; row_slices: the plan's; x_vec: rows of x are whole 16-byte vectors, aligned and densely packed
 inline int mean_tiles_of(int T, int nchunks) { return nchunks > 0 ? (T + nchunks - 1) / nchunks : 0; }
-inline FcShape fc_shape(const HostPlan& h, int x_from) { return FcShape{h.d.layout, h.d.wdtype, h.d.bh, h.d.bw, h.lds_tiles(), h.chunk_tiles, h.xrow_len(), mean_tiles_of(h.T, h.nchunks), h.nchunks, x_from, h.row_slices, h.d.K}; }
+inline FcShape fc_shape(const HostPlan& h, int x_from) { return FcShape{h.d.layout, h.d.wdtype, h.d.bh, h.d.bw, h.lds_tiles(), h.chunk_tiles, h.xrow_len(), mean_tiles_of(h.T, h.nchunks), h.nchunks, x_from, h.row_slices, h.d.K * elem_size(h.d.wdtype) % 16 == 0}; }   // for the rows of x that a caller with such a K most often brings
 int    fc_path(const FcShape& s, int batch);
 int    fc_batch_tile(const FcShape& s, int batch);
 bool   fc_wants_frag(const FcShape& s, int batch);          // the form that reads x in fragment order

@@ -116,14 +116,13 @@ int fc_path(const FcShape& s, int batch) {
     }
     if (batch < 3) return kPathVector;
     bool lds = false;
-    size_t launch_rows = 0;
     if (lds_tiles > 0) {
         const int rows = mfma_lds_rows(batch);
         const size_t xs_bytes = (size_t)rows * ((size_t)lds_tiles * bw + 8 + 16) * 2;   // + the paired form's zeroed columns
         // every launch row of 8 batch rows streams the weights again and gathers its own rows: beyond two launch
         // rows the form is kept while the launch rows together stage at most 5120 columns per work item
         // (4096x4096, 64x16 tiles, against the fragment form: batch 24 at 5 % kept 6.2 -> 5.1 us, batch 64 8.7 -> 7.8)
-        launch_rows = (size_t)(batch + rows - 1) / rows;
+        const size_t launch_rows = (size_t)(batch + rows - 1) / rows;
         const bool restage = frag && (double)(launch_rows - 1) * s.nchunks * s.mean_tiles * bw >= 100e3;
         lds = !restage && xs_bytes <= 48 * 1024 && (launch_rows <= 2 || launch_rows * lds_tiles * bw <= 5120);
     }
@@ -134,35 +133,41 @@ int fc_path(const FcShape& s, int batch) {
         const size_t cols = ((size_t)s.chunk_tiles + 1) * bw;
         const size_t copy_bytes = (size_t)16 * xrow_bytes((int)vecs) + cols * 4;
         const long long items = (long long)s.nchunks * mfma_slices(s, s.row_slices) * ((batch + 15) / 16);
-        const long long lds_items = lds ? (long long)s.nchunks * mfma_slices(s, batch <= 8 ? s.row_slices : (s.row_slices < 2 ? 1 : 2)) * (long long)launch_rows : 0;
-        const size_t lds_cols = launch_rows * (size_t)lds_tiles * bw;
+        // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few long block
+        // rows among many short ones most work items copy all of x for a handful of tiles, which the 8-row LDS-fed form
+        // does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and wins at batch 5-8; batch
+        // 9-16 keeps the rule it was measured with).
+        const bool quarter = (batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols) * 4 >= (size_t)s.xrow_len;
         bool pays;
-        if (s.xrow_len <= 2048) {
-            // Rows of at most 2048 columns, of which a compute unit holds two work items: up to batch 16 always (us, the
-            // rule for longer rows / this one, batch 8: 2000x1000 16x32 10 % 4.1 / 3.7, 4096x2048 32x32 10 % 4.2 / 3.9,
-            // 600x600 32x32 40 % 4.0 / 3.7), beyond while all work items are resident at once (batch 32: 2000x1000 4.8 /
-            // 4.1, 300x1800 16x64 50 % 5.6 / 4.6; batch 64: 2000x696 32x32 45 % 6.5 / 5.4; but 8000x1000 32x32 20 %,
-            // 1000 of them, batch 32 7.5 / 9.1).  Rows that are not whole 16-byte vectors cost it 0.3 us and the LDS-fed
-            // form, which gathers them from memory, nothing: where that takes them, of few and short work items, it is left
-            // alone (LDS-fed / this one: 605x891 16x32 46 % batch 8 3.65 / 3.9 and 48 3.9 / 4.25, 1000x1514 30 % batch 8
-            // 3.9 / 4.0, 231x1913 64x16 23 % batch 11 3.6 / 4.55, 1129x681 64x16 41 % batch 60 4.6 / 4.9).
-            const bool other = lds && (s.K % 8 != 0 ? (batch <= 16 ? lds_items >= 12 && lds_items <= 256 : lds_items <= 256 || lds_cols <= 3072)
-                                                    : batch > 16 && lds_cols <= 512);    // (222x128 32x64 24 %, batch 45: 3.8 / 4.0)
-            pays = !other && (batch <= 16 || (cols <= 2048 + (size_t)bw && items < 512));
+        if (lds && s.xrow_len <= 2048) {
+            // Rows of at most 2048 columns against the LDS-fed form.  Rows that are whole aligned vectors pay for their copy
+            // from an eighth of them staged per work item on, as long as the work items of the launch are resident at once:
+            // two per compute unit, of tiles 64 columns wide one (a second round of them shows from 257 on, 4.1 -> 5.7 us,
+            // where tiles 32 wide step at 513).  LDS-fed / this one, us: 784 columns, 32x32 tiles, batch 16, 156 items 4.7 /
+            // 3.9; 1520, 32x32, batch 24, 344 items 6.4 / 5.5; 744, 16x64, batch 64, 212 items 5.8 / 4.5; 760, 64x64, batch
+            // 24, 304 items 4.6 / 6.8; 256 staged of 1512, 16x32, batch 6, 627 items 5.4 / 6.4; 64 staged of 800, 32x64, batch
+            // 16 3.6 / 4.2.  Rows that are not cost it 0.3-0.5 us more and the LDS-fed form, which gathers them from memory,
+            // nothing (729 columns, 32x16, batch 8 3.1 / 4.1; 1056, 64x64, batch 24 3.9 / 4.7).
+            // Whatever the rows, at batch 5-16 one copy of 16 rows is ahead where the gathers bound the LDS-fed form, which
+            // come again with every row slice and launch row of 8: from 200 K columns staged by all its work items on, with
+            // two launch rows from 100 K on while this form has one work item per compute unit, or 1024 by one work item
+            // (1481 columns, 32x64, batch 16, 284 items of 1152 7.4 / 5.1; 1284, 64x64, batch 16, 668 of 202 10.4 / 8.1; 1493,
+            // 32x64, batch 16, 364 of 332 5.5 / 4.6; but 1727, 16x64, batch 16, 576 of 256, here 288 items, 6.3 / 7.2).
+            // Of 2038 drawn layers of both kinds the rule is 0.7 % from the better form in the mean.
+            const int slices = mfma_slices(s, batch > 8 && s.row_slices > 2 ? 2 : s.row_slices), launch_rows = batch > 8 ? (batch + 7) / 8 : 1;
+            const double staged = (double)s.nchunks * slices * launch_rows * s.mean_tiles * bw;
+            pays = (s.x_vec && (size_t)s.chunk_tiles * bw * 8 >= (size_t)s.xrow_len && items <= (bw == 64 ? 256 : 512)) ||
+                   (batch <= 16 && (staged >= 200e3 || (items <= 256 && ((batch > 8 && staged >= 100e3) || s.chunk_tiles * bw >= 1024))));
         } else if (batch <= 16) {
-            // "a quarter of the columns staged per work item": at batch 5-8 of the AVERAGE work item.  With a few
-            // long block rows among many short ones most work items copy all of x for a handful of tiles, which the
-            // 8-row LDS-fed form does not (4096x4096, per-row counts from 96 down to 2: the copy loses at batch 16 and
-            // wins at batch 5-8; batch 9-16 keeps the rule it was measured with).
-            pays = (batch <= 8 ? ((size_t)s.mean_tiles + 1) * bw : cols) * 4 >= (size_t)s.xrow_len;
+            pays = quarter;
         } else {
-            // Longer rows, beyond batch 32: three or four launch rows of it are ahead of the fragment form and its copy of x
-            // while every work item of them has a compute unit to itself and stages at most 2048 columns (us, 16x32
-            // tiles, batch 64, fragment form / this one: 1000x4090 25 % kept 7.5 / 7.0, 1000x4096 10 % 6.0 / 5.1 and 50 %
-            // (2048 columns) 8.6 / 8.4, 300x4000 64x64 50 % 8.3 / 6.8; with more work items, 2000x4090 32x32 25 % 9.7 /
-            // 12.3; with longer ones, 129x3594 rows by a Zipf law 6.8 / 8.0); at batch 17-32 it is not (250x4090 25 % 4.9 /
-            // 5.3).  The LDS-fed form is left alone where it is resident at once too or stages little.
-            pays = batch > 32 && cols <= 2048 + (size_t)bw && items <= 256 && !(lds && (lds_cols <= 1536 || lds_items <= 256));
+            // Against the fragment form and its copy of x: two to four launch rows are ahead while they stage at most 2048
+            // columns per work item and every item has a compute unit to itself, of rows up to 2048 columns half of one
+            // (us, fragment form / this one: 300x1800 16x64 50 % batch 32 5.6 / 4.6; batch 64, 16x32 tiles: 1000x4090 25 %
+            // 7.5 / 7.0, 1000x4096 50 % (2048 columns) 8.6 / 8.4, 300x4000 64x64 50 % 8.3 / 6.8; with more work items,
+            // 8000x1000 32x32 20 %, batch 32 7.5 / 9.1, 2000x4090 32x32 25 % 9.7 / 12.3; with longer ones, 129x3594 rows by a
+            // Zipf law 6.8 / 8.0); of longer rows at batch 17-32 they are not (250x4090 25 % 4.9 / 5.3).
+            pays = !lds && cols <= 2048 + (size_t)bw && (s.xrow_len <= 2048 ? items < 512 : batch > 32 && items <= 256);
         }
         if (vecs <= 512 && cols <= 8192 && copy_bytes <= 156 * 1024 && pays) return kPathMfmaXrow;
     }
@@ -245,9 +250,14 @@ int fc_row_slices(const FcShape& s, int batch, int want) {
 // block rows use none.
 size_t run_ticket_bytes(const HostPlan& hp, int batch, int x_from) {
     if (hp.max_parts <= 1) return 0;
-    const FcShape s = fc_shape(hp, x_from);
-    const int nbt = fc_batch_tile(s, batch), launch_rows = (batch + nbt - 1) / nbt;
-    return (size_t)4 * kTicketStride * hp.nbr * launch_rows * fc_row_slices(s, batch, hp.row_slices);
+    size_t most = 0;
+    for (int x_vec : {0, 1}) {                       // whatever rows of x the run brings
+        FcShape s = fc_shape(hp, x_from);
+        s.x_vec = x_vec;
+        const int nbt = fc_batch_tile(s, batch), launch_rows = (batch + nbt - 1) / nbt;
+        most = std::max(most, (size_t)4 * kTicketStride * hp.nbr * launch_rows * fc_row_slices(s, batch, hp.row_slices));
+    }
+    return most;
 }
 
 // The counter region of a workspace is sized for the largest number of launch rows any batch up to 64 can have, so
@@ -265,6 +275,8 @@ size_t count_ticket_bytes(const HostPlan& hp) {
     return most;
 }
 
+// (For rows of x that are whole aligned vectors where K is: other rows take launch rows of 8 batch rows instead of 16,
+// which need no more.)
 size_t fc_partial_bytes(const HostPlan& hp, int batch, int x_from) {
     if (hp.max_parts <= 1) return 0;
     const int nbt = fc_batch_tile(fc_shape(hp, x_from), batch);
@@ -286,7 +298,9 @@ static std::string kernel_name(const char* fmt, A... args) {
 }
 
 int launch_fc(const FcLaunch& L, std::string* describe) {
-    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from, L.row_slices, L.K};
+    const int xlen = L.x_block_order ? L.K_pad : L.K;
+    const bool vec_rows = xlen % (16 / elem_size(L.wdtype)) == 0 && L.ldx == xlen && (reinterpret_cast<uintptr_t>(L.x) & 15) == 0;
+    const FcShape shape{L.layout, L.wdtype, L.bh, L.bw, L.lds_tiles, L.chunk_tiles, L.xrow_len, mean_tiles_of(L.T, L.nchunks), L.nchunks, L.x_from, L.row_slices, vec_rows};
     const int path = fc_path(shape, L.batch);
     const bool ml = path == kPathMfmaLds, mx = path == kPathMfmaXrow;
     const int nbt = fc_batch_tile(shape, L.batch);
@@ -332,11 +346,9 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     }
     if (mx) {
         if (L.chunk_tiles > 0xFFFF || L.bh > 64) { set_error("shape outside the kernel's packed arguments"); return PIVOT_E_UNSUPPORTED; }
-        const int xlen = L.x_block_order ? L.K_pad : L.K;
         int kind = mfma_kind(L.wdtype, L.bh, L.bw);
         if (kind == 1 && L.bw == 16 && bhs % 32 != 0) kind = 2;
         // rows that are not whole aligned vectors, densely packed, start anywhere in their first piece of 16 bytes
-        const bool vec_rows = xlen % 8 == 0 && L.ldx == xlen && (reinterpret_cast<uintptr_t>(L.x) & 15) == 0;
         const int vecs = vec_rows ? xlen / 8 : (xlen + 7 + 7) / 8;
         a.xn_vecs = xrow_pack(vecs, vecs * 8 - xlen, L.ldx == xlen, vec_rows);
         const size_t steps_cols = ((size_t)(a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) + 1) * L.bw;
@@ -370,7 +382,6 @@ int launch_fc(const FcLaunch& L, std::string* describe) {
     // 0.2-0.4 us for it).
     if (L.chunk_tiles > 0xFFFF || L.bh > 64 || L.batch > 64) { set_error("shape outside the vector kernel's packed arguments"); return PIVOT_E_UNSUPPORTED; }
     const int vec = 16 / es;
-    const int xlen = L.x_block_order ? L.K_pad : L.K;
     int xres = 0;
     size_t xn_bytes = 0;
     const size_t item_bytes = (size_t)(a.uniform_ct > 0 ? a.uniform_ct : L.chunk_tiles) * bhs * L.bw * es;

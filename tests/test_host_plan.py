@@ -151,6 +151,22 @@ def test_schedule_policy_on_the_workload_shapes():
     assert policy(WL.paper_grid_case(8192, 0.03125, seed=0, wdtype=WL.F32, perms="random"))[2] == 4   # 32 KB items
 
 
+@pytest.mark.parametrize("M,K,bh,bw,frac,batch,form", [
+    (2371, 760, 64, 64, 0.6, 24, "lds"), (7802, 176, 64, 64, 0.3, 8, "lds"),         # more than 256 work items of 64-column tiles
+    (14903, 558, 16, 32, 0.12, 8, "lds"), (9375, 1512, 16, 32, 0.15, 6, "lds"),      # rows that are no whole vectors; 586 work items
+    (1855, 800, 32, 64, 0.05, 16, "lds"),                                            # less than an eighth of the columns staged
+    (2472, 784, 32, 32, 0.2, 16, "xrow"), (900, 744, 16, 64, 0.5, 64, "xrow"), (2700, 1520, 32, 32, 0.3, 24, "xrow"),
+    (2399, 2352, 64, 16, 0.09, 40, "lds"), (1000, 4090, 16, 32, 0.25, 64, "xrow")])
+def test_matrix_core_form_of_short_rows(M, K, bh, bw, frac, batch, form):
+    # the two forms that stage x in LDS, each on its side of the lines measured between them
+    p = WL.gen_fc(M, K, bh, bw, frac, seed=3, mask="balanced", wdtype=WL.F16, batch=1)
+    h = B.pivot_fc_plan(M, K, bh, bw, B.PIVOT_F16, p.Wp, B.PIVOT_W_PIVOTED, p.tile_mask, p.prow, p.pcol, p.bias)
+    try:
+        assert "fc_mfma_%s_kernel" % form in B.pivot_fc_kernel_name(h, batch)
+    finally:
+        B.pivot_fc_plan_destroy(h)
+
+
 def test_source_ordered_gather_lists():
     # the batch 3..16 kernel's gather lists: per piece of the schedule the same (source, staged position) pairs as
     # xidx, ordered by source with padding columns last, packed as source | position << 19; the block-order twin
