@@ -405,6 +405,18 @@ void pivot_mlp_plan_destroy(pivot_mlp_plan_t* plan) {
 
 namespace {
 
+// Whether a workgroup of the one-workgroup form could store outputs over inputs that another one has yet to read: several
+// batch rows whose x and y share memory.  With a launch per layer x is read before y is stored.
+bool group_would_overwrite(const pivot_mlp_plan_t* mp, const void* x, int64_t ldx, const void* y, int64_t ldy, int batch) {
+    if (batch < 2) return false;
+    const HostPlan& f = mp->layers[0]->host;
+    const HostPlan& l = mp->layers.back()->host;
+    const int M = (mp->flags & PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER) ? l.M_pad : l.d.M;
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+    const uintptr_t x1 = x0 + ((size_t)(batch - 1) * ldx + f.d.K) * elem_size(f.d.wdtype), y1 = y0 + ((size_t)(batch - 1) * ldy + M) * 4;
+    return x0 < y1 && y0 < x1;
+}
+
 // Workspace of a chain: [arrival counters of layer 0] [of layer 1] ... [partial sums of layer 0] ... [block-order
 // copy of x (matrix path)] [intermediate 0] ...  The counters come first and their sizes do not depend on the
 // batch, so they are only ever touched as counters, whatever batches the workspace is reused with (they rely on
@@ -455,7 +467,7 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
     const pivot_fc_plan_t* last = plan->layers[Lc - 1];
     if (ldx < plan->layers[0]->host.d.K || ldy < (keep ? last->host.M_pad : last->host.d.M)) { set_error("ldx/ldy too small"); return PIVOT_E_SHAPE; }
     char* ws = reinterpret_cast<char*>(ws_dev);
-    if (plan->group_ok && batch >= plan->group.batch_from)
+    if (plan->group_ok && batch >= plan->group.batch_from && !group_would_overwrite(plan, x_dev, ldx, y_dev, ldy, batch))
         return launch_chain_group(plan->group, x_dev, ldx, plan->layers[0]->dev.pcol_pad, reinterpret_cast<float*>(y_dev), ldy, batch, stream);
     if (batch == 1 && plan->persist_ok) {
         // the whole chain in one launch; intermediates are the plan's own (value, tag) pairs

@@ -104,3 +104,30 @@ def test_batch_rows_equal_single_runs(wdtype, batch):
         B.pivot_mlp_plan_destroy(mlp)
         for h in plans:
             B.pivot_fc_plan_destroy(h)
+
+
+@pytest.mark.parametrize("batch,shift", [(2, 0), (8, 0), (64, 0), (8, 700)])
+def test_outputs_stored_over_the_inputs(batch, shift):
+    # several batch rows whose y lies in the memory of x: every row is read before any is overwritten, as with a
+    # launch per layer (whose bits these are: the one-workgroup form is not taken)
+    probs = WL.config4(seed=56, batch=batch, dims=(256, 200, 144), bh=16, bw=16, frac=0.15)
+    plans = [G.dev_plan(p) for p in probs]
+    res = []
+    for flags, shared in ((0, True), (B.PIVOT_MLP_LAUNCH_PER_LAYER, False)):
+        mlp = B.pivot_mlp_plan(plans, flags)
+        try:
+            st = torch.cuda.current_stream().cuda_stream
+            K, M = probs[0].K, probs[-1].M
+            buf = torch.zeros(batch * K + shift + batch * M, dtype=torch.float32, device="cuda")
+            x = buf[:batch * K].view(batch, K)
+            x.copy_(torch.from_numpy(probs[0].x))
+            y = buf[shift:shift + batch * M].view(batch, M) if shared else torch.empty(batch, M, device="cuda")
+            ws = G.workspace(B.pivot_mlp_workspace_bytes(mlp, batch))
+            B.pivot_mlp_run(mlp, x.data_ptr(), K, y.data_ptr(), M, batch, ws.data_ptr(), ws.numel(), st)
+            torch.cuda.synchronize()
+            res.append(y.clone())
+        finally:
+            B.pivot_mlp_plan_destroy(mlp)
+    for h in plans:
+        B.pivot_fc_plan_destroy(h)
+    assert torch.equal(res[0], res[1])
