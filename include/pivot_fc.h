@@ -285,24 +285,30 @@ int  pivot_fc_run_static(const pivot_fc_plan_t* plan, const void* x_dev, int64_t
  * All layers must share wdtype and device.  Layer plans are borrowed and must
  * outlive the chain plan.
  *
- * Two forms.  A chain of BRC plans of one tile width whose work items
- * are whole block rows, at most 1024 per layer and all resident on the device
- * at once, runs at batch 1 in ONE launch (view.one_launch = 1): workgroup g
- * takes work item g of every layer in turn, an intermediate activation is
- * stored as a (value, launch tag) pair, and the next layer's gather re-reads
- * the pairs it needs until they carry this launch's tag.  The pairs and the
- * launch counters live in device memory owned by the chain plan, so launches
- * of one chain plan must not overlap (one stream, or ordered by events), and
- * nothing else should occupy the device while it runs: its workgroups wait
- * for each other.  A wait that does not end within 2^18 polls gives up, the
- * status word reads 1 and y_dev is undefined; pivot_mlp_status synchronises
- * the stream, returns the status of the launches since its last call and
- * clears it.  Of those, a chain of at most 128 (two layers) or 256 KB of
- * weights that sixteen wavefronts can share out, whose inputs fit beside each
- * other in LDS, runs in one workgroup per batch row, at every batch, from a
- * copy of the weights that the chain plan holds: none of its runs waits for
- * anything and the status stays 0.  Every other chain and batch (or
- * PIVOT_MLP_LAUNCH_PER_LAYER) runs one launch per layer.
+ * Three forms (pivot_mlp_kernel_name tells which one a batch takes).
+ * - A chain of BRC plans of one tile width whose work items are whole block
+ *   rows, at most 1024 per layer and all resident on the device at once, runs
+ *   at batch 1 in ONE launch (view.one_launch = 1): workgroup g takes work item
+ *   g of every layer in turn, an intermediate activation is stored as a (value,
+ *   launch tag) pair, and the next layer's gather re-reads the pairs it needs
+ *   until they carry this launch's tag.  The pairs and the launch counters live
+ *   in device memory owned by the chain plan, so launches of one chain plan must
+ *   not overlap (one stream, or ordered by events), and nothing else should
+ *   occupy the device while it runs: its workgroups wait for each other.  A wait
+ *   that does not end within 2^18 polls gives up, the status word reads 1 and
+ *   y_dev is undefined; pivot_mlp_status synchronises the stream, returns the
+ *   status of the launches since its last call and clears it.
+ * - Of those (view.one_launch = 1 as well), a chain whose weights sixteen
+ *   wavefronts can share out in at most 16 pieces of 1 KB each (8 in a chain of
+ *   two layers: 256 or 128 KB in all), whose first layer has at most 2048
+ *   columns per boundary between layers and whose inputs fit beside each other
+ *   in 60 KB of LDS, runs in one workgroup per batch row, from a copy of the
+ *   weights that the chain plan holds.  At every batch, except that chains of
+ *   three layers with more than 12 pieces (192 KB) take the first form at batch
+ *   1, and that several batch rows whose x and y share memory take the third.
+ *   Runs of this form wait for nothing, may overlap, and leave the status at 0.
+ * - Every other chain and batch (or PIVOT_MLP_LAUNCH_PER_LAYER) runs one launch
+ *   per layer.
  */
 #define PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER 1
 #define PIVOT_MLP_LAUNCH_PER_LAYER       2
@@ -314,7 +320,7 @@ typedef struct pivot_mlp_view {
     const int32_t* const* dst;   /* [L-1] arrays, dst[l] has M_pad_l entries:
                                     dst[l][r] = invpcol_{l+1}[prow_l[r]], -1 in padding        */
     const int32_t* identity;     /* [L-1] flags: 1 if q[l] is the identity                    */
-    int32_t one_launch;          /* 1 if batch-1 runs of this chain take the one-launch form  */
+    int32_t one_launch;          /* 1 if batch-1 runs of this chain take one launch           */
 } pivot_mlp_view;
 
 int    pivot_mlp_plan(pivot_fc_plan_t* const* layers, int L, int flags, pivot_mlp_plan_t** out);
@@ -326,6 +332,12 @@ size_t pivot_mlp_workspace_bytes(const pivot_mlp_plan_t* plan, int batch);
 int    pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx,
                      void* y_dev, int64_t ldy, int batch,
                      void* ws_dev, size_t ws_bytes, void* stream);
+/* Which form pivot_mlp_run takes at this batch, for x and y that share no
+ * memory: "mlp_persist_kernel" (the first, to which the rules on overlapping
+ * launches and on the status apply), "mlp_group_kernel<type, tile width, pieces
+ * per wavefront>" or "launch per layer".  buf receives at most buf_len bytes
+ * including the terminating 0. */
+int    pivot_mlp_kernel_name(const pivot_mlp_plan_t* plan, int batch, char* buf, size_t buf_len);
 /* *status = 0 if every one-launch run of this chain since the last call completed, 1 if a wait gave up. */
 int    pivot_mlp_status(const pivot_mlp_plan_t* plan, void* stream, int* status);
 /* The same information without a synchronising call: *word_dev receives the device address of the chain's

@@ -33,7 +33,7 @@ EXPORTS = [
     "pivot_fc_plan", "pivot_fc_plan_host_view", "pivot_fc_plan_clone", "pivot_fc_plan_destroy",
     "pivot_fc_workspace_bytes", "pivot_workspace_init", "pivot_fc_run", "pivot_fc_run_static", "pivot_fc_kernel_name",
     "pivot_mlp_plan", "pivot_mlp_plan_host_view", "pivot_mlp_plan_destroy",
-    "pivot_mlp_workspace_bytes", "pivot_mlp_run", "pivot_mlp_status", "pivot_mlp_status_word",
+    "pivot_mlp_workspace_bytes", "pivot_mlp_run", "pivot_mlp_kernel_name", "pivot_mlp_status", "pivot_mlp_status_word",
     "pivot_lstm_workspace_bytes", "pivot_lstm_run", "pivot_lstm_status", "pivot_lstm_status_word", "pivot_lstm_restore", "pivot_lstm_kernel_name",
     "pivot_dense_run", "pivot_csr_run", "pivot_null_run", "pivot_stream_read_run", "pivot_exchange_probe_run", "pivot_feedback_search",
 ]
@@ -110,6 +110,7 @@ def lib():
     L.pivot_mlp_workspace_bytes.argtypes = [vp, i32]
     L.pivot_mlp_workspace_bytes.restype = sz
     L.pivot_mlp_run.argtypes = [vp, vp, i64, vp, i64, i32, vp, sz, vp]
+    L.pivot_mlp_kernel_name.argtypes = [vp, i32, C.c_char_p, sz]
     L.pivot_mlp_status.argtypes = [vp, vp, C.POINTER(C.c_int)]
     L.pivot_mlp_status_word.argtypes = [vp, C.POINTER(vp)]
     L.pivot_lstm_status_word.argtypes = [vp, i32, i32, vp, C.POINTER(vp)]
@@ -255,6 +256,13 @@ def pivot_mlp_workspace_bytes(mlp, batch):
 
 def pivot_mlp_run(mlp, x_ptr, ldx, y_ptr, ldy, batch, ws_ptr, ws_bytes, stream=None):
     _check(lib().pivot_mlp_run(mlp, x_ptr, ldx, y_ptr, ldy, batch, ws_ptr, ws_bytes, stream))
+
+
+def pivot_mlp_kernel_name(mlp, batch):
+    """The form pivot_mlp_run takes for this chain at this batch."""
+    buf = C.create_string_buffer(256)
+    _check(lib().pivot_mlp_kernel_name(mlp, batch, buf, 256))
+    return buf.value.decode()
 
 
 def pivot_mlp_status(mlp, stream=None):

@@ -523,6 +523,17 @@ int pivot_mlp_run(const pivot_mlp_plan_t* plan, const void* x_dev, int64_t ldx, 
     return PIVOT_OK;
 }
 
+int pivot_mlp_kernel_name(const pivot_mlp_plan_t* plan, int batch, char* buf, size_t buf_len) {
+    if (!plan || !buf || buf_len == 0) { set_error("plan and buf are required"); return PIVOT_E_NULL; }
+    buf[0] = 0;
+    if (plan->device < 0) { set_error("host-only chain cannot run"); return PIVOT_E_NO_DEVICE; }
+    if (batch < 1 || batch > 64) { set_error("batch %d outside 1..64", batch); return PIVOT_E_SHAPE; }
+    const ChainGroup& g = plan->group;
+    if (plan->group_ok && batch >= g.batch_from) snprintf(buf, buf_len, "mlp_group_kernel<%s, %d, %d>", g.wdtype == PIVOT_F32 ? "float" : "_Float16", g.bw, g.nslots);
+    else snprintf(buf, buf_len, "%s", plan->persist_ok && batch == 1 ? "mlp_persist_kernel" : "launch per layer");
+    return PIVOT_OK;
+}
+
 int pivot_mlp_status(const pivot_mlp_plan_t* plan, void* stream, int* status) {
     if (!plan || !status) { set_error("plan and status are required"); return PIVOT_E_NULL; }
     *status = 0;

@@ -291,7 +291,7 @@ struct pivot_mlp_plan {
     size_t persist_smem = 0, persist_smem_copy = 0;
     uint32_t* persist_ctl = nullptr;
     std::vector<unsigned long long*> persist_pairs;
-    // one-workgroup form of chains whose weights fit its registers, image in dev_base
+    // one-workgroup form of chains whose weights its wavefronts share out, image in dev_base
     bool group_ok = false;
     pivot::ChainGroup group;
 };

@@ -19,7 +19,7 @@ def _layers(probs):
             for p in probs]
 
 
-def _run_chain(probs, flags=0, chunk_tiles=0, repeats=2, want_one_launch=None):
+def _run_chain(probs, flags=0, chunk_tiles=0, repeats=2, want_one_launch=None, form=None):
     plans = [G.dev_plan(p, chunk_tiles=chunk_tiles) for p in probs]
     mlp = B.pivot_mlp_plan(plans, flags)
     try:
@@ -28,6 +28,8 @@ def _run_chain(probs, flags=0, chunk_tiles=0, repeats=2, want_one_launch=None):
             assert view["one_launch"] == int(want_one_launch)
         x = probs[0].x
         batch = x.shape[0]
+        if form is not None:
+            assert form in B.pivot_mlp_kernel_name(mlp, batch)
         xd = torch.from_numpy(x).cuda()
         keep = bool(flags & B.PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER)
         last = probs[-1]
@@ -54,8 +56,8 @@ def _run_chain(probs, flags=0, chunk_tiles=0, repeats=2, want_one_launch=None):
             B.pivot_fc_plan_destroy(h)
 
 
-def _check_chain(probs, flags=0, chunk_tiles=0, want_one_launch=None, repeats=2):
-    y = _run_chain(probs, flags=flags, chunk_tiles=chunk_tiles, want_one_launch=want_one_launch, repeats=repeats)
+def _check_chain(probs, flags=0, chunk_tiles=0, want_one_launch=None, repeats=2, form=None):
+    y = _run_chain(probs, flags=flags, chunk_tiles=chunk_tiles, want_one_launch=want_one_launch, repeats=repeats, form=form)
     bd = np.float16 if probs[0].wdtype == WL.F16 else None
     outs, scales, chain = O.oracle_mlp(_layers(probs), probs[0].x, boundary_dtype=bd, return_all=True)
     assert not np.isnan(y).any()

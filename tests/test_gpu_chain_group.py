@@ -31,6 +31,7 @@ def _in_one_workgroup(probs):
         torch.cuda.synchronize()
         counters = (ctypes.c_uint32 * 1024)()
         assert hip.hipMemcpy(counters, ctypes.c_void_p(B.pivot_mlp_status_word(mlp) - 4096), 4096, 2) == 0
+        assert ("mlp_group_kernel" in B.pivot_mlp_kernel_name(mlp, 1)) == (not any(counters))
         return not any(counters)
     finally:
         B.pivot_mlp_plan_destroy(mlp)
@@ -82,8 +83,20 @@ def test_batch_rows_equal_single_runs(wdtype, batch):
     # a workgroup per batch row: row for row the bits of runs of one, whatever lies between the rows of x and y
     probs = WL.config4(seed=54, batch=batch, dims=(203, 130, 75), bh=16, bw=16, frac=0.15, wdtype=wdtype)
     _check_chain(probs, want_one_launch=True)
-    # three layers of 13-16 wave-loads a wavefront (fp32): from batch 2 on
-    _check_chain(WL.config4(seed=55, batch=batch, dims=(600, 400, 200, 100), bh=64, bw=64, frac=0.1, wdtype=wdtype), want_one_launch=True)
+    # three layers of 13-16 wave-loads a wavefront (fp32): from batch 2 on, at batch 1 in many workgroups that wait
+    three = WL.config4(seed=55, batch=batch, dims=(600, 400, 200, 100), bh=64, bw=64, frac=0.1, wdtype=wdtype)
+    _check_chain(three, want_one_launch=True, form="mlp_group_kernel<%s, 64, %d>" % (("float", 16) if wdtype == WL.F32 else ("_Float16", 8)))
+    plans = [G.dev_plan(p) for p in three]
+    mlp = B.pivot_mlp_plan(plans, 0)
+    try:
+        assert ("mlp_persist_kernel" if wdtype == WL.F32 else "mlp_group_kernel") in B.pivot_mlp_kernel_name(mlp, 1)
+        for bad in (0, 65):
+            with pytest.raises(B.PivotError):
+                B.pivot_mlp_kernel_name(mlp, bad)
+    finally:
+        B.pivot_mlp_plan_destroy(mlp)
+        for h in plans:
+            B.pivot_fc_plan_destroy(h)
     plans = [G.dev_plan(p) for p in probs]
     mlp = B.pivot_mlp_plan(plans, 0)
     try:

@@ -106,6 +106,9 @@ def test_config4_chain_plan_at_full_size_is_bit_exact(eliminated):
     mlp = B.pivot_mlp_plan(plans, 0)
     try:
         mv = B.pivot_mlp_plan_host_view(mlp, views)
+        with pytest.raises(B.PivotError) as e:            # (the form depends on the device)
+            B.pivot_mlp_kernel_name(mlp, 1)
+        assert e.value.code == B.PIVOT_E_NO_DEVICE
     finally:
         B.pivot_mlp_plan_destroy(mlp)
         for h in plans:
