@@ -24,13 +24,13 @@ SHAPES = [(bh, bw) for bh in (8, 16, 32, 64) for bw in (8, 16, 32, 64)]
 @pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
 @pytest.mark.parametrize("bh,bw", SHAPES)
 def test_every_tile_shape_behind_a_boundary(bh, bw, wdtype):
-    # a layer fed by another one takes this kernel from batch 2 on, whatever its size
+    # a layer fed by another one in a launch of its own takes this kernel from batch 2 on, whatever its size
     for i, (batch, chunk) in enumerate([(2, 0), (15, 3), (16, 0), (17, 1), (33, 2), (64, 0)]):
         probs = WL.config4(seed=70 + i, batch=batch, dims=(100, 5 * bw + 3, 3 * bh - 1), bh=bh, bw=bw, frac=0.7, wdtype=wdtype,
                            eliminated=bool(i % 2))
         if i >= 4:
             probs[1].tile_mask[0, :] = 0            # an empty block row
-        err, _ = _check_chain(probs, chunk_tiles=chunk)
+        err, _ = _check_chain(probs, chunk_tiles=chunk, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER)
         print("%s %dx%d batch %d: %.3g" % (wdtype, bh, bw, batch, err), flush=True)
         assert err <= 1e-5 or wdtype == WL.F16
 
@@ -41,7 +41,7 @@ def test_fp32_behind_a_boundary_few_batch_rows(K, M, bh, bw, frac):
     # batches where the choice changes; intermediates in rows or in fragment order
     for i, batch in enumerate((2, 3, 4, 5, 8, 9)):
         probs = WL.config4(seed=60 + i, batch=batch, dims=(50, K, M), bh=bh, bw=bw, frac=frac, eliminated=bool(i % 2))
-        err, _ = _check_chain(probs)
+        err, _ = _check_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER)
         print("%d -> %d %dx%d batch %d: %.3g" % (K, M, bh, bw, batch, err), flush=True)
         assert err <= 1e-5
 
@@ -100,7 +100,7 @@ def test_infinities_reach_the_rows_of_their_tiles_and_stay_infinite(bh, bw, wdty
         c = int(np.flatnonzero(p.tile_mask[br])[-1]) * bw + 2
         j = int(p.pcol[c])
         probs[0].bias[j] = np.inf
-        y = _run_chain(probs)
+        y = _run_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER)
         h, _ = G.oracle_of(probs[0])
         h = h.astype(np.float16 if wdtype == WL.F16 else np.float32).astype(np.float64)
         assert np.isinf(h[:, j]).all() and np.isfinite(np.delete(h, j, axis=1)).all()

@@ -86,7 +86,7 @@ def test_single_layer_chain_equals_fc_run():
 
 def test_fp16_chain_batch16_uses_matrix_cores():
     probs = WL.config4(seed=7, batch=16, dims=(256, 128, 96), wdtype=WL.F16)
-    _check_chain(probs, chunk_tiles=2)
+    _check_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER, chunk_tiles=2)
 
 
 @pytest.mark.parametrize("seed", [0, 1, 2])
@@ -108,13 +108,17 @@ def test_config4_full(eliminated, seed):
                                         (16, 16, (100, 32, 300)),              # most workgroups have no item in the first layer
                                         (16, 32, (64, 300, 40, 130))])         # ... none in the middle layer
 @pytest.mark.parametrize("wdtype", [WL.F32, WL.F16])
-def test_one_launch_chain_batch1(wdtype, eliminated, bh, bw, dims):
+@pytest.mark.parametrize("wide", [False, True])
+def test_one_launch_chain_batch1(wdtype, eliminated, bh, bw, dims, wide):
     # chains whose work items are whole block rows run at batch 1 in ONE launch: intermediates travel as
     # (value, launch tag) pairs.  Ragged M and K (padding rows are never stored, padding columns never waited
-    # for), several tile shapes, 2 to 5 layers, both boundary variants, five launches in a row (a tag per launch)
+    # for), several tile shapes, 2 to 7 layers, both boundary variants, five launches in a row (a tag per launch).
+    # wide: behind a layer too large for the form of small chains in one workgroup, which most of the others take
+    form = "mlp_persist_kernel" if wide else None
+    dims = dims + (1500, 1000) if wide else dims
     probs = WL.config4(seed=21 + bh, dims=dims, eliminated=eliminated, bh=bh, bw=bw, frac=0.4, wdtype=wdtype)
-    _check_chain(probs, want_one_launch=True, repeats=5)
-    _check_chain(probs, flags=B.PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER, want_one_launch=True)
+    _check_chain(probs, want_one_launch=True, repeats=5, form=form)
+    _check_chain(probs, flags=B.PIVOT_MLP_KEEP_FINAL_BLOCK_ORDER, want_one_launch=True, form=form)
     y1 = _run_chain(probs, want_one_launch=True)
     y2 = _run_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER, want_one_launch=False)
     bd = np.float16 if wdtype == WL.F16 else None
@@ -126,7 +130,7 @@ def test_one_launch_chain_long_first_input_copied_into_lds():
     # a first layer whose work items stream more than 48 KB copies x into LDS whole and gathers from there;
     # an x that is not 16-byte aligned takes the element gather instead, with the same result
     probs = WL.config4(seed=33, dims=(4096, 64, 48), frac=0.5)
-    _check_chain(probs, want_one_launch=True, repeats=3)
+    _check_chain(probs, want_one_launch=True, repeats=3, form="mlp_persist_kernel")
     plans = [G.dev_plan(p) for p in probs]
     mlp = B.pivot_mlp_plan(plans, 0)
     try:
@@ -152,10 +156,11 @@ def test_one_launch_chain_in_a_replayed_graph():
     # the launch tag comes from a counter in device memory, so a captured launch gets a fresh tag on every
     # replay with no host work: several replays, eager work in between, every result equal to the eager one
     import bench_util as BU
-    probs = WL.config4(seed=34, dims=(520, 256, 96, 40), frac=0.4)
+    probs = WL.config4(seed=34, dims=(520, 256, 96, 1500, 40), frac=0.4)
     plans = [G.dev_plan(p) for p in probs]
     mlp = B.pivot_mlp_plan(plans, 0)
     try:
+        assert B.pivot_mlp_kernel_name(mlp, 1) == "mlp_persist_kernel"
         xd = torch.from_numpy(probs[0].x).cuda()
         ws = G.workspace(B.pivot_mlp_workspace_bytes(mlp, 1))
         yd = torch.full((1, probs[-1].M), float("nan"), dtype=torch.float32, device="cuda")
@@ -185,22 +190,25 @@ def test_one_launch_chain_in_a_replayed_graph():
             B.pivot_fc_plan_destroy(h)
 
 
-def test_one_launch_chain_degenerate_layers():
+@pytest.mark.parametrize("form,dims", [("mlp_group_kernel", (200, 96, 130, 5)), ("mlp_persist_kernel", (200, 1500, 1000, 96, 130, 5))])
+def test_one_launch_chain_degenerate_layers(form, dims):
     # a middle layer without any kept tile (its outputs are relu(b), still tagged and waited for), an output
     # layer narrower than one tile, and a block row without tiles in the first layer
-    probs = WL.config4(seed=35, dims=(200, 96, 130, 5), frac=0.4)
-    probs[1].tile_mask[:] = 0
+    probs = WL.config4(seed=35, dims=dims, frac=0.4)
+    probs[-2].tile_mask[:] = 0
     probs[0].tile_mask[1, :] = 0
-    _check_chain(probs, want_one_launch=True, repeats=3)
-    _check_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER, want_one_launch=False)
+    _check_chain(probs, want_one_launch=True, repeats=3, form=form)
+    _check_chain(probs, flags=B.PIVOT_MLP_LAUNCH_PER_LAYER, want_one_launch=False, form="launch per layer")
 
 
 def test_one_launch_chain_falls_back():
-    # split block rows and batch > 1 keep one launch per layer
+    # split block rows and (but for small chains) batch > 1 keep one launch per layer
     probs = WL.config4(seed=30, dims=(200, 96, 128), eliminated=False, frac=0.6)
-    _check_chain(probs, chunk_tiles=1, want_one_launch=False)
+    _check_chain(probs, chunk_tiles=1, want_one_launch=False, form="launch per layer")
+    probs3 = WL.config4(seed=32, batch=3, dims=(200, 1500, 1000))
+    _check_chain(probs3, want_one_launch=True, form="launch per layer")
     probs3 = WL.config4(seed=32, batch=3, dims=(200, 96, 128))
-    _check_chain(probs3)                                  # one_launch plan, batch 3: per-layer launches
+    _check_chain(probs3, want_one_launch=True, form="mlp_group_kernel")
     wide = WL.config4(seed=36, dims=(64, 40000, 32), frac=0.5)
     _check_chain(wide, want_one_launch=False)             # 1250 block rows: more work items than the form takes
 
