@@ -1013,7 +1013,7 @@ __host__ __device__ constexpr int xrow_bytes(int vecs) { return ((vecs + 1) | 1)
 inline int xrow_pack(int vecs, int missing, bool packed, bool vec_rows) { return vecs | missing << 10 | (packed ? 1 << 16 : 0) | (vec_rows ? 1 << 17 : 0); }
 inline int xrow_xv(int xn_vecs) { return (xn_vecs & 0x3FF) - ((xn_vecs >> 17) & 1 ? 0 : 1) <= 256 ? 4 : 8; }
 // XV: vectors of one row a lane copies (2 rows per wavefront): with 4 (rows of at most 2048 elements) two workgroups fit the
-// registers of a compute unit, with 8 one does.
+// registers of a compute unit (the kernels' second launch bound: four wavefronts a SIMD), with 8 one does.
 template <int KIND, int BH, int BW, int XV, int OUT>
 __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTail& a) {
     using MF = Mfma<KIND>;
@@ -1198,11 +1198,11 @@ __device__ __forceinline__ void fc_mfma_xrow_body(PIVOT_GEMV_PARAMS, const FcTai
 }
 
 template <int KIND, int BH, int BW, int XV>
-__global__ void __launch_bounds__(512) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
+__global__ void __launch_bounds__(512, XV == 4 ? 4 : 2) fc_mfma_xrow_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_mfma_xrow_body<KIND, BH, BW, XV, kRows>(PIVOT_GEMV_PASS, a);
 }
 template <int KIND, int BH, int BW, int XV>
-__global__ void __launch_bounds__(512) fc_mfma_xrow_chain_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
+__global__ void __launch_bounds__(512, XV == 4 ? 4 : 2) fc_mfma_xrow_chain_kernel(PIVOT_GEMV_PARAMS, FcTail a) {
     fc_mfma_xrow_body<KIND, BH, BW, XV, kFragOrder>(PIVOT_GEMV_PASS, a);
 }
 
