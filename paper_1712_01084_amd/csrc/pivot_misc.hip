@@ -425,7 +425,7 @@ int launch_csr(const int32_t* row_ptr, const int32_t* col, const void* val, int 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float sigmoidf_(float v) { return 1.0f / (1.0f + __expf(-v)); }
 
-// Arguments stay within 64 bytes: a launch whose arguments need more costs the host 0.8 us more.
+// Few arguments: beyond 112 bytes of them a launch costs the host 0.07-0.7 us more (FcTail).
 // flags: batch | fp16 << 8 | fragment order << 9.
 constexpr int lstm_flags(int batch, int wdtype, int frag) { return batch | (wdtype == PIVOT_F16 ? 256 : 0) | (frag ? 512 : 0); }
 
@@ -474,18 +474,21 @@ int launch_lstm_cell(const LstmCellLaunch& L) {
 // group of one batch row; blockIdx.y is the step.
 // What bounds it: the launch and two dependent trips, the group's sources and their values.  All values are asked for
 // together, of fp16 rows x and (in the first step) h for every element, whichever it needs: behind a branch per element
-// they came one trip after the other (2048 units, 1024 inputs, fp16, batch 8: 5.8 -> 2.6 us).  Workgroups of one
-// wavefront, for the few groups there are.
-template <typename WT>
-__global__ void __launch_bounds__(64) lstm_inputs_kernel(const int32_t* __restrict__ pcol_pad, const WT* __restrict__ xs,
+// they came one trip after the other (2048 units, 1024 inputs, fp16, batch 8: 5.8 -> 2.6 us).  NT: threads a workgroup.
+// One wavefront, for the few groups there are, but for those that one workgroup of four covers: the launch behind it
+// then waits for one XCD (a single step, us, one wavefront / four: fp32, 80 to 192 groups of all rows 6.4-6.8 / 5.8-6.2;
+// fp16, 72 to 80 6.6-7.0 / 6.2-6.5, 136 to 192 7.0-7.2 / 7.0-7.5, 256 6.9 / 7.5; 512 and more, fp32 7.6-9.7 / 7.8-10.2,
+// fp16 6.6-8.2 / 7.3-9.7).
+template <typename WT, int NT>
+__global__ void __launch_bounds__(NT) lstm_inputs_kernel(const int32_t* __restrict__ pcol_pad, const WT* __restrict__ xs,
                                                          const float* __restrict__ h0, WT* __restrict__ xg, uint32_t* __restrict__ ctl,
                                                          unsigned step_vecs, int H, int I, int K_pad, int flags) {
     using V = typename Elem<WT>::vec;
     constexpr int VEC = Elem<WT>::VEC;
     const int batch = flags & 0xFF, ngroups = K_pad / VEC;
-    const int i = blockIdx.x * 64 + threadIdx.x, t = blockIdx.y;
+    const int i = blockIdx.x * NT + threadIdx.x, t = blockIdx.y;
     if (t == 0)                                         // (shared out: by one workgroup alone 0.1 us)
-        for (int k = i; k < (int)kLstmCtlBytes / 4; k += (ngroups * batch + 63) / 64 * 64) ctl[k] = 0u;
+        for (int k = i; k < (int)kLstmCtlBytes / 4; k += (ngroups * batch + NT - 1) / NT * NT) ctl[k] = 0u;
     if (i >= ngroups * batch) return;
     const bool frag = (flags & 512) != 0;
     const int g = frag ? i / batch : i % ngroups, b = frag ? i % batch : i / ngroups;
@@ -532,16 +535,22 @@ int launch_lstm_restore(const uint32_t* ctl, const float* saved, float* h, float
     return PIVOT_OK;
 }
 
+template <typename WT, int NT>
+static void launch_lstm_inputs_t(const LstmInputsLaunch& L, int groups, hipStream_t st) {
+    hipLaunchKernelGGL((lstm_inputs_kernel<WT, NT>), dim3((unsigned)((groups + NT - 1) / NT), L.steps), dim3(NT), 0, st, L.pcol_pad, (const WT*)L.xs, L.h0, (WT*)L.xg,
+                       L.ctl, (unsigned)(L.xg_step_bytes / 16), L.H, L.I, L.K_pad, lstm_flags(L.batch, L.wdtype, L.frag));
+}
+
 int launch_lstm_inputs(const LstmInputsLaunch& L) {
     hipStream_t st = reinterpret_cast<hipStream_t>(L.stream);
-    const int es = elem_size(L.wdtype), ngroups = L.K_pad * es / 16;
-    const dim3 grid((unsigned)(((size_t)ngroups * L.batch + 63) / 64), L.steps);
-    const unsigned step_vecs = (unsigned)(L.xg_step_bytes / 16);
-    const int flags = lstm_flags(L.batch, L.wdtype, L.frag);
-    if (L.wdtype == PIVOT_F16)
-        hipLaunchKernelGGL(lstm_inputs_kernel<_Float16>, grid, dim3(64), 0, st, L.pcol_pad, (const _Float16*)L.xs, L.h0, (_Float16*)L.xg, L.ctl, step_vecs, L.H, L.I, L.K_pad, flags);
-    else
-        hipLaunchKernelGGL(lstm_inputs_kernel<float>, grid, dim3(64), 0, st, L.pcol_pad, (const float*)L.xs, L.h0, (float*)L.xg, L.ctl, step_vecs, L.H, L.I, L.K_pad, flags);
+    const int groups = L.K_pad * elem_size(L.wdtype) / 16 * L.batch;
+    if (L.wdtype == PIVOT_F16) {
+        if (groups <= 128) launch_lstm_inputs_t<_Float16, 256>(L, groups, st);
+        else               launch_lstm_inputs_t<_Float16, 64>(L, groups, st);
+    } else {
+        if (groups <= 192) launch_lstm_inputs_t<float, 256>(L, groups, st);
+        else               launch_lstm_inputs_t<float, 64>(L, groups, st);
+    }
     HIP_TRY(hipGetLastError());
     return PIVOT_OK;
 }
