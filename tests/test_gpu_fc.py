@@ -126,18 +126,19 @@ def test_fp16_16_column_tiles_in_16_row_slices_pair_their_tiles(bh, sl, batch):
 
 
 @pytest.mark.parametrize("batch", [5, 8, 9, 12, 16])
-@pytest.mark.parametrize("bh,bw,K", [(64, 16, 1024), (64, 16, 1000), (32, 32, 4096), (16, 64, 333), (64, 64, 2048)])
+@pytest.mark.parametrize("bh,bw,K", [(64, 16, 1024), (64, 16, 1000), (32, 32, 4096), (16, 64, 333), (16, 64, 2333), (64, 64, 2048)])
 def test_fp16_batch_5_to_16_gathers_fragments_from_a_copy_of_x(bh, bw, K, batch):
     # batch 5..16: the rows of x are copied into LDS and every lane gathers the eight values of its B fragment
     # from there.  Rows that are whole aligned vectors are copied with 16-byte loads, anything else (K not a
-    # multiple of 8, a row stride above K, an x that starts off a 16-byte boundary) element by element; rows past
-    # the batch are never read from memory; whole and split block rows, every row-slice form, an empty block row
-    # (batch 5..8 takes this form from a quarter of the columns per AVERAGE work item on, hence the denser mask)
+    # multiple of 8, a row stride above K, an x that starts off a 16-byte boundary) starts late in its first piece; rows
+    # past the batch are never read from memory; whole and split block rows, every row-slice form, an empty block row
+    # (batch 5..8 takes this form from a quarter of the columns per AVERAGE work item on, hence the denser mask; short
+    # rows that are no whole vectors stay with the form that stages the columns of a work item)
     p = WL.gen_fc(3 * bh + 7, K, bh, bw, 0.3 if batch > 8 else 0.5, seed=300 + batch + bh, wdtype=WL.F16, batch=batch, act=WL.ACT_RELU)
     p.tile_mask[1, :] = 0
     plan = G.dev_plan(p)
     try:
-        assert "fc_mfma_xrow_kernel" in B.pivot_fc_kernel_name(plan, batch)
+        assert ("fc_mfma_lds_kernel" if K == 333 else "fc_mfma_xrow_kernel") in B.pivot_fc_kernel_name(plan, batch)
         st = torch.cuda.current_stream().cuda_stream
         ws = G.workspace(B.pivot_fc_workspace_bytes(plan, batch))
         y_ref, D = G.oracle_of(p)

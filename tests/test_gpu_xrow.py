@@ -17,10 +17,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,K,bh,bw,batch", [(100, 4096, 16, 32, 16), (90, 2048, 16, 32, 16), (60, 2047, 32, 32, 16), (70, 2056, 64, 64, 9), (500, 600, 32, 16, 29), (70, 4095, 64, 16, 5), (64, 4089, 32, 16, 13), (2100, 33, 16, 64, 13), (4200, 9, 16, 32, 7),
                                                (1000, 4090, 16, 32, 64), (200, 4095, 64, 16, 33), (300, 4000, 64, 64, 47),   # several launch rows, the last one short
                                                (90, 2048, 16, 32, 64), (90, 1999, 16, 32, 61), (300, 1999, 32, 16, 60), (70, 2047, 16, 64, 64)])   # short rows of any alignment: where the other LDS form does not fit
-def test_rows_of_any_alignment(M, K, bh, bw, batch):
+def test_rows_of_any_alignment(M, K, bh, bw, batch, row_slices=0):
     p = WL.gen_fc(M, K, bh, bw, 0.6 if batch <= 16 else 0.3, seed=5, wdtype=WL.F16, batch=batch, act=WL.ACT_NONE)
     y_ref, D = O.oracle_fc(p.Wp, p.tile_mask, p.prow, p.pcol, p.bias, p.x, bh, bw, p.act, return_scale=True)
-    plan = G.dev_plan(p)
+    plan = G.dev_plan(p, row_slices=row_slices)
     try:
         # (few columns in rows that are no whole vectors: the other LDS form)
         assert ("fc_mfma_xrow_kernel" if K > 64 else "fc_mfma_lds_kernel") in B.pivot_fc_kernel_name(plan, batch)
@@ -37,6 +37,12 @@ def test_rows_of_any_alignment(M, K, bh, bw, batch):
                 assert O.max_scaled_error(y.cpu().numpy(), y_ref, D) <= G.TOL[p.wdtype], (ldx, off)
     finally:
         B.pivot_fc_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("M,K,bh,batch", [(300, 1999, 32, 60), (200, 2041, 64, 64)])
+def test_rows_of_any_alignment_whole_row_blocks(M, K, bh, batch):
+    # 32x32x16 matrix instructions: slices of 32 and 64 rows of 16-column tiles
+    test_rows_of_any_alignment(M, K, bh, 16, batch, row_slices=1)
 
 
 @pytest.mark.parametrize("M,K,bh,bw,frac,batch", [(300, 3000, 16, 32, 0.1, 8), (300, 3001, 64, 16, 0.08, 12), (400, 891, 16, 32, 0.4, 16), (200, 2100, 32, 64, 0.1, 33)])
