@@ -2,8 +2,7 @@
 // one-launch form over many workgroups (pivot_mlp_persist.hip) pays a
 // device-wide exchange of about 1.8 us per boundary, a launch per layer, which
 // larger batches of larger chains take, an empty launch's turnaround and a
-// trip; of a chain this small the whole stream fits the registers of one
-// workgroup, and a boundary is an LDS barrier.  Batch rows meet only in the
+// trip; here a boundary is an LDS barrier.  Batch rows meet only in the
 // caches: each has a compute unit of its own, which reads the weights at the
 // rate it would read them alone.
 //
@@ -11,8 +10,11 @@
 // sixteen wavefronts take them: slot k of wavefront w is the 1 KB at
 // (16 k + w) KB, beside it, per lane, where its piece of the input stands in
 // LDS, where its output goes, and the bias.  No address depends on another
-// load: everything is requested at kernel start, and the launch is one trip to
-// memory, an LDS gather of x and one LDS barrier per layer.  A wavefront takes
+// load: the first eight slots (up to 128 KB, the whole of most chains) and up
+// to 1024 elements of x are requested at kernel start and come in one trip; a
+// later slot is requested when the one eight before it is consumed, further x
+// in turns of 1024 with a trip each.  Then an LDS gather of x and one LDS
+// barrier per layer.  A wavefront takes
 // whole units (the rows of one wave-load of a block row), so no sums cross
 // wavefronts; layer ends fall on the same slot in all of them.  Intermediates
 // of fp16 chains are rounded to fp16 once, like those of the other forms.
