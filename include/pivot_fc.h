@@ -210,7 +210,8 @@ int    pivot_workspace_init(void* ws_dev, size_t ws_bytes, void* stream);
  * tiles, reduce, add bias, activate, scatter through prow.
  *
  *   x_dev  device, [batch][K] of wdtype, row stride ldx elements, natural coordinates
- *   y_dev  device, [batch][M] fp32, row stride ldy elements, natural coordinates
+ *   y_dev  device, [batch][M] fp32, row stride ldy elements, natural coordinates;
+ *          shares no memory with x (outputs are stored while others still read x)
  *   batch  1..64.  F16 plans whose tiles fit an MFMA shape use the matrix
  *          cores from batch 3 on: fed from x-segments staged
  *          in LDS (4 or 8 batch rows per workgroup, gathered through the

@@ -143,11 +143,13 @@ int fc_path(const FcShape& s, int batch) {
             // Rows of at most 2048 columns against the LDS-fed form.  Rows that are whole aligned vectors pay for their copy
             // from an eighth of them staged per work item on, while the work items of the launch run beside each other: two
             // per compute unit, of tiles 64 columns wide one (their time steps from 257 on, 4.1 -> 5.7 us, of tiles 32 wide
-            // at 513; registers and LDS would hold two of either, why the wide ones do not gain is not known).  LDS-fed / this one, us: 784 columns, 32x32 tiles, batch 16, 156 items 4.7 /
-            // 3.9; 1520, 32x32, batch 24, 344 items 6.4 / 5.5; 744, 16x64, batch 64, 212 items 5.8 / 4.5; 760, 64x64, batch
-            // 24, 304 items 4.6 / 6.8; 256 staged of 1512, 16x32, batch 6, 627 items 5.4 / 6.4; 64 staged of 800, 32x64, batch
-            // 16 3.6 / 4.2.  Rows that are not cost it 0.3-0.5 us more and the LDS-fed form, which gathers them from memory,
-            // nothing (729 columns, 32x16, batch 8 3.1 / 4.1; 1056, 64x64, batch 24 3.9 / 4.7).
+            // at 513; registers and LDS would hold two of either, why the wide ones do not gain is not known.  The 256 is a
+            // literal so that a plan made without a device names the same kernel).  LDS-fed / this one, us: 784 columns,
+            // 32x32 tiles, batch 16, 156 items 4.7 / 3.9; 1520, 32x32, batch 24, 344 items 6.4 / 5.5; 744, 16x64, batch 64,
+            // 212 items 5.8 / 4.5; 760, 64x64, batch 24, 304 items 4.6 / 6.8; 256 staged of 1512, 16x32, batch 6, 627 items
+            // 5.4 / 6.4; 64 staged of 800, 32x64, batch 16 3.6 / 4.2.  Rows that are not cost it 0.3-0.5 us more and the
+            // LDS-fed form, which gathers them from memory, nothing (729 columns, 32x16, batch 8 3.1 / 4.1; 713, 64x16,
+            // batch 64 3.4 / 4.4; 795, 64x32, batch 24 3.5 / 4.0).
             // Whatever the rows, at batch 5-16 one copy of 16 rows is ahead where the gathers bound the LDS-fed form, which
             // come again with every row slice and launch row of 8: from 200 K columns staged by all its work items on, with
             // two launch rows from 100 K on while this form has one work item per compute unit, or 1024 by one work item
