@@ -151,15 +151,17 @@ int fc_path(const FcShape& s, int batch) {
             // LDS-fed form, which gathers them from memory, nothing (729 columns, 32x16, batch 8 3.1 / 4.1; 713, 64x16,
             // batch 64 3.4 / 4.4; 795, 64x32, batch 24 3.5 / 4.0).
             // Whatever the rows, at batch 5-16 one copy of 16 rows is ahead where the gathers bound the LDS-fed form, which
-            // come again with every row slice and launch row of 8: from 200 K columns staged by all its work items on, with
-            // two launch rows from 100 K on while this form has one work item per compute unit, or 1024 by one work item
-            // (1481 columns, 32x64, batch 16, 284 items of 1152 7.4 / 5.1; 1284, 64x64, batch 16, 668 of 202 10.4 / 8.1; 1493,
-            // 32x64, batch 16, 364 of 332 5.5 / 4.6; but 1727, 16x64, batch 16, 576 of 256, here 288 items, 6.3 / 7.2).
-            // Of 2038 drawn layers of both kinds the rule is 0.7 % from the better form in the mean.
+            // come again with every row slice and launch row of 8: from 200 K columns staged by all its work items on, 120 K
+            // where it has two launch rows, while this form has at most 512 work items, and from 1024 columns staged by one of
+            // at most 256 on (1481 columns, 32x64, batch 16, 284 items of 1152 7.4 / 5.1; 1284, 64x64, batch 16, 668 of 202
+            // 10.4 / 8.1; 752, 64x64, batch 9, 548 of 276 9.9 / 6.3; 1493, 32x64, batch 16, 364 of 332 5.5 / 4.6; but 1727,
+            // 16x64, batch 16, 576 of 256 6.3 / 7.2; of more than 512 work items, whose partial sums of 16 rows also take twice
+            // the scratch, batch 5-8 lost 1.2x in the mean, up to 1.5x).
+            // Of 2400 drawn layers with rows of both kinds the rule is 0.6 % from the better form in the mean.
             const int slices = mfma_slices(s, batch > 8 && s.row_slices > 2 ? 2 : s.row_slices), launch_rows = batch > 8 ? (batch + 7) / 8 : 1;
             const double staged = (double)s.nchunks * slices * launch_rows * s.mean_tiles * bw;
             pays = (s.x_vec && (size_t)s.chunk_tiles * bw * 8 >= (size_t)s.xrow_len && items <= (bw == 64 ? 256 : 512)) ||
-                   (batch <= 16 && (staged >= 200e3 || (items <= 256 && ((batch > 8 && staged >= 100e3) || s.chunk_tiles * bw >= 1024))));
+                   (batch <= 16 && ((staged >= (batch > 8 ? 120e3 : 200e3) && items <= 512) || (items <= 256 && s.chunk_tiles * bw >= 1024)));
         } else if (batch <= 16) {
             pays = quarter;
         } else {
@@ -168,8 +170,9 @@ int fc_path(const FcShape& s, int batch) {
             // (us, fragment form / this one: 300x1800 16x64 50 % batch 32 5.6 / 4.6; batch 64, 16x32 tiles: 1000x4090 25 %
             // 7.5 / 7.0, 1000x4096 50 % (2048 columns) 8.6 / 8.4, 300x4000 64x64 50 % 8.3 / 6.8; with more work items,
             // 8000x1000 32x32 20 %, batch 32 7.5 / 9.1, 2000x4090 32x32 25 % 9.7 / 12.3; with longer ones, 129x3594 rows by a
-            // Zipf law 6.8 / 8.0); of longer rows at batch 17-32 they are not (250x4090 25 % 4.9 / 5.3).
-            pays = !lds && cols <= 2048 + (size_t)bw && (s.xrow_len <= 2048 ? items < 512 : batch > 32 && items <= 256);
+            // Zipf law 6.8 / 8.0; 64 columns wide, 3724x2024 16x64 7 % batch 32, 466 items 6.35 / 7.5, 1710x1128 22 % batch 64,
+            // 428 items 6.3 / 7.4, 364 items 0.97x); of longer rows at batch 17-32 they are not (250x4090 25 % 4.9 / 5.3).
+            pays = !lds && cols <= 2048 + (size_t)bw && (s.xrow_len <= 2048 ? items < (bw == 64 ? 384 : 512) : batch > 32 && items <= 256);
         }
         if (vecs <= 512 && cols <= 8192 && copy_bytes <= 156 * 1024 && pays) return kPathMfmaXrow;
     }

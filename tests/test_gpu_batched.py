@@ -153,6 +153,25 @@ def test_static_scratch_takes_shorter_launch_rows_where_long_ones_do_not_fit():
         B.pivot_fc_plan_destroy(plan)
 
 
+def test_static_scratch_takes_many_pieces_of_short_rows():
+    # 6400 pieces of 32 rows: partial sums of a launch row of 16 batch rows are 13 MB, of 8, which layers of so many work
+    # items take at this batch, 6.6 MB.  Whole numbers: every order of summation gives the same bits
+    M, K, batch = 12800, 2048, 6
+    rng = np.random.default_rng(85)
+    W = np.ascontiguousarray(np.tile(rng.integers(-2, 3, (77, K)).astype(np.float16), (M // 77 + 1, 1))[:M])
+    x = torch.from_numpy(rng.integers(-2, 3, (batch, K)).astype(np.float16)).cuda()
+    ident = lambda n: np.arange(n, dtype=np.int32)
+    plan = B.pivot_fc_plan(M, K, 32, 32, B.PIVOT_F16, W, B.PIVOT_W_PIVOTED, np.ones((M // 32, K // 32), np.uint8), ident(M), ident(K),
+                           None, chunk_tiles=4, device=0)
+    try:
+        y = torch.full((batch, M), float("nan"), device="cuda")
+        B.pivot_fc_run_static(plan, x.data_ptr(), K, y.data_ptr(), M, batch, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(y, x.float() @ torch.from_numpy(W).cuda().float().t())
+    finally:
+        B.pivot_fc_plan_destroy(plan)
+
+
 def test_static_scratch_without_room_for_the_copy():
     # 64 rows of 50000 fp32 columns are 12.8 MB, more than the built-in scratch holds: the kernels that need no copy run
     p = WL.gen_fc(96, 50000, 32, 32, 0.9, seed=82, batch=64)
